@@ -662,7 +662,7 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     M.pr = part_layout(nR, (int32_t)M.nA);
     M.sl = seg_layout(nL, M.nA, M.plan.q2bits);
     M.sr = seg_layout(nR, M.nA, M.plan.q2bits);
-    M.jl = rjoin_layout(P, M.plan.qbits);
+    M.jl = rjoin_layout(P, M.plan.qbits, nR);
     M.tl = table_layout(nL, P);
     M.ql = probe_layout(nR, P);
     const size_t kL = (size_t)(nL > 0 ? nL : 1), kR = (size_t)(nR > 0 ? nR : 1);
@@ -798,9 +798,9 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     }
 
     // 3. radix join of every sub-bucket in LDS, if every build sub-bucket fits
-    const RJoinWs jw = rjoin_ws(b + M.rjoin_off, M.jl);
+    const RJoinWs jw = rjoin_ws(b + M.rjoin_off, M.jl, P);
     if (e == hipSuccess)
-        e = launch_rjoin_plan(subL, subR, M.S, jw, chunked, stream);
+        e = launch_rjoin_plan(subL, subR, M.S, jw, chunked, d_status, stream);
     if (e == hipSuccess)
         e = launch_rjoin(lk, lv, subL, rk, rv, subR, key_type, P, pl.qbits, jw, o, d_status,
                          chunked, stream);
@@ -811,7 +811,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     // when the whole build side fits it: then they are not launched.
     if (chunked || n_left <= kJoinCap) {
         if (e == hipSuccess)
-            e = launch_merge_finalize(P, pl.qbits, jw, nullptr, o, stream);
+            e = launch_merge_finalize(pl.qbits, jw, nullptr, o, stream);
         return e;
     }
     int64_t *offPL = (int64_t *)(b + M.offPL_off), *offPR = (int64_t *)(b + M.offPR_off);
@@ -819,9 +819,10 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     const ProbeWs w = probe_ws(b + M.probe_off, M.ql);
     if (e == hipSuccess)
         e = launch_fallback_setup(offAL, offAR, 1 << pl.q1bits, P, n_left, n_right, offPL, offPR,
-                                  t.d_offsets, t.d_flags, t.d_bump, w, jw.use, stream);
+                                  t.d_offsets, t.d_flags, t.d_bump, w,
+                                  (const int32_t *)jw.plan_out + 1, stream);
     TView v = make_view(t, t.d_offsets, 0, P);
-    v.skip = jw.use;
+    v.skip = (const int32_t *)jw.plan_out + 1;
     // grids sized to the rows (~16K per workgroup): these launches mostly
     // return at once, and return sooner with fewer workgroups
     auto blocks = [](int64_t rows) { return (int)std::min<int64_t>((rows >> 14) + 1, 1 << 20); };
@@ -831,7 +832,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
         e = launch_probe_group(rk1, rv1, key_type, P, v, 0, w, o, d_status, blocks(n_right),
                                stream);
     if (e == hipSuccess)
-        e = launch_merge_finalize(P, pl.qbits, jw, &w, o, stream);
+        e = launch_merge_finalize(pl.qbits, jw, &w, o, stream);
     return e;
 }
 
@@ -1085,7 +1086,7 @@ struct FusedMerge {
     SegLayout sl = {}, sr = {};
     size_t partL = 0, partR = 0, lk1 = 0, lv1 = 0, rk1 = 0, rv1 = 0, offAL = 0, offAR = 0,
            digL = 0, digR = 0, segL = 0, segR = 0, lk2 = 0, lv2 = 0, rk2 = 0, rv2 = 0, subL = 0,
-           subR = 0, jst = 0, jbase = 0, bytes = 0, base = 0;
+           subR = 0, jst = 0, jcursor = 0, bytes = 0, base = 0;
     int64_t blocks[kSteps] = {};
 };
 
@@ -1134,7 +1135,7 @@ FusedMerge fused_merge(const mdx_merge_desc &d, int32_t idx, const Tuned &t)
     take(F.subL, two ? (size_t)(F.S + 1) * 8 : 0);
     take(F.subR, two ? (size_t)(F.S + 1) * 8 : 0);
     take(F.jst, (size_t)F.S * 8);
-    take(F.jbase, (size_t)F.S * 8);
+    take(F.jcursor, (size_t)d.P * 8);
     F.bytes = o;
     F.blocks[kTiles] = F.pl.ntiles + F.pr.ntiles;
     F.blocks[kScan] = (2 * F.nA + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -1171,7 +1172,7 @@ size_t fixed_bytes(int32_t count)
 // Merges of one key width and tile shape within one wave.
 struct BatchUnit {
     int kt = 0, R = 0, maxD = 1, maxbits = 0;
-    bool dig = false;
+    bool dig = false, by_part = false;  // some merge writes digits / places by partition
     std::vector<int32_t> merges;  // indexes into the FusedMerge list
     int64_t total[kSteps] = {};
     size_t part_off = 0, seg_off = 0, join_off = 0, pre_off[kSteps] = {}, ticket_off = 0;
@@ -1385,7 +1386,7 @@ int32_t mdx_batch_create(int32_t count, const mdx_merge_desc *h_descs,
                 jr.subR = offAR;
             }
             jr.jstatus = (uint64_t *)(b + f.jst);
-            jr.jbase = (int64_t *)(b + f.jbase);
+            jr.jcursor = (uint64_t *)(b + f.jcursor);
             jr.S = f.S;
             jr.o.key = d.d_out_key;
             jr.o.lpay = d.d_out_lpay;
@@ -1396,6 +1397,7 @@ int32_t mdx_batch_create(int32_t count, const mdx_merge_desc *h_descs,
             jr.P = d.P;
             jr.qbits = f.plan.qbits;
             jr.by_part = rjoin_by_partition(f.plan.qbits, rjoin_grid(u.total[kSubs])) ? 1 : 0;
+            u.by_part = u.by_part || jr.by_part;
             memcpy(B->h_image + u.join_off + j * sizeof(JoinRec), &jr, sizeof(jr));
             for (int st = 0; st < kSteps; ++st)
                 pre[st].push_back(pre[st].back() + (uint32_t)f.blocks[st]);
@@ -1405,7 +1407,7 @@ int32_t mdx_batch_create(int32_t count, const mdx_merge_desc *h_descs,
     }
     int launches = B->image_bytes > 0 ? 1 : 0;
     for (const BatchUnit &u : B->units)
-        launches += 4 + (u.total[kSegPlan] > 0 ? 4 : 0) + 3;
+        launches += 4 + (u.total[kSegPlan] > 0 ? 4 : 0) + 2 + (u.by_part ? 1 : 0);
     B->launches = launches;
     B->d_ws = ws;
     (void)hipGetDevice(&B->device);
@@ -1462,7 +1464,7 @@ int32_t mdx_batch_run(mdx_batch *batch, hipStream_t stream)
             e = launch_rjoin_batch((const JoinRec *)(img + u.join_off), M,
                                    (const uint32_t *)(img + u.pre_off[kSubs]),
                                    (uint32_t)u.total[kSubs], (uint32_t *)(img + u.ticket_off), u.kt,
-                                   stream);
+                                   u.by_part, stream);
     }
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }

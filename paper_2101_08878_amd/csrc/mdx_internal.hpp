@@ -247,44 +247,70 @@ constexpr int kJoinBatch = kJoinThreads * kJoinRows;
 #endif
 constexpr double kJoinFill = MDX_JOIN_FILL;
 
-// One chained-scan tile per sub-bucket.
+// A join item: a sub-bucket, or one probe batch of a sub-bucket that holds
+// several (a probe key repeated very often: each of its items builds the
+// table again, which costs a fraction of a batch's count and emit, and runs
+// on a workgroup of its own).  Items are numbered sub-bucket by sub-bucket,
+// batch by batch, and are the tiles of the chained scan.
 struct RJoinLayout {
-    int64_t S;
-    size_t status_off, tile_base_off, misc_off, bytes;
+    int64_t S, max_items;
+    size_t status_off, cursor_off, istart_off, isub_off, plan_off, misc_off, bytes;
 };
 
-inline RJoinLayout rjoin_layout(int32_t P, int qbits)
+constexpr int64_t kPlanChunk = 4096;  // sub-buckets planned per workgroup
+
+inline RJoinLayout rjoin_layout(int32_t P, int qbits, int64_t n_probe)
 {
     RJoinLayout L;
     L.S = (int64_t)P << qbits;
+    L.max_items = L.S + n_probe / kJoinBatch;
     size_t o = 0;
     L.status_off = o;
-    o += align_up((size_t)L.S * sizeof(uint64_t));
-    L.tile_base_off = o;
-    o += align_up((size_t)L.S * sizeof(int64_t));
-    L.misc_off = o;  // ticket (u32), use flag (i32)
-    o += align_up(64);
+    o += align_up((size_t)L.max_items * sizeof(uint64_t));
+    L.cursor_off = o;
+    o += align_up((size_t)P * sizeof(uint64_t));
+    L.istart_off = o;
+    o += align_up((size_t)(L.S + 1) * sizeof(uint32_t));
+    L.isub_off = o;
+    o += align_up((size_t)L.max_items * sizeof(uint32_t));
+    L.plan_off = o;
+    o += align_up((size_t)((L.S + kPlanChunk - 1) / kPlanChunk) * sizeof(uint64_t));
+    L.misc_off = o;  // ticket, plan ticket, then the plan's results
+    o += align_up(256);
     L.bytes = o;
     return L;
 }
 
 struct RJoinWs {
-    uint64_t *status;
-    int64_t *tile_base;
+    uint64_t *status;       // [max_items] chained scan (the first P of them by partition)
+    uint64_t *cursor;       // [P] output cursors (by partition)
+    uint32_t *istart;       // [S + 1] first item of every sub-bucket (valid when items != S)
+    uint32_t *isub;         // [max_items] sub-bucket of every item (likewise)
+    uint64_t *plan;         // chained scan of the planning workgroups
     uint32_t *ticket;
-    int32_t *use;  // 1: every build sub-bucket fits an LDS table
-    int64_t S;
+    uint32_t *plan_ticket;
+    // the plan's results: the number of items, and 1 if every build
+    // sub-bucket fits an LDS table, else 0 (together, for one load)
+    uint32_t *plan_out;
+    int64_t S, max_items;
+    int32_t P;
 };
 
-inline RJoinWs rjoin_ws(void *base, const RJoinLayout &L)
+inline RJoinWs rjoin_ws(void *base, const RJoinLayout &L, int32_t P)
 {
     char *b = (char *)base;
     RJoinWs w;
     w.status = (uint64_t *)(b + L.status_off);
-    w.tile_base = (int64_t *)(b + L.tile_base_off);
+    w.cursor = (uint64_t *)(b + L.cursor_off);
+    w.istart = (uint32_t *)(b + L.istart_off);
+    w.isub = (uint32_t *)(b + L.isub_off);
+    w.plan = (uint64_t *)(b + L.plan_off);
     w.ticket = (uint32_t *)(b + L.misc_off);
-    w.use = (int32_t *)(b + L.misc_off + 16);
+    w.plan_ticket = w.ticket + 1;
+    w.plan_out = w.ticket + 32;  // not on the tickets' cache line
     w.S = L.S;
+    w.max_items = L.max_items;
+    w.P = P;
     return w;
 }
 
@@ -461,23 +487,25 @@ hipError_t launch_join_count(const void *lk, const int64_t *lofs, int64_t n_buil
                              int64_t *off_probe, uint64_t *pcount, int64_t *out_offsets,
                              int32_t *status, hipStream_t s);
 
-// Radix join: plan (the LDS-fit flag from the build sub-buckets, cleared
-// chained scan), join, output offsets.  chunked: a build sub-bucket larger
+// Radix join: plan (the LDS-fit flag from the build sub-buckets, the items,
+// the cleared chained scan), join (which writes the output offsets too,
+// unless it places rows by partition).  chunked: a build sub-bucket larger
 // than a table is joined in table-sized chunks (the flag stays set and no
 // global-table join is needed); otherwise such a sub-bucket clears the flag
 // and the join does nothing.
 hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S,
-                             const RJoinWs &w, bool chunked, hipStream_t s);
+                             const RJoinWs &w, bool chunked, int32_t *status, hipStream_t s);
 hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, const void *rk,
                         const int64_t *rv, const int64_t *subR, int key_bytes, int32_t P,
                         int qbits, const RJoinWs &w, const ProbeOut &o, int32_t *status,
                         bool chunked, hipStream_t s);
 // Radix join of every merge of a batch (one key width): record m describes
-// merge m (its S sub-buckets, its chained scan jstatus/jbase of S entries,
-// output); Spre [M + 1] prefix of the merges' S in device memory, S its
-// total; ticket: a device counter.  Clears the chained scans, joins (a build
-// sub-bucket larger than an LDS table is joined in table-sized chunks), and
-// writes every merge's output offsets.
+// merge m (its S sub-buckets, its chained scan jstatus of S entries and
+// cursors jcursor of P, output); Spre [M + 1] prefix of the merges' S in device memory, S its
+// total; ticket: a device counter; by_part: some merge places its rows by
+// partition.  Clears the chained scans, joins (a build sub-bucket larger than
+// an LDS table is joined in table-sized chunks), and writes every merge's
+// output offsets.
 struct JoinRec {
     const void *lk;
     const int64_t *lv;
@@ -486,7 +514,7 @@ struct JoinRec {
     const int64_t *rv;
     const int64_t *subR;  // [S + 1]
     uint64_t *jstatus;    // [S]
-    int64_t *jbase;       // [S]
+    uint64_t *jcursor;    // [P]
     int64_t S;
     ProbeOut o;
     int32_t *status;
@@ -505,11 +533,12 @@ int rjoin_grid(int64_t S);
 bool rjoin_by_partition(int qbits, int64_t G);
 
 hipError_t launch_rjoin_batch(const JoinRec *recs, int M, const uint32_t *Spre, uint32_t S,
-                              uint32_t *ticket, int key_bytes, hipStream_t s);
+                              uint32_t *ticket, int key_bytes, bool by_part, hipStream_t s);
 
-// A merge's output offsets: the radix join's when it ran, else (pw non-null)
-// the global-table probe's.
-hipError_t launch_merge_finalize(int32_t P, int qbits, const RJoinWs &w, const ProbeWs *pw,
+// A merge's output offsets where the radix join did not write them itself:
+// its partition cursors', or (pw non-null) the global-table probe's when that
+// ran.  Nothing is launched when neither can be.
+hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeWs *pw,
                                  const ProbeOut &o, hipStream_t s);
 
 

@@ -11,9 +11,14 @@
 //   2. counts the output rows of all its probe rows (walking each row's
 //      chain) and takes the output row of its first one (output placement,
 //      below);
-//   3. writes (key, left payload, right payload) rows.  When the probe rows
-//      fit one batch (4096 rows) they stay in registers between 2 and 3;
-//      otherwise they are read and looked up again.
+//   3. writes (key, left payload, right payload) rows; the probe rows stay
+//      in registers between 2 and 3.  A merge's sub-bucket with more probe
+//      rows than one batch (4096: a probe key repeated very often) is taken
+//      one batch per workgroup, each building the table again.  (One
+//      workgroup for all of a sub-bucket's batches, reading them once to
+//      count and once to write, took 16.3 ms of a 1E7 x 5E7 merge whose
+//      probe keys are Zipf(1.1).)  The fused batch joins such a sub-bucket in
+//      one workgroup.
 // Sub-buckets are numbered partition-major, and partition p's output is the
 // contiguous range [out_off[p], out_off[p+1]).  Global memory is only
 // streamed: the random accesses of the join all hit LDS.  The partition
@@ -24,7 +29,7 @@
 //
 // Latency hiding: two workgroups per CU, one running while the other waits
 // on the dependent steps of its sub-bucket; inside a sub-bucket the loads
-// are issued in the order they are needed (join_one_batch), and the hash
+// are issued in the order they are needed (count_one_batch), and the hash
 // chains of a thread's probe rows are walked four at a time without
 // branches, so that their LDS reads are in flight together.
 #include <algorithm>
@@ -75,17 +80,17 @@ __device__ __forceinline__ int64_t uniform(int64_t x)
 // Partition p's output rows form one range, [base(p), base(p+1)); the order
 // of its sub-buckets' rows inside that range is free (row order inside a
 // partition is implementation-defined).  Two ways to place them:
-//  - by sub-bucket: a chained scan over all sub-buckets in ticket order
-//    (pst[s] its status, part[s] its first output row).  A sub-bucket
-//    waits until every sub-bucket ticketed before it has been counted.
-//  - by partition: a sub-bucket takes its rows from its partition's cursor
-//    part[p] with one atomic add (the low kDoneBits count the sub-buckets
-//    counted, the bits above the rows taken), and base(p) is the exclusive
-//    prefix of the partition totals, a chained scan over the P entries of
-//    pst: the last sub-bucket of p to be counted publishes p's total.  A
-//    sub-bucket then waits only while an earlier partition still has
-//    sub-buckets being counted.  The sub-buckets of earlier partitions were
-//    all ticketed before this one, to running workgroups, so the wait ends.
+//  - by sub-bucket: a chained scan over all items in ticket order (pst[t]
+//    the status of item t).  An item waits until every item ticketed before
+//    it has been counted.
+//  - by partition: an item takes its rows from its partition's cursor with
+//    one atomic add (the low kDoneBits count the items counted, the bits
+//    above the rows taken), and base(p) is the exclusive prefix of the
+//    partition totals, a chained scan over the P entries of pst: the last
+//    item of p to be counted publishes p's total.  An item then waits only
+//    while an earlier partition still has items being counted.  The items of
+//    earlier partitions were all ticketed before this one, to running
+//    workgroups, so the wait ends.
 // By partition pays when partitions hold many more sub-buckets than there
 // are workgroups: then few sub-buckets wait at all (1E8 x 1E8 at P = 1:
 // 13.7 instead of 18.4 us per sub-bucket and workgroup).  With partitions
@@ -93,42 +98,56 @@ __device__ __forceinline__ int64_t uniform(int64_t x)
 // the partition before and are all released at once when it completes, and
 // their output writes then contend (21 us per sub-bucket): by sub-bucket.
 struct Place {
-    uint64_t *part;   // by partition: [P] rows taken << kDoneBits | counted;
-                      // by sub-bucket: [S] first output row of each
-    uint64_t *pst;    // [P] or [S]: chained-scan status
-    int32_t qbits;    // 2^qbits sub-buckets per partition (qbits < kDoneBits)
-    int32_t by_part;  // 1: by partition, 0: by sub-bucket
+    uint64_t *cursor;        // by partition: [P] rows taken << kDoneBits | items counted
+    uint64_t *pst;           // [P] or [items]: chained-scan status
+    const uint32_t *istart;  // [S + 1] first item of every sub-bucket; null: item = sub-bucket
+    int64_t nitems;
+    int64_t *offsets;        // [P + 1] output offsets (written here unless by partition)
+    int32_t qbits;           // 2^qbits sub-buckets per partition
+    int32_t by_part;         // 1: by partition, 0: by sub-bucket
 };
-// A merge has at most 2^22 sub-buckets, so the count of a partition's never
-// carries into its rows; the rows taken are kept modulo 2^41 (a carry out
-// of them is lost), and a partition reaching 2^41 output rows (far beyond
-// any output buffer) is reported as an output overflow.
-constexpr int kDoneBits = 23;
+// A merge has at most 2^22 sub-buckets and 2^22 further probe batches (2^34
+// rows), so the count of a partition's items never carries into its rows;
+// the rows taken are kept modulo 2^40 (a carry out of them is lost), and a
+// partition reaching 2^40 output rows (far beyond any output buffer) is
+// reported as an output overflow.
+constexpr int kDoneBits = 24;
 constexpr uint64_t kDoneMask = (1ull << kDoneBits) - 1;
 constexpr uint64_t kRowsLimit = 1ull << (64 - kDoneBits);
 
-// Wave 0 of a workgroup: the output row of sub-bucket s's first row, for its
-// `total` rows.  (cp, cb): the workgroup's last partition and that
-// partition's base, kept across sub-buckets (cp = -1: none yet).
-__device__ inline int64_t place_rows(const Place &pl, int64_t s, int64_t total, int &cp,
-                                     int64_t &cb, int lane, int32_t *status)
+// Wave 0 of a workgroup: the output row of the first row of item t, a batch
+// of sub-bucket s (its first one: `first`), for its `total` rows.  By
+// sub-bucket, the item that starts a partition writes the partition's output
+// offset, and the last one the total.  (cp, cb): the workgroup's last
+// partition and that partition's base, kept across items (cp = -1: none yet).
+__device__ inline int64_t place_rows(const Place &pl, int64_t t, int64_t s, bool first,
+                                     int64_t total, int &cp, int64_t &cb, int lane,
+                                     int32_t *status)
 {
+    const int p = (int)(s >> pl.qbits);
     if (!pl.by_part) {
-        const int64_t ex = lookback(pl.pst, s, total, lane, status);
-        if (lane == 0)
-            pl.part[s] = (uint64_t)ex;
+        const int64_t ex = lookback(pl.pst, t, total, lane, status);
+        if (lane == 0) {
+            if (first && s == (int64_t)p << pl.qbits)
+                pl.offsets[p] = ex;
+            if (t == pl.nitems - 1)
+                pl.offsets[p + 1] = ex + total;
+        }
         return ex;
     }
-    const int p = (int)(s >> pl.qbits);
     uint64_t old = 0;
     if (lane == 0)
-        old = atomicAdd((unsigned long long *)(pl.part + p), ((uint64_t)total << kDoneBits) + 1);
+        old = atomicAdd((unsigned long long *)(pl.cursor + p), ((uint64_t)total << kDoneBits) + 1);
     old = __shfl(old, 0, kWave);
     const uint64_t before = old >> kDoneBits;  // rows of p taken before these
-    if (lane == 0 && ((uint64_t)total >= kRowsLimit || before + (uint64_t)total >= kRowsLimit))
-        or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
-    if (lane == 0 && (old & kDoneMask) + 1 == (1ull << pl.qbits))
-        st_agent(pl.pst + p, kFlagAgg | (before + (uint64_t)total));
+    if (lane == 0) {
+        if ((uint64_t)total >= kRowsLimit || before + (uint64_t)total >= kRowsLimit)
+            or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
+        const int64_t s0 = (int64_t)p << pl.qbits, s1 = (int64_t)(p + 1) << pl.qbits;
+        const uint64_t items = pl.istart ? pl.istart[s1] - pl.istart[s0] : (uint64_t)(s1 - s0);
+        if ((old & kDoneMask) + 1 == items)
+            st_agent(pl.pst + p, kFlagAgg | (before + (uint64_t)total));
+    }
     if (p != cp) {
         bool ok;
         cb = prefix_before(pl.pst, p, lane, status, &ok);
@@ -140,66 +159,172 @@ __device__ inline int64_t place_rows(const Place &pl, int64_t s, int64_t total, 
     return cb + (int64_t)before;
 }
 
-// chunked: oversized build sub-buckets are joined in chunks (the LDS-fit
-// flag stays 1).
-__global__ __launch_bounds__(kBlock) void rj_plan(const int64_t *__restrict__ subL, int64_t S,
-                                                  RJoinWs w, int chunked)
+// ---- plan --------------------------------------------------------------------
+// Items of a sub-bucket: its probe batches, one when there is at most one
+// or nothing to match.
+__device__ __forceinline__ uint32_t items_of(int64_t nb, int64_t nr)
 {
-    int over = 0;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x; s < S; s += stride) {
-        w.status[s] = 0;
-        w.tile_base[s] = 0;
-        over |= (subL[s + 1] - subL[s]) > kJoinCap;
-    }
-    if (over && !chunked)
-        *w.use = 0;  // rj_plan_init set it to 1 before this kernel
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        *w.ticket = 0;
+    return nb > 0 && nr > kJoinBatch ? (uint32_t)((nr + kJoinBatch - 1) / kJoinBatch) : 1u;
 }
 
-__global__ void rj_plan_init(RJoinWs w)
+constexpr int kPlanPerThread = 8;
+static_assert(kPlanChunk == (int64_t)kBlock * kPlanPerThread, "a thread plans 8 sub-buckets");
+
+// Block: sub-buckets [s0, s0 + m), m <= kPlanChunk: exclusive prefix of their
+// items into pre[0..m] (LDS); over: some build side exceeds a table.  Returns
+// the items.  The items are counted with consecutive lanes on consecutive
+// sub-buckets; the prefix is formed only when some sub-bucket has several.
+__device__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t s0, int m,
+                               uint32_t *pre, int64_t *scratch, bool &over)
 {
-    *w.use = 1;
+    const int tid = threadIdx.x;
+    int64_t nb[kPlanPerThread], nr[kPlanPerThread];
+#pragma unroll
+    for (int k = 0; k < kPlanPerThread; ++k) {
+        // indices past the end are clamped: no load behind a branch
+        const int i = k * kBlock + tid;
+        const int64_t c = s0 + (i < m ? i : m - 1);
+        nb[k] = subL[c + 1] - subL[c];
+        nr[k] = subR[c + 1] - subR[c];
+    }
+    int big = 0, over_ = 0;
+#pragma unroll
+    for (int k = 0; k < kPlanPerThread; ++k) {
+        const int i = k * kBlock + tid;
+        const uint32_t ni = items_of(nb[k], nr[k]);
+        big |= ni > 1;
+        over_ |= nb[k] > kJoinCap;
+        if (i < m)
+            pre[i] = ni;
+    }
+    over = __syncthreads_or(over_) != 0;
+    if (!__syncthreads_or(big)) {
+        for (int i = tid; i <= m; i += kBlock)
+            pre[i] = (uint32_t)i;
+        __syncthreads();
+        return m;
+    }
+    uint32_t ni[kPlanPerThread], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPlanPerThread; ++k) {
+        const int i = tid * kPlanPerThread + k;
+        ni[k] = i < m ? pre[i] : 0u;
+        sum += ni[k];
+    }
+    int64_t total;  // (the scan's barriers: every item count has been read)
+    uint32_t run = (uint32_t)block_excl_scan((int64_t)sum, scratch, &total);
+#pragma unroll
+    for (int k = 0; k < kPlanPerThread; ++k) {
+        const int i = tid * kPlanPerThread + k;
+        if (i < m)
+            pre[i] = run;
+        run += ni[k];
+    }
+    if (tid == 0)
+        pre[m] = (uint32_t)total;
+    __syncthreads();
+    return total;
+}
+
+// Block: the item list of those sub-buckets, whose first item is `base`.
+__device__ void plan_list(const RJoinWs &w, int64_t s0, int m, int64_t base, const uint32_t *pre)
+{
+    const int total = (int)pre[m];
+    for (int k = threadIdx.x; k < m; k += kBlock)
+        w.istart[s0 + k] = (uint32_t)base + pre[k];
+    for (int i = threadIdx.x; i < total; i += kBlock) {
+        int l = 0, h = m - 1;  // the last k with pre[k] <= i
+        if (total == m)
+            l = i;
+        else
+            while (l < h) {
+                const int mid = (l + h + 1) >> 1;
+                if (pre[mid] <= (uint32_t)i)
+                    l = mid;
+                else
+                    h = mid - 1;
+            }
+        w.isub[base + i] = (uint32_t)(s0 + l);
+    }
+}
+
+// Chained scan and cursors cleared (whole grid).
+__device__ __forceinline__ void plan_clear(const RJoinWs &w)
+{
+    const int64_t stride = (int64_t)gridDim.x * kBlock, i0 = (int64_t)blockIdx.x * kBlock;
+    for (int64_t i = i0 + threadIdx.x; i < w.max_items; i += stride)
+        w.status[i] = 0;
+    for (int64_t i = i0 + threadIdx.x; i < w.P; i += stride)
+        w.cursor[i] = 0;
+}
+
+// chunked: oversized build sub-buckets are joined in chunks (the LDS-fit
+// flag stays 1).
+__global__ __launch_bounds__(kBlock) void rj_plan(const int64_t *__restrict__ subL,
+                                                  const int64_t *__restrict__ subR, RJoinWs w,
+                                                  int chunked, int32_t *status)
+{
+    __shared__ uint32_t pre[kPlanChunk + 1];
+    __shared__ int64_t scratch[kWavesPerBlock];
+    __shared__ int64_t s_base;
+    __shared__ uint32_t s_chunk;
+    plan_clear(w);
+    if (threadIdx.x == 0)
+        s_chunk = atomicAdd(w.plan_ticket, 1u);
+    __syncthreads();
+    const int64_t b = s_chunk, s0 = b * kPlanChunk;
+    if (s0 >= w.S)
+        return;  // a workgroup that only clears
+    const int m = (int)(w.S - s0 < kPlanChunk ? w.S - s0 : kPlanChunk);
+    bool over;
+    const int64_t total = plan_prefix(subL, subR, s0, m, pre, scratch, over);
+    if (over && !chunked)
+        w.plan_out[1] = 0;  // rj_plan_init set it to 1 before this kernel
+    if (threadIdx.x < kWave) {
+        const int64_t base = lookback(w.plan, b, total, threadIdx.x, status);
+        if (threadIdx.x == 0)
+            s_base = base;
+    }
+    __syncthreads();
+    plan_list(w, s0, m, s_base, pre);
+    if (s0 + m == w.S && threadIdx.x == 0) {
+        w.istart[w.S] = (uint32_t)(s_base + total);
+        w.plan_out[0] = (uint32_t)(s_base + total);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void rj_plan_init(RJoinWs w, int chunks)
+{
+    for (int i = threadIdx.x; i < chunks; i += kBlock)
+        w.plan[i] = 0;
+    if (threadIdx.x == 0) {
+        w.plan_out[1] = 1;
+        *w.ticket = 0;
+        *w.plan_ticket = 0;
+    }
 }
 
 // One block for the whole plan when there are few sub-buckets: the flag is
 // decided by a block-wide OR, so it needs no earlier kernel to set it.
-constexpr int kPlanOnePerThread = 8;
-
-__global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict__ subL, int64_t S,
-                                                      RJoinWs w, int chunked)
+__global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict__ subL,
+                                                      const int64_t *__restrict__ subR, RJoinWs w,
+                                                      int chunked)
 {
-    // Every thread's loads are issued together: indices past S are clamped
-    // to S - 1 (S >= 1) and their results ignored, so no load sits behind a
-    // branch.
-    int64_t a[kPlanOnePerThread], b[kPlanOnePerThread];
-#pragma unroll
-    for (int k = 0; k < kPlanOnePerThread; ++k) {
-        const int64_t s = threadIdx.x + (int64_t)k * kBlock;
-        const int64_t c = s < S ? s : S - 1;
-        a[k] = subL[c];
-        b[k] = subL[c + 1];
-    }
-    int over = 0;
-#pragma unroll
-    for (int k = 0; k < kPlanOnePerThread; ++k) {
-        const int64_t s = threadIdx.x + (int64_t)k * kBlock;
-        over |= s < S && b[k] - a[k] > kJoinCap;
-        if (s < S) {
-            w.status[s] = 0;
-            w.tile_base[s] = 0;
-        }
-    }
-    over = __syncthreads_or(over);
+    __shared__ uint32_t pre[kPlanChunk + 1];
+    __shared__ int64_t scratch[kWavesPerBlock];
+    const int m = (int)w.S;
+    bool over;
+    const int64_t total = plan_prefix(subL, subR, 0, m, pre, scratch, over);
     if (threadIdx.x == 0) {
-        *w.use = over && !chunked ? 0 : 1;
+        w.plan_out[1] = over && !chunked ? 0 : 1;
         *w.ticket = 0;
+        w.plan_out[0] = (uint32_t)total;
+        w.istart[m] = (uint32_t)total;
     }
+    plan_clear(w);
+    if (total != m)
+        plan_list(w, 0, m, 0, pre);
 }
-
-// Sub-buckets up to which rj_plan_one runs.
-constexpr int64_t kPlanOneMax = (int64_t)kBlock * kPlanOnePerThread;
 
 // This thread's rows of the batch starting at rb (the same on every lane),
 // up to re (rb < re): rb + j kJoinThreads + tid.  Rows past re load the
@@ -228,14 +353,14 @@ __device__ __forceinline__ void load_batch(const K *__restrict__ rk, const int64
 // branches: a finished chain sits on the sentinel row, whose link points to
 // itself, so every step issues all G::walk rows' LDS reads at once.
 template <class G, typename K>
-__device__ __forceinline__ void match_batch(int64_t rb, int64_t re, bool any, const int64_t *tkey,
+__device__ __forceinline__ void match_batch(int64_t rb, int64_t re, const int64_t *tkey,
                                             const uint16_t *tn, const uint32_t *head, const K *kk,
                                             uint32_t *mf)
 {
     constexpr uint32_t kSent = Tab<G>::sent;
     constexpr int kWalk = G::walk;
     const int64_t left = re - rb;
-    const uint32_t n = any ? (uint32_t)(left < kJoinBatch ? left : kJoinBatch) : 0u;
+    const uint32_t n = (uint32_t)(left < kJoinBatch ? left : kJoinBatch);
 #pragma unroll
     for (int g = 0; g < kJoinRows; g += kWalk) {
         int64_t h[kWalk];
@@ -406,8 +531,9 @@ struct JoinLds {
     int64_t *s_excl, *s_total;
 };
 
-// The common sub-bucket: its build rows fit one table and its probe rows one
-// batch (0 < nb <= G::cap, 0 < eR - bR <= kJoinBatch).  A wave's loads
+// The common item: its build rows fit one table and its probe rows one batch
+// (0 < nb <= G::cap, 0 < eR - bR <= kJoinBatch): builds the table and counts
+// the matches of every probe row (mf; per-wave sums in L.cw).  A wave's loads
 // complete in the order they were issued, and waiting for one waits for all
 // issued before it; so they are issued in the order they are needed, with
 // no branch around any of them (so that the compiler counts them exactly):
@@ -415,13 +541,12 @@ struct JoinLds {
 // match), then, once the table is built, the probe payloads (needed only to
 // write the output, so they arrive during the count and the chained scan).
 template <class G, typename K>
-__device__ __forceinline__ void join_one_batch(const K *__restrict__ lk,
-                                               const int64_t *__restrict__ lv, int64_t bL,
-                                               int64_t nb, const K *__restrict__ rk,
-                                               const int64_t *__restrict__ rv, int64_t bR,
-                                               int64_t eR, const Place &pl, int64_t s, int &cp,
-                                               int64_t &cb, const ProbeOut &o, int32_t *status,
-                                               const JoinLds &L)
+__device__ __forceinline__ void count_one_batch(const K *__restrict__ lk,
+                                                const int64_t *__restrict__ lv, int64_t bL,
+                                                int64_t nb, const K *__restrict__ rk,
+                                                const int64_t *__restrict__ rv, int64_t bR,
+                                                int64_t eR, const JoinLds &L, K *kk, int64_t *vv,
+                                                uint32_t *mf)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint32_t blast = (uint32_t)nb - 1, plast = (uint32_t)(eR - bR) - 1;
@@ -437,7 +562,6 @@ __device__ __forceinline__ void join_one_batch(const K *__restrict__ lk,
         const uint32_t i = (uint32_t)(j * kJoinThreads + tid);
         bv[j] = __builtin_nontemporal_load(lv + bL + (i < blast ? i : blast));
     }
-    K kk[kJoinRows];
 #pragma unroll
     for (int j = 0; j < kJoinRows; ++j) {
         const uint32_t r = (uint32_t)(j * kJoinThreads + tid);
@@ -457,69 +581,47 @@ __device__ __forceinline__ void join_one_batch(const K *__restrict__ lk,
         }
     }
     __syncthreads();
-    int64_t vv[kJoinRows];
 #pragma unroll
     for (int j = 0; j < kJoinRows; ++j) {
         const uint32_t r = (uint32_t)(j * kJoinThreads + tid);
         vv[j] = __builtin_nontemporal_load(rv + bR + (r < plast ? r : plast));
     }
-
-    uint32_t mf[kJoinRows];
-    match_batch<G>(bR, eR, true, L.tkey, L.tn, L.head, kk, mf);
+    match_batch<G>(bR, eR, L.tkey, L.tn, L.head, kk, mf);
     cell_sums(mf, L.cw, lane, wv);
-    __syncthreads();
-    if (wv == 0) {
-        const int64_t total = cell_scan(L.cw, lane);
-        const int64_t ex = place_rows(pl, s, total, cp, cb, lane, status);
-        if (lane == 0) {
-            *L.s_excl = ex;
-            *L.s_total = total;
-        }
-    }
-    __syncthreads();
-    const int64_t E = *L.s_excl, total = *L.s_total;
-    if (E + total > o.cap) {
-        if (tid == 0 && total > 0)
-            or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
-    } else if (total > 0) {
-        emit_batch<G>(kk, vv, mf, L.cw, E, L.tkey, L.tp, L.tn, (K *)o.key, o.lpay, o.rpay, lane,
-                      wv);
-    }
 }
 
-// Sub-bucket s of one merge: build rows [bL, bL + nb), probe rows [bR, eR).
-// Counts its output rows, takes them from its partition (place_rows), then
-// writes them.  With CHUNKED,
-// a build side larger than the table is joined one table-sized chunk at a
-// time (every chunk against every probe row: each pair of rows meets once);
-// otherwise nb <= G::cap.
-template <class G, typename K, bool CHUNKED>
-__device__ __forceinline__ void join_sub_bucket(const K *__restrict__ lk,
-                                                const int64_t *__restrict__ lv, int64_t bL,
-                                                int64_t nb, const K *__restrict__ rk,
-                                                const int64_t *__restrict__ rv, int64_t bR,
-                                                int64_t eR, const Place &pl, int64_t s, int &cp,
-                                                int64_t &cb, const ProbeOut &o,
-                                                int32_t *status, const JoinLds &L)
+// Item t of one merge, of sub-bucket s (its first item: `first`): build rows
+// [bL, bL + nb), probe rows [bR, eR).  Counts its output rows, takes them
+// (place_rows), then writes them.  Without LOOPS, the build rows fit one
+// table and the probe rows one batch.  With LOOPS a larger build side is
+// joined one table-sized chunk at a time, every chunk against every probe
+// batch (each pair of rows meets once), counting first and writing in a
+// second round.
+template <class G, typename K, bool LOOPS>
+__device__ __forceinline__ void join_item(const K *__restrict__ lk, const int64_t *__restrict__ lv,
+                                          int64_t bL, int64_t nb, const K *__restrict__ rk,
+                                          const int64_t *__restrict__ rv, int64_t bR, int64_t eR,
+                                          const Place &pl, int64_t t, int64_t s, bool first,
+                                          int &cp, int64_t &cb, const ProbeOut &o, int32_t *status,
+                                          const JoinLds &L)
 {
+    constexpr int64_t kCap = G::cap;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     K *out_key = (K *)o.key;
-    const int64_t nbatch = (eR - bR + kJoinBatch - 1) / kJoinBatch;
+    const bool any = nb > 0 && eR > bR;
+    const bool loops = LOOPS && any && (nb > kCap || eR - bR > kJoinBatch);
     K kk[kJoinRows];
     int64_t vv[kJoinRows];
     uint32_t mf[kJoinRows];
 
-    constexpr int64_t kCap = G::cap;
-    if (CHUNKED && nb > kCap && nbatch > 0) {
-        const int64_t nch = (nb + kCap - 1) / kCap;
-        int64_t total = 0;
-        for (int64_t c = 0; c < nch; ++c) {
-            const int64_t c0 = c * kCap;
+    int64_t counted = 0;  // the rows of a looped item
+    if (loops) {
+        for (int64_t c0 = 0; c0 < nb; c0 += kCap) {
             build_table<G>(lk, lv, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
                            L.head);
-            for (int64_t b = 0; b < nbatch; ++b) {
-                load_batch(rk, rv, bR + b * kJoinBatch, eR, kk, vv);
-                match_batch<G>(bR + b * kJoinBatch, eR, true, L.tkey, L.tn, L.head, kk, mf);
+            for (int64_t b = bR; b < eR; b += kJoinBatch) {
+                load_batch(rk, rv, b, eR, kk, vv);
+                match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
                 cell_sums(mf, L.cw, lane, wv);
                 __syncthreads();
                 if (wv == 0) {
@@ -528,111 +630,54 @@ __device__ __forceinline__ void join_sub_bucket(const K *__restrict__ lk,
                         *L.s_total = all;
                 }
                 __syncthreads();
-                total += *L.s_total;
+                counted += *L.s_total;
             }
         }
-        if (wv == 0) {
-            const int64_t ex = place_rows(pl, s, total, cp, cb, lane, status);
-            if (lane == 0)
-                *L.s_excl = ex;
-        }
+    } else if (any) {
+        count_one_batch<G, K>(lk, lv, bL, nb, rk, rv, bR, eR, L, kk, vv, mf);
         __syncthreads();
-        const int64_t E = *L.s_excl;
-        if (E + total > o.cap) {
-            if (tid == 0 && total > 0)
-                or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
-            return;
-        }
-        int64_t run = E;
-        for (int64_t c = 0; c < nch && total > 0; ++c) {
-            const int64_t c0 = c * kCap;
-            build_table<G>(lk, lv, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
-                           L.head);
-            for (int64_t b = 0; b < nbatch; ++b) {
-                load_batch(rk, rv, bR + b * kJoinBatch, eR, kk, vv);
-                match_batch<G>(bR + b * kJoinBatch, eR, true, L.tkey, L.tn, L.head, kk, mf);
-                cell_sums(mf, L.cw, lane, wv);
-                __syncthreads();
-                if (wv == 0) {
-                    const int64_t all = cell_scan(L.cw, lane);
-                    if (lane == 0)
-                        *L.s_total = all;
-                }
-                __syncthreads();
-                emit_batch<G>(kk, vv, mf, L.cw, run, L.tkey, L.tp, L.tn, out_key, o.lpay, o.rpay,
-                              lane, wv);
-                run += *L.s_total;
-                __syncthreads();  // cw, s_total and the table are reused
-            }
-        }
-        return;
     }
-
-    if (nb > 0 && nb <= kCap && nbatch == 1) {
-        join_one_batch<G, K>(lk, lv, bL, nb, rk, rv, bR, eR, pl, s, cp, cb, o, status, L);
-        return;
-    }
-
-    // Any other sub-bucket (no build rows, no probe rows, or probe rows
-    // beyond one batch).
-    const bool any = nb > 0 && nbatch > 0;
-    if (any)
-        build_table<G>(lk, lv, bL, nb, L.tkey, L.tp, L.tn, L.head);
-
-    // Count every probe row's matches.
-    int64_t total = 0;
-    for (int64_t b = 0; b < nbatch; ++b) {
-        load_batch(rk, rv, bR + b * kJoinBatch, eR, kk, vv);
-        match_batch<G>(bR + b * kJoinBatch, eR, any, L.tkey, L.tn, L.head, kk, mf);
-        cell_sums(mf, L.cw, lane, wv);
-        __syncthreads();
-        if (wv == 0) {
-            const int64_t all = cell_total(L.cw, lane);
-            if (lane == 0)
-                *L.s_total = all;
-        }
-        __syncthreads();
-        total += *L.s_total;
-    }
-
-    // Output rows from the partition's cursor.
     if (wv == 0) {
-        const int64_t ex = place_rows(pl, s, total, cp, cb, lane, status);
-        if (lane == 0)
+        const int64_t rows = loops ? counted : (any ? cell_scan(L.cw, lane) : 0);
+        const int64_t ex = place_rows(pl, t, s, first, rows, cp, cb, lane, status);
+        if (lane == 0) {
             *L.s_excl = ex;
+            *L.s_total = rows;
+        }
     }
     __syncthreads();
-    const int64_t E = *L.s_excl;
-
-    // Write the output rows.
+    const int64_t E = *L.s_excl, total = *L.s_total;
+    if (total == 0)
+        return;
     if (E + total > o.cap) {
-        if (tid == 0 && total > 0)
+        if (tid == 0)
             or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
-    } else if (total > 0) {
-        if (nbatch == 1) {
-            if (wv == 0)
-                cell_scan(L.cw, lane);
+        return;
+    }
+    if (!loops) {
+        emit_batch<G>(kk, vv, mf, L.cw, E, L.tkey, L.tp, L.tn, out_key, o.lpay, o.rpay, lane, wv);
+        return;
+    }
+    int64_t run = E;
+    for (int64_t c0 = 0; c0 < nb; c0 += kCap) {
+        __syncthreads();  // s_total has been read, the last chunk's table used
+        build_table<G>(lk, lv, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
+                       L.head);
+        for (int64_t b = bR; b < eR; b += kJoinBatch) {
+            load_batch(rk, rv, b, eR, kk, vv);
+            match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
+            cell_sums(mf, L.cw, lane, wv);
             __syncthreads();
-            emit_batch<G>(kk, vv, mf, L.cw, E, L.tkey, L.tp, L.tn, out_key, o.lpay, o.rpay, lane,
-                          wv);
-        } else {
-            int64_t run = E;
-            for (int64_t b = 0; b < nbatch; ++b) {
-                load_batch(rk, rv, bR + b * kJoinBatch, eR, kk, vv);
-                match_batch<G>(bR + b * kJoinBatch, eR, any, L.tkey, L.tn, L.head, kk, mf);
-                cell_sums(mf, L.cw, lane, wv);
-                __syncthreads();
-                if (wv == 0) {
-                    const int64_t all = cell_scan(L.cw, lane);
-                    if (lane == 0)
-                        *L.s_total = all;
-                }
-                __syncthreads();
-                emit_batch<G>(kk, vv, mf, L.cw, run, L.tkey, L.tp, L.tn, out_key, o.lpay, o.rpay,
-                              lane, wv);
-                run += *L.s_total;
-                __syncthreads();  // cw and s_total are reused by the next batch
+            if (wv == 0) {
+                const int64_t all = cell_scan(L.cw, lane);
+                if (lane == 0)
+                    *L.s_total = all;
             }
+            __syncthreads();
+            emit_batch<G>(kk, vv, mf, L.cw, run, L.tkey, L.tp, L.tn, out_key, o.lpay, o.rpay, lane,
+                          wv);
+            run += *L.s_total;
+            __syncthreads();  // cw, s_total and the table are reused
         }
     }
 }
@@ -641,7 +686,7 @@ __device__ __forceinline__ void join_sub_bucket(const K *__restrict__ lk,
 // with kJoinSimdWaves waves each.
 constexpr int kJoinSimdWaves = kJoinPerCu * kJoinThreads / (4 * kWave);
 
-// Sub-buckets are taken strictly in ticket order, just before each is
+// Items are taken strictly in ticket order, just before each is
 // started: a ticket taken ahead of time would make later sub-buckets wait
 // for it in the chained scan.
 #define MDX_JOIN_LDS(G)                                                                    \
@@ -677,21 +722,31 @@ __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_joi
     const K *__restrict__ rk, const int64_t *__restrict__ rv, const int64_t *__restrict__ subR,
     RJoinWs w, int qbits, int by_part, ProbeOut o, int32_t *status)
 {
-    if (!CHUNKED && *w.use == 0)
-        return;
     MDX_JOIN_LDS(MergeJoin)
-    const int64_t S = w.S;
-    const Place pl = {(uint64_t *)w.tile_base, w.status, qbits, by_part};
+    // no items when the plan found a build side too large; the first ticket is
+    // taken while these loads are under way
+    const int64_t n = !CHUNKED && w.plan_out[1] == 0 ? 0 : w.plan_out[0];
+    const bool split = n != w.S;  // some sub-bucket is several items
+    const Place pl = {w.cursor, w.status, split ? w.istart : nullptr, n, o.offsets, qbits, by_part};
     int cp = -1;
     int64_t cb = 0;
     for (;;) {
-        const int64_t s = take_ticket(w.ticket, &s_next);
-        if (s >= S)
+        const int64_t t = take_ticket(w.ticket, &s_next);
+        if (t >= n)
             break;
+        const int64_t s = split ? w.isub[t] : t;
         const int64_t bL = subL[s], nb = subL[s + 1] - bL;
-        join_sub_bucket<MergeJoin, K, CHUNKED>(lk, lv, bL, nb, rk, rv, subR[s], subR[s + 1], pl,
-                                               s, cp, cb, o, status, L);
-        __syncthreads();  // the table is reused by the next sub-bucket
+        int64_t bR = subR[s], eR = subR[s + 1];
+        bool first = true;
+        if (split) {
+            const int64_t c = t - w.istart[s];
+            first = c == 0;
+            bR += c * kJoinBatch;
+            eR = nb > 0 && bR + kJoinBatch < eR ? bR + kJoinBatch : eR;
+        }
+        join_item<MergeJoin, K, CHUNKED>(lk, lv, bL, nb, rk, rv, bR, eR, pl, t, s, first, cp, cb, o,
+                                         status, L);
+        __syncthreads();  // the table is reused by the next item
     }
 }
 
@@ -723,9 +778,10 @@ __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_joi
         const int64_t s = t - c0;
         const int64_t *subL = r.subL, *subR = r.subR;
         const int64_t bL = subL[s];
-        const Place pl = {(uint64_t *)r.jbase, r.jstatus, r.qbits, r.by_part};
-        join_sub_bucket<BatchJoin, K, true>((const K *)r.lk, r.lv, bL, subL[s + 1] - bL, (const K *)r.rk,
-                                 r.rv, subR[s], subR[s + 1], pl, s, cp, cb, r.o, r.status, L);
+        const Place pl = {r.jcursor, r.jstatus, nullptr, r.S, r.o.offsets, r.qbits, r.by_part};
+        join_item<BatchJoin, K, true>((const K *)r.lk, r.lv, bL, subL[s + 1] - bL, (const K *)r.rk,
+                                      r.rv, subR[s], subR[s + 1], pl, s, s, true, cp, cb, r.o,
+                                      r.status, L);
         __syncthreads();  // the table is reused by the next sub-bucket
     }
 }
@@ -736,32 +792,23 @@ __global__ __launch_bounds__(kBlock) void rj_clear_batch(const JoinRec *__restri
                                                          uint32_t *ticket)
 {
     const JoinRec &r = B[blockIdx.x];
-    for (int64_t s = threadIdx.x; s < r.S; s += kBlock) {
+    for (int64_t s = threadIdx.x; s < r.S; s += kBlock)
         r.jstatus[s] = 0;
-        r.jbase[s] = 0;
-    }
+    for (int p = threadIdx.x; p < r.P; p += kBlock)
+        r.jcursor[p] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *ticket = 0;
 }
 
-// offsets[0..P] from the placement, one block: by sub-bucket, the first
-// output row of each partition's first sub-bucket and the scan's total; by
-// partition, the exclusive prefix of the partition totals (the rows each
-// partition's cursor took).
-__device__ inline void offsets_from_place(const uint64_t *part, const uint64_t *pst, int P,
-                                          int qbits, int64_t S, bool by_part, int64_t *offsets)
+// offsets[0..P] of a placement by partition, one block: the exclusive prefix
+// of the rows each partition's cursor took.
+__device__ inline void offsets_from_cursors(const uint64_t *cursor, int P, int64_t *offsets)
 {
-    if (!by_part) {
-        const int64_t total = (int64_t)(ld_agent(pst + S - 1) & kValMask);
-        for (int p = threadIdx.x; p <= P; p += kBlock)
-            offsets[p] = p < P ? (int64_t)part[(int64_t)p << qbits] : total;
-        return;
-    }
     __shared__ int64_t scratch[kWavesPerBlock];
     int64_t carry = 0;
     for (int b = 0; b < P; b += kBlock) {
         const int p = b + threadIdx.x;
-        const int64_t v = p < P ? (int64_t)(ld_agent(part + p) >> kDoneBits) : 0;
+        const int64_t v = p < P ? (int64_t)(ld_agent(cursor + p) >> kDoneBits) : 0;
         int64_t all;
         const int64_t ex = block_excl_scan(v, scratch, &all);
         if (p < P)
@@ -772,23 +819,24 @@ __device__ inline void offsets_from_place(const uint64_t *part, const uint64_t *
         offsets[P] = carry;
 }
 
-// Block m: merge m's output offsets.
+// Block m: merge m's output offsets (those placed by partition).
 __global__ __launch_bounds__(kBlock) void rj_finalize_batch(const JoinRec *__restrict__ B)
 {
     const JoinRec &r = B[blockIdx.x];
-    offsets_from_place((const uint64_t *)r.jbase, r.jstatus, r.P, r.qbits, r.S, r.by_part != 0,
-                       r.o.offsets);
+    if (r.by_part)
+        offsets_from_cursors(r.jcursor, r.P, r.o.offsets);
 }
 
-// Output offsets of a merge: from the radix join's partition cursors when it
-// ran (*w.use), else from the global-table probe's chained scan (probe tiles,
-// partition-major).
-__global__ __launch_bounds__(kBlock) void merge_finalize(int P, int qbits, int by_part, RJoinWs w,
-                                                         ProbeWs pw, bool fallback, ProbeOut o)
+// Output offsets of a merge that rj_join did not write: from the partition
+// cursors, or from the global-table probe's chained scan (probe tiles,
+// partition-major) when that ran (use flag 0).
+__global__ __launch_bounds__(kBlock) void merge_finalize(int by_part, RJoinWs w, ProbeWs pw,
+                                                         bool fallback, ProbeOut o)
 {
-    if (*w.use != 0) {
-        offsets_from_place((const uint64_t *)w.tile_base, w.status, P, qbits, w.S, by_part != 0,
-                           o.offsets);
+    const int P = w.P;
+    if (w.plan_out[1] != 0) {
+        if (by_part)
+            offsets_from_cursors(w.cursor, P, o.offsets);
     } else if (fallback) {
         const int64_t TT = pw.tile_start[P];
         const int64_t total = TT > 0 ? (int64_t)(ld_agent(pw.status + TT - 1) & kValMask) : 0;
@@ -816,17 +864,17 @@ bool rjoin_by_partition(int qbits, int64_t G)
 }
 
 hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S,
-                             const RJoinWs &w, bool chunked, hipStream_t s)
+                             const RJoinWs &w, bool chunked, int32_t *status, hipStream_t s)
 {
-    (void)subR;
-    if (S <= kPlanOneMax) {
-        hipLaunchKernelGGL(rj_plan_one, dim3(1), dim3(kBlock), 0, s, subL, S, w, (int)chunked);
+    if (S <= kPlanChunk) {
+        hipLaunchKernelGGL(rj_plan_one, dim3(1), dim3(kBlock), 0, s, subL, subR, w, (int)chunked);
         return hipGetLastError();
     }
-    const int64_t cus = device_fill_blocks() / 8 > 0 ? device_fill_blocks() / 8 : 1;
-    const int G = (int)std::min<int64_t>(cus, (S + kBlock - 1) / kBlock + 1);
-    hipLaunchKernelGGL(rj_plan_init, dim3(1), dim3(1), 0, s, w);
-    hipLaunchKernelGGL(rj_plan, dim3(G), dim3(kBlock), 0, s, subL, S, w, (int)chunked);
+    // a workgroup per chunk of sub-buckets, and more to clear the items' status
+    const int chunks = (int)((S + kPlanChunk - 1) / kPlanChunk);
+    const int G = (int)std::max<int64_t>(chunks, std::min<int64_t>(256, w.max_items / kBlock));
+    hipLaunchKernelGGL(rj_plan_init, dim3(1), dim3(kBlock), 0, s, w, chunks);
+    hipLaunchKernelGGL(rj_plan, dim3(G), dim3(kBlock), 0, s, subL, subR, w, (int)chunked, status);
     return hipGetLastError();
 }
 
@@ -836,7 +884,7 @@ void launch_rjoin_kernel(int G, const void *lk, const int64_t *lv, const int64_t
                          const RJoinWs &w, int qbits, const ProbeOut &o, int32_t *status,
                          hipStream_t s)
 {
-    const int by_part = rjoin_by_partition(qbits, G) ? 1 : 0;
+    const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
     if (key_bytes == 8)
         hipLaunchKernelGGL((rj_join<int64_t, CHUNKED>), dim3(G), dim3(kJoinThreads), 0, s,
                            (const int64_t *)lk, lv, subL, (const int64_t *)rk, rv, subR, w, qbits,
@@ -853,7 +901,7 @@ hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, 
                         bool chunked, hipStream_t s)
 {
     (void)P;
-    const int G = rjoin_grid(w.S);
+    const int G = rjoin_grid(w.max_items);
     trace_begin("rj_join", s);
     if (chunked)
         launch_rjoin_kernel<true>(G, lk, lv, subL, rk, rv, subR, key_bytes, w, qbits, o, status,
@@ -866,7 +914,7 @@ hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, 
 }
 
 hipError_t launch_rjoin_batch(const JoinRec *recs, int M, const uint32_t *Spre, uint32_t S,
-                              uint32_t *ticket, int key_bytes, hipStream_t s)
+                              uint32_t *ticket, int key_bytes, bool by_part, hipStream_t s)
 {
     if (M <= 0)
         return hipSuccess;
@@ -880,17 +928,20 @@ hipError_t launch_rjoin_batch(const JoinRec *recs, int M, const uint32_t *Spre, 
         hipLaunchKernelGGL(rj_join_batch<int32_t>, dim3(G), dim3(kJoinThreads), 0, s, recs, Spre,
                            M, ticket);
     trace_end("rj_join", s);
-    hipLaunchKernelGGL(rj_finalize_batch, dim3((unsigned)M), dim3(kBlock), 0, s, recs);
+    if (by_part)
+        hipLaunchKernelGGL(rj_finalize_batch, dim3((unsigned)M), dim3(kBlock), 0, s, recs);
     return hipGetLastError();
 }
 
-hipError_t launch_merge_finalize(int32_t P, int qbits, const RJoinWs &w, const ProbeWs *pw,
+hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeWs *pw,
                                  const ProbeOut &o, hipStream_t s)
 {
     const ProbeWs none = {};
     const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
-    hipLaunchKernelGGL(merge_finalize, dim3(1), dim3(kBlock), 0, s, P, qbits, by_part, w,
-                       pw ? *pw : none, pw != nullptr, o);
+    if (!by_part && !pw)
+        return hipSuccess;
+    hipLaunchKernelGGL(merge_finalize, dim3(1), dim3(kBlock), 0, s, by_part, w, pw ? *pw : none,
+                       pw != nullptr, o);
     return hipGetLastError();
 }
 

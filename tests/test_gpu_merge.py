@@ -11,7 +11,8 @@ import numpy as np
 import pytest
 
 import oracle
-from tests.gpu_util import announce, assert_join_equals_oracle, require_gpu, run_merge
+from tests.gpu_util import (announce, assert_join_equals_oracle, dev, host, require_gpu,
+                            run_merge)
 from tests.helpers import part_np
 from workloads import config_inputs, edge_tables, match_fraction_tables, uniform_tables, zipf_tables
 
@@ -226,3 +227,57 @@ def test_merge_paper_scale_properties(P):
     kl, vl, kr, vr = config_inputs("paper")
     got = run_merge(kl, vl, kr, vr, P, cap=n)
     assert assert_paper_merge(kl, kr, P, got) == 30_000_000
+
+
+@pytest.mark.parametrize("hot", [4095, 4096, 4097, 8192, 8193, 40_961])
+def test_merge_hot_probe_key_items(hot):
+    """A probe key repeated around multiples of a probe batch (4096 rows): its
+    sub-bucket is one join item up to a batch and one per batch beyond it.  A
+    second hot key, absent from the build side, makes items without output."""
+    announce(f"merge hot probe key x {hot}")
+    rng = np.random.default_rng(hot)
+    kl = rng.permutation(60_000).astype(np.int64)
+    kr = np.concatenate([np.full(hot, 31, np.int64), np.full(9000, 70_000, np.int64),
+                         rng.integers(0, 120_000, 30_000)])
+    kr = kr[rng.permutation(kr.size)]
+    vl, vr = np.arange(kl.size, dtype=np.int64), np.arange(kr.size, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    for P in (1, 5):
+        got = run_merge(kl, vl, kr, vr, P, cap=total)
+        assert got["status"] == 0
+        assert_join_equals_oracle(kl, vl, kr, vr, P, got)
+
+
+@pytest.mark.parametrize("P", [1, 3])
+def test_merge_hot_probe_key_many_sub_buckets(P):
+    """The item list over more sub-buckets than one workgroup plans (8192 at
+    P = 1, rows placed by partition; 6144 at P = 3, by sub-bucket), with a
+    tenth of the probe rows on one key."""
+    announce(f"merge hot probe key, many sub-buckets, P={P}")
+    kl, vl, kr, vr = config_inputs("paper", scale=0.13)
+    kr = kr.copy()
+    kr[np.random.default_rng(P).integers(0, kr.size, kr.size // 10)] = 12_345
+    got = run_merge(kl, vl, kr, vr, P)
+    assert_paper_merge(kl, kr, P, got)
+
+
+def test_merge_batch_chunked_hot_items():
+    """A lane merge whose one sub-bucket has more build rows than a table and
+    more probe rows than a batch: chunks and items together."""
+    announce("lanes: hot build and probe key")
+    import torch
+
+    import paper_2101_08878_amd as mdx
+    rng = np.random.default_rng(3)
+    kl = np.concatenate([np.full(3600, 5, np.int64), rng.integers(10, 40_000, 20_000)])
+    kr = np.concatenate([np.full(4200, 5, np.int64), rng.integers(10, 40_000, 10_000)])
+    kl, kr = kl[rng.permutation(kl.size)], kr[rng.permutation(kr.size)]
+    vl, vr = np.arange(kl.size, dtype=np.int64), np.arange(kr.size, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    job = mdx.MergeJob(dev(kl), dev(vl), dev(kr), dev(vr), 4, total, status=status)
+    mdx.mdx_merge_batch([job], lanes=1)
+    torch.cuda.synchronize()
+    got = dict(key=host(job.out[0]), lpay=host(job.out[1]), rpay=host(job.out[2]),
+               off=host(job.out_offsets), status=int(status.item()), cap=total)
+    assert_join_equals_oracle(kl, vl, kr, vr, 4, got)
