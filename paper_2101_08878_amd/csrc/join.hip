@@ -143,16 +143,14 @@ __global__ __launch_bounds__(kBlock) void tbl_init(TView v)
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void tbl_insert(const K *__restrict__ keys,
-                                                     const int64_t *__restrict__ pay, TView v,
-                                                     int32_t *status)
+__global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int32_t *status)
 {
     if (skipped(v.skip))
         return;
     const int64_t o0 = v.off[v.pb], o1 = v.off[v.pe];
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t r = o0 + (int64_t)blockIdx.x * kBlock + threadIdx.x; r < o1; r += stride) {
-        const uint64_t h = fmix64(key_bits(keys[r]));
+        const uint64_t h = fmix64(key_bits(key_at<K>(in, r)));
         const int p = upper_index(v.off, v.pb, v.pe, r);
         if ((int)part_of(h, v.d) != p) {
             or_status(status, MDX_DEV_BAD_PARTITIONING);
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(kBlock) void tbl_insert(const K *__restrict__ keys,
                 if (__hip_atomic_compare_exchange_strong(sp, &expect, h, __ATOMIC_RELAXED,
                                                          __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT)) {
-                    sp[1] = (uint64_t)pay[r];
+                    sp[1] = (uint64_t)pay_at(in, r);
                     break;
                 }
                 w = expect;
@@ -210,12 +208,12 @@ __global__ __launch_bounds__(kBlock) void grp_reset(TView v)
 
 // Slot of row r if r belongs to a repeated-key partition of the view, else -1.
 template <typename K>
-__device__ __forceinline__ int64_t dup_row_slot(const K *keys, const TView &v, int64_t o0,
+__device__ __forceinline__ int64_t dup_row_slot(const Cols &in, const TView &v, int64_t o0,
                                                 int64_t r, int64_t o1)
 {
     if (r >= o1)
         return -1;
-    const uint64_t h = fmix64(key_bits(keys[r]));
+    const uint64_t h = fmix64(key_bits(key_at<K>(in, r)));
     const int p = upper_index(v.off, v.pb, v.pe, r);
     if (!v.flags[p] || (int)part_of(h, v.d) != p)
         return -1;
@@ -268,7 +266,7 @@ __device__ __forceinline__ void agg_rows(const TView &v, int64_t &o0, int64_t &r
 
 // value[s] += rows of the slot's key.
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_count(const K *__restrict__ keys, TView v)
+__global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
 {
     if (skipped(v.skip))
         return;
@@ -285,7 +283,7 @@ __global__ __launch_bounds__(kBlock) void grp_count(const K *__restrict__ keys, 
     agg_rows(v, o0, r0, r1);
     const int64_t o1 = v.off[v.pe];
     for (int64_t r = r0 + threadIdx.x; r < r1; r += kBlock) {
-        const int64_t s = dup_row_slot(keys, v, o0, r, o1);
+        const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
         if (s < 0)
             continue;
         const int e = agg_insert(mkey, s);
@@ -367,8 +365,7 @@ __global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
 // range per slot; then every row takes the next place of its slot's range
 // (rows the map could not hold take a place from the slot directly).
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_scatter(const K *__restrict__ keys,
-                                                      const int64_t *__restrict__ pay, TView v)
+__global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
 {
     if (skipped(v.skip))
         return;
@@ -392,7 +389,7 @@ __global__ __launch_bounds__(kBlock) void grp_scatter(const K *__restrict__ keys
     const int64_t o1 = v.off[v.pe];
     for (int i = threadIdx.x; i < kAggRows; i += kBlock) {
         const int64_t r = r0 + i;
-        const int64_t s = dup_row_slot(keys, v, o0, r, o1);
+        const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
         int e = kRowSkip;
         if (s >= 0) {
             e = agg_insert(mkey, s);
@@ -420,10 +417,10 @@ __global__ __launch_bounds__(kBlock) void grp_scatter(const K *__restrict__ keys
         if (e >= 0) {
             at = mbase[e] + (int64_t)atomicAdd(&mcnt[e], 1u);
         } else {
-            const int64_t s = dup_row_slot(keys, v, o0, r, o1);
+            const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
             at = (int64_t)atomicAdd((unsigned long long *)&v.slots[2 * s + 1], 1ull);
         }
-        v.grouped[at] = pay[r];
+        v.grouped[at] = pay_at(in, r);
     }
 }
 
@@ -489,9 +486,7 @@ __global__ __launch_bounds__(kBlock) void fallback_setup(
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_chain(const K *__restrict__ pk,
-                                                      const int64_t *__restrict__ pv, TView v,
-                                                      int group, ProbeWs w, ProbeOut o,
+__global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int group, ProbeWs w, ProbeOut o,
                                                       int32_t *status)
 {
     if (skipped(v.skip))
@@ -526,8 +521,8 @@ __global__ __launch_bounds__(kBlock) void probe_chain(const K *__restrict__ pk,
         for (int c = 0; c < RP; ++c) {
             const int64_t r = rbeg + (int64_t)c * kBlock + tid;
             const bool valid = r < rend;
-            kk[c] = valid ? __builtin_nontemporal_load(pk + r) : K(0);
-            vv[c] = valid ? __builtin_nontemporal_load(pv + r) : 0;
+            kk[c] = valid ? key_at<K>(in, r) : K(0);
+            vv[c] = valid ? pay_at(in, r) : 0;
         }
 #pragma unroll
         for (int c = 0; c < RP; ++c) {
@@ -626,9 +621,7 @@ __global__ __launch_bounds__(kBlock) void probe_chain(const K *__restrict__ pk,
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_expand(const K *__restrict__ pk,
-                                                       const int64_t *__restrict__ pv, TView v,
-                                                       int group, ProbeWs w, ProbeOut o)
+__global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int group, ProbeWs w, ProbeOut o)
 {
     if (skipped(v.skip))
         return;
@@ -662,9 +655,9 @@ __global__ __launch_bounds__(kBlock) void probe_expand(const K *__restrict__ pk,
                     }
                     const int64_t r = D.rbeg + l;
                     const int64_t at = D.base + q;
-                    out_key[at] = pk[r];
+                    out_key[at] = key_at<K>(in, r);
                     o.lpay[at] = v.grouped[w.row_gs[r] + (q - pre[l])];
-                    o.rpay[at] = pv[r];
+                    o.rpay[at] = pay_at(in, r);
                 }
             }
             __syncthreads();
@@ -920,8 +913,7 @@ static int table_grid(int max_blocks)
 }
 
 template <typename K>
-hipError_t run_build(const K *keys, const int64_t *pay, const TView &v, int64_t rows,
-                     int32_t *status, int max_blocks, hipStream_t s)
+hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *status, int max_blocks, hipStream_t s)
 {
     const int G = table_grid(max_blocks);
     // the grouping kernels' workgroups each take a fixed share of the rows
@@ -934,37 +926,37 @@ hipError_t run_build(const K *keys, const int64_t *pay, const TView &v, int64_t 
     hipLaunchKernelGGL(tbl_init, dim3(G), dim3(kBlock), 0, s, v);
     trace_end("tbl_init", s);
     trace_begin("tbl_insert", s);
-    hipLaunchKernelGGL((tbl_insert<K>), dim3(G), dim3(kBlock), 0, s, keys, pay, v, status);
+    hipLaunchKernelGGL((tbl_insert<K>), dim3(G), dim3(kBlock), 0, s, in, v, status);
     trace_end("tbl_insert", s);
     hipLaunchKernelGGL(grp_reset, dim3(G), dim3(kBlock), 0, s, v);
     trace_begin("grp_count", s);
-    hipLaunchKernelGGL((grp_count<K>), dim3(Gr), dim3(kBlock), 0, s, keys, v);
+    hipLaunchKernelGGL((grp_count<K>), dim3(Gr), dim3(kBlock), 0, s, in, v);
     trace_end("grp_count", s);
     trace_begin("grp_alloc", s);
     hipLaunchKernelGGL(grp_alloc, dim3(Gs), dim3(kBlock), 0, s, v);
     trace_end("grp_alloc", s);
     trace_begin("grp_scatter", s);
-    hipLaunchKernelGGL((grp_scatter<K>), dim3(Gr), dim3(kBlock), 0, s, keys, pay, v);
+    hipLaunchKernelGGL((grp_scatter<K>), dim3(Gr), dim3(kBlock), 0, s, in, v);
     trace_end("grp_scatter", s);
     return hipGetLastError();
 }
 
 template <typename K>
-hipError_t run_probe_group(const K *pk, const int64_t *pv, const TView &v, int group,
+hipError_t run_probe_group(const Cols &in, const TView &v, int group,
                            const ProbeWs &w, const ProbeOut &o, int32_t *status, int max_blocks,
                            hipStream_t s)
 {
     const int G = table_grid(max_blocks);
     trace_begin("probe_chain", s);
-    hipLaunchKernelGGL((probe_chain<K>), dim3(G), dim3(kBlock), 0, s, pk, pv, v, group, w, o,
+    hipLaunchKernelGGL((probe_chain<K>), dim3(G), dim3(kBlock), 0, s, in, v, group, w, o,
                        status);
     trace_end("probe_chain", s);
     // The expansion's work is the output rows, which can be millions for one
     // probe row: it always gets a full device (it returns at once when no
     // tile deferred rows).
     trace_begin("probe_expand", s);
-    hipLaunchKernelGGL((probe_expand<K>), dim3(table_grid(0)), dim3(kBlock), 0, s, pk, pv, v,
-                       group, w, o);
+    hipLaunchKernelGGL((probe_expand<K>), dim3(table_grid(0)), dim3(kBlock), 0, s, in, v, group,
+                       w, o);
     trace_end("probe_expand", s);
     return hipGetLastError();
 }
@@ -1020,12 +1012,12 @@ hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab
     return hipGetLastError();
 }
 
-hipError_t launch_build(const void *keys, const int64_t *pay, int key_bytes, const TView &v,
-                        int64_t rows, int32_t *status, int max_blocks, hipStream_t s)
+hipError_t launch_build(const Cols &table, int key_bytes, const TView &v, int64_t rows,
+                        int32_t *status, int max_blocks, hipStream_t s)
 {
     if (key_bytes == 8)
-        return run_build<int64_t>((const int64_t *)keys, pay, v, rows, status, max_blocks, s);
-    return run_build<int32_t>((const int32_t *)keys, pay, v, rows, status, max_blocks, s);
+        return run_build<int64_t>(table, v, rows, status, max_blocks, s);
+    return run_build<int32_t>(table, v, rows, status, max_blocks, s);
 }
 
 hipError_t launch_fallback_setup(const int64_t *offAL, const int64_t *offAR, int stride,
@@ -1046,16 +1038,14 @@ hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const Pr
     return hipGetLastError();
 }
 
-hipError_t launch_probe_group(const void *pkeys, const int64_t *ppay, int key_bytes, int32_t P,
+hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
                               const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
                               int32_t *status, int max_blocks, hipStream_t s)
 {
     (void)P;
     if (key_bytes == 8)
-        return run_probe_group<int64_t>((const int64_t *)pkeys, ppay, v, group, w, o, status,
-                                        max_blocks, s);
-    return run_probe_group<int32_t>((const int32_t *)pkeys, ppay, v, group, w, o, status,
-                                    max_blocks, s);
+        return run_probe_group<int64_t>(table, v, group, w, o, status, max_blocks, s);
+    return run_probe_group<int32_t>(table, v, group, w, o, status, max_blocks, s);
 }
 
 hipError_t launch_probe_finalize(int32_t P, const ProbeWs &w, const ProbeOut &o,

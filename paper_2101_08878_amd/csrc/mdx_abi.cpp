@@ -249,7 +249,7 @@ int32_t mdx_hash_partition(const void *d_keys, const int64_t *d_payload, int64_t
         return fail(MDX_ERR_WORKSPACE, "mdx_hash_partition: workspace needs " +
                                            std::to_string(L.bytes) + " bytes");
     const PartArgs t = {d_keys, d_payload, n, d_keys_out, d_payload_out, d_offsets, nullptr, d_ws};
-    hipError_t e = launch_partition(&t, 1, key_type, P, 0, 0, 0, stream);
+    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
 
@@ -320,7 +320,7 @@ int32_t mdx_hash_partition_noalloc(const void *d_keys, const int64_t *d_payload,
     if (int32_t e = scratch_address(&ws, W))
         return e;
     const PartArgs t = {d_keys, d_payload, n, d_keys_out, d_payload_out, d_offsets, nullptr, ws};
-    hipError_t e = launch_partition(&t, 1, key_type, P, 0, 0, 0, stream);
+    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
 
@@ -406,7 +406,7 @@ int32_t mdx_join_build(const void *d_keys, const int64_t *d_payload, const int64
     hipError_t e = launch_table_setup(d_offsets, n, t.d_offsets, t.d_flags, t.d_bump, P, stream);
     if (e != hipSuccess)
         return hip_fail(e, W);
-    e = launch_build(d_keys, d_payload, key_type, make_view(t, t.d_offsets, 0, P), n, d_status, 0,
+    e = launch_build(cols_of(d_keys, d_payload, key_type), key_type, make_view(t, t.d_offsets, 0, P), n, d_status, 0,
                      stream);
     if (e != hipSuccess)
         return hip_fail(e, W);
@@ -485,7 +485,7 @@ int32_t mdx_join_probe(const mdx_table *h_table, const void *d_keys, const int64
     o.offsets = d_out_offsets;
     hipError_t e = launch_probe_plan(d_offsets, n, P, w, nullptr, stream);
     if (e == hipSuccess)
-        e = launch_probe_group(d_keys, d_payload, kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o,
+        e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o,
                                d_status, 0, stream);
     if (e == hipSuccess)
         e = launch_probe_finalize(P, w, o, nullptr, stream);
@@ -645,9 +645,8 @@ struct MergeLayout {
     RJoinLayout jl;
     TableLayout tl;
     ProbeLayout ql;
-    size_t partL_off, partR_off, lk1_off, lv1_off, rk1_off, rv1_off, offAL_off, offAR_off,
-        offPL_off, offPR_off, digL_off, digR_off, segL_off, segR_off, lk2_off, lv2_off, rk2_off,
-        rv2_off, subL_off, subR_off, rjoin_off, table_off, probe_off, bytes;
+    size_t partL_off, partR_off, l1_off, r1_off, offAL_off, offAR_off, offPL_off, offPR_off,
+        digL_off, digR_off, segL_off, segR_off, l2_off, r2_off, subL_off, subR_off, rjoin_off, table_off, probe_off, bytes;
 };
 
 // chunked: the merge joins oversized build sub-buckets in chunks and has no
@@ -674,10 +673,8 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     };
     take(M.partL_off, M.pl.bytes);
     take(M.partR_off, M.pr.bytes);
-    take(M.lk1_off, kL * kt);
-    take(M.lv1_off, kL * 8);
-    take(M.rk1_off, kR * kt);
-    take(M.rv1_off, kR * 8);
+    take(M.l1_off, rows_bytes((int64_t)kL, kt));
+    take(M.r1_off, rows_bytes((int64_t)kR, kt));
     take(M.offAL_off, (size_t)(M.nA + 1) * 8);
     take(M.offAR_off, (size_t)(M.nA + 1) * 8);
     take(M.offPL_off, (size_t)(P + 1) * 8);
@@ -686,10 +683,8 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     take(M.digR_off, two ? kR + 4 : 0);
     take(M.segL_off, two ? M.sl.bytes : 0);
     take(M.segR_off, two ? M.sr.bytes : 0);
-    take(M.lk2_off, two ? kL * kt : 0);
-    take(M.lv2_off, two ? kL * 8 : 0);
-    take(M.rk2_off, two ? kR * kt : 0);
-    take(M.rv2_off, two ? kR * 8 : 0);
+    take(M.l2_off, two ? rows_bytes((int64_t)kL, kt) : 0);
+    take(M.r2_off, two ? rows_bytes((int64_t)kR, kt) : 0);
     take(M.subL_off, two ? (size_t)(M.S + 1) * 8 : 0);
     take(M.subR_off, two ? (size_t)(M.S + 1) * 8 : 0);
     take(M.rjoin_off, M.jl.bytes);
@@ -758,8 +753,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     char *b = (char *)d_ws;
     const MergePlan &pl = M.plan;
     const int nA = (int)M.nA;
-    void *lk1 = b + M.lk1_off, *rk1 = b + M.rk1_off;
-    int64_t *lv1 = (int64_t *)(b + M.lv1_off), *rv1 = (int64_t *)(b + M.rv1_off);
+    void *l1 = b + M.l1_off, *r1 = b + M.r1_off;
     int64_t *offAL = (int64_t *)(b + M.offAL_off), *offAR = (int64_t *)(b + M.offAR_off);
     int32_t *d_status = d.d_status;
     ProbeOut o;
@@ -775,24 +769,21 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     uint8_t *digL = two ? (uint8_t *)(b + M.digL_off) : nullptr;
     uint8_t *digR = two ? (uint8_t *)(b + M.digR_off) : nullptr;
     const PartArgs pt[2] = {
-        {d.d_left_keys, d.d_left_payload, n_left, lk1, lv1, offAL, digL, b + M.partL_off},
-        {d.d_right_keys, d.d_right_payload, n_right, rk1, rv1, offAR, digR, b + M.partR_off}};
-    hipError_t e = launch_partition(pt, 2, key_type, P, pl.q1bits, pl.q1bits, pl.q2bits, stream);
+        {d.d_left_keys, d.d_left_payload, n_left, l1, nullptr, offAL, digL, b + M.partL_off},
+        {d.d_right_keys, d.d_right_payload, n_right, r1, nullptr, offAR, digR, b + M.partR_off}};
+    hipError_t e = launch_partition(pt, 2, key_type, P, pl.q1bits, true, pl.q1bits, pl.q2bits, stream);
 
     // 2. split every first-pass bucket by the next q2bits: sub-buckets
-    const void *lk = lk1, *rk = rk1;
-    const int64_t *lv = lv1, *rv = rv1, *subL = offAL, *subR = offAR;
+    const void *lrows = l1, *rrows = r1;
+    const int64_t *subL = offAL, *subR = offAR;
     if (two && e == hipSuccess) {
-        void *lk2 = b + M.lk2_off, *rk2 = b + M.rk2_off;
-        int64_t *lv2 = (int64_t *)(b + M.lv2_off), *rv2 = (int64_t *)(b + M.rv2_off);
+        void *l2 = b + M.l2_off, *r2 = b + M.r2_off;
         int64_t *sL = (int64_t *)(b + M.subL_off), *sR = (int64_t *)(b + M.subR_off);
-        const SegArgs st[2] = {{lk1, lv1, digL, n_left, offAL, lk2, lv2, sL, b + M.segL_off},
-                               {rk1, rv1, digR, n_right, offAR, rk2, rv2, sR, b + M.segR_off}};
+        const SegArgs st[2] = {{l1, digL, n_left, offAL, l2, sL, b + M.segL_off},
+                               {r1, digR, n_right, offAR, r2, sR, b + M.segR_off}};
         e = launch_seg_partition(st, 2, key_type, nA, pl.q1bits, pl.q2bits, stream);
-        lk = lk2;
-        rk = rk2;
-        lv = lv2;
-        rv = rv2;
+        lrows = l2;
+        rrows = r2;
         subL = sL;
         subR = sR;
     }
@@ -802,8 +793,8 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     if (e == hipSuccess)
         e = launch_rjoin_plan(subL, subR, M.S, jw, chunked, d_status, stream);
     if (e == hipSuccess)
-        e = launch_rjoin(lk, lv, subL, rk, rv, subR, key_type, P, pl.qbits, jw, o, d_status,
-                         chunked, stream);
+        e = launch_rjoin(lrows, n_left, subL, rrows, n_right, subR, key_type, P, pl.qbits, jw, o, d_status, chunked,
+                         stream);
 
     // 4. otherwise (a sub-bucket too large for LDS: heavy key repetition),
     // the global-table join over the first-pass output; its kernels do
@@ -827,9 +818,9 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     // return at once, and return sooner with fewer workgroups
     auto blocks = [](int64_t rows) { return (int)std::min<int64_t>((rows >> 14) + 1, 1 << 20); };
     if (e == hipSuccess)
-        e = launch_build(lk1, lv1, key_type, v, n_left, d_status, blocks(n_left), stream);
+        e = launch_build(cols_of_rows(l1, n_left, key_type), key_type, v, n_left, d_status, blocks(n_left), stream);
     if (e == hipSuccess)
-        e = launch_probe_group(rk1, rv1, key_type, P, v, 0, w, o, d_status, blocks(n_right),
+        e = launch_probe_group(cols_of_rows(r1, n_right, key_type), key_type, P, v, 0, w, o, d_status, blocks(n_right),
                                stream);
     if (e == hipSuccess)
         e = launch_merge_finalize(pl.qbits, jw, &w, o, stream);
@@ -1084,8 +1075,8 @@ struct FusedMerge {
     int R = 0, kt = 0, wave = 0;
     PartLayout pl = {}, pr = {};
     SegLayout sl = {}, sr = {};
-    size_t partL = 0, partR = 0, lk1 = 0, lv1 = 0, rk1 = 0, rv1 = 0, offAL = 0, offAR = 0,
-           digL = 0, digR = 0, segL = 0, segR = 0, lk2 = 0, lv2 = 0, rk2 = 0, rv2 = 0, subL = 0,
+    size_t partL = 0, partR = 0, l1 = 0, r1 = 0, offAL = 0, offAR = 0,
+           digL = 0, digR = 0, segL = 0, segR = 0, l2 = 0, r2 = 0, subL = 0,
            subR = 0, jst = 0, jcursor = 0, bytes = 0, base = 0;
     int64_t blocks[kSteps] = {};
 };
@@ -1110,7 +1101,8 @@ FusedMerge fused_merge(const mdx_merge_desc &d, int32_t idx, const Tuned &t)
         F.sr = seg_layout(d.n_right, F.nA, F.plan.q2bits);
     }
     const size_t kL = (size_t)(d.n_left > 0 ? d.n_left : 1),
-                 kR = (size_t)(d.n_right > 0 ? d.n_right : 1), kt = (size_t)d.key_type;
+                 kR = (size_t)(d.n_right > 0 ? d.n_right : 1);
+    const size_t bL = rows_bytes((int64_t)kL, d.key_type), bR = rows_bytes((int64_t)kR, d.key_type);
     size_t o = 0;
     auto take = [&](size_t &field, size_t bytes) {
         field = o;
@@ -1118,20 +1110,16 @@ FusedMerge fused_merge(const mdx_merge_desc &d, int32_t idx, const Tuned &t)
     };
     take(F.partL, F.pl.bytes);
     take(F.partR, F.pr.bytes);
-    take(F.lk1, kL * kt);
-    take(F.lv1, kL * 8);
-    take(F.rk1, kR * kt);
-    take(F.rv1, kR * 8);
+    take(F.l1, bL);
+    take(F.r1, bR);
     take(F.offAL, (size_t)(F.nA + 1) * 8);
     take(F.offAR, (size_t)(F.nA + 1) * 8);
     take(F.digL, two ? kL + 4 : 0);
     take(F.digR, two ? kR + 4 : 0);
     take(F.segL, two ? F.sl.bytes : 0);
     take(F.segR, two ? F.sr.bytes : 0);
-    take(F.lk2, two ? kL * kt : 0);
-    take(F.lv2, two ? kL * 8 : 0);
-    take(F.rk2, two ? kR * kt : 0);
-    take(F.rv2, two ? kR * 8 : 0);
+    take(F.l2, two ? bL : 0);
+    take(F.r2, two ? bR : 0);
     take(F.subL, two ? (size_t)(F.S + 1) * 8 : 0);
     take(F.subR, two ? (size_t)(F.S + 1) * 8 : 0);
     take(F.jst, (size_t)F.S * 8);
@@ -1356,37 +1344,33 @@ int32_t mdx_batch_create(int32_t count, const mdx_merge_desc *h_descs,
             uint8_t *digR = two ? (uint8_t *)(b + f.digR) : nullptr;
             int64_t *offAL = (int64_t *)(b + f.offAL), *offAR = (int64_t *)(b + f.offAR);
             const PartArgs pt[2] = {
-                {d.d_left_keys, d.d_left_payload, d.n_left, b + f.lk1, (int64_t *)(b + f.lv1),
-                 offAL, digL, b + f.partL},
-                {d.d_right_keys, d.d_right_payload, d.n_right, b + f.rk1, (int64_t *)(b + f.rv1),
-                 offAR, digR, b + f.partR}};
+                {d.d_left_keys, d.d_left_payload, d.n_left, b + f.l1, nullptr, offAL, digL, b + f.partL},
+                {d.d_right_keys, d.d_right_payload, d.n_right, b + f.r1, nullptr, offAR, digR, b + f.partR}};
             part_rec(pt, f.kt, d.P, f.plan.q1bits, f.R, f.plan.q1bits, f.plan.q2bits,
                      B->h_image + u.part_off + j * part_rec_bytes());
             JoinRec jr = {};
             if (two) {
                 const SegArgs sa[2] = {
-                    {b + f.lk1, (int64_t *)(b + f.lv1), digL, d.n_left, offAL, b + f.lk2,
-                     (int64_t *)(b + f.lv2), (int64_t *)(b + f.subL), b + f.segL},
-                    {b + f.rk1, (int64_t *)(b + f.rv1), digR, d.n_right, offAR, b + f.rk2,
-                     (int64_t *)(b + f.rv2), (int64_t *)(b + f.subR), b + f.segR}};
+                    {b + f.l1, digL, d.n_left, offAL, b + f.l2, (int64_t *)(b + f.subL),
+                     b + f.segL},
+                    {b + f.r1, digR, d.n_right, offAR, b + f.r2, (int64_t *)(b + f.subR),
+                     b + f.segR}};
                 seg_rec(sa, f.kt, f.nA, f.plan.q1bits, f.plan.q2bits,
                         B->h_image + u.seg_off + j * seg_rec_bytes());
-                jr.lk = b + f.lk2;
-                jr.lv = (const int64_t *)(b + f.lv2);
+                jr.lrows = b + f.l2;
                 jr.subL = (const int64_t *)(b + f.subL);
-                jr.rk = b + f.rk2;
-                jr.rv = (const int64_t *)(b + f.rv2);
+                jr.rrows = b + f.r2;
                 jr.subR = (const int64_t *)(b + f.subR);
             } else {
-                jr.lk = b + f.lk1;
-                jr.lv = (const int64_t *)(b + f.lv1);
+                jr.lrows = b + f.l1;
                 jr.subL = offAL;
-                jr.rk = b + f.rk1;
-                jr.rv = (const int64_t *)(b + f.rv1);
+                jr.rrows = b + f.r1;
                 jr.subR = offAR;
             }
             jr.jstatus = (uint64_t *)(b + f.jst);
             jr.jcursor = (uint64_t *)(b + f.jcursor);
+            jr.nL = d.n_left;
+            jr.nR = d.n_right;
             jr.S = f.S;
             jr.o.key = d.d_out_key;
             jr.o.lpay = d.d_out_lpay;
@@ -1746,11 +1730,11 @@ int32_t mdx_server_submit_probe(mdx_server *srv, const mdx_table *h_table,
     hipError_t e = ready ? hipStreamWaitEvent(st, ready, 0) : hipSuccess;
     const PartArgs pa = {d.d_keys, d.d_payload, d.n, pk, pv, poff, nullptr, b + L.part_off};
     if (e == hipSuccess)
-        e = launch_partition(&pa, 1, kt, P, 0, 0, 0, st);
+        e = launch_partition(&pa, 1, kt, P, 0, false, 0, 0, st);
     if (e == hipSuccess)
         e = launch_probe_plan(poff, d.n, P, w, nullptr, st);
     if (e == hipSuccess)
-        e = launch_probe_group(pk, pv, kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o, d.d_status,
+        e = launch_probe_group(cols_of(pk, pv, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o, d.d_status,
                                0, st);
     if (e == hipSuccess)
         e = launch_probe_finalize(P, w, o, nullptr, st);

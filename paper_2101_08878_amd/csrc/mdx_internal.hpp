@@ -13,7 +13,7 @@ namespace mdx {
 constexpr size_t kAlign = 256;
 constexpr size_t kMaxLdsBytes = 160 * 1024;  // LDS of one gfx950 CU
 
-inline size_t align_up(size_t x, size_t a = kAlign)
+__host__ __device__ inline size_t align_up(size_t x, size_t a = kAlign)
 {
     return (x + a - 1) / a * a;
 }
@@ -24,6 +24,28 @@ inline int ceil_log2(int64_t x)
     while (b < 62 && ((int64_t)1 << b) < x)
         ++b;
     return b;
+}
+
+// Rows<K> of n rows in one buffer: 16-byte rows, or int32 keys and then the
+// payloads.
+__host__ __device__ inline size_t row_keys_bytes(int64_t n)
+{
+    return align_up((size_t)n * 4);
+}
+
+inline size_t rows_bytes(int64_t n, int key_bytes)
+{
+    return key_bytes == 8 ? (size_t)n * 16 : row_keys_bytes(n) + (size_t)n * 8;
+}
+
+template <typename K>
+__host__ __device__ inline Rows<K> make_rows(const void *buf, int64_t n)
+{
+    char *b = (char *)buf;
+    if constexpr (sizeof(K) == 8)
+        return Rows<K>{(i64x2 *)b, nullptr};
+    else
+        return Rows<K>{(K *)b, (int64_t *)(b + row_keys_bytes(n))};
 }
 
 inline Dest make_dest(int32_t P, int sbits = 0)
@@ -77,9 +99,10 @@ inline PartLayout part_layout(int64_t n, int32_t P, int R = 0)
 
 // One table of a partition launch: stable partition into
 // make_dest(P, sbits).ndest destinations; off has ndest + 1 entries; ws holds
-// part_layout(n, ndest).bytes.  With dig (n bytes), every output row's
-// digit_of(h, dshift, dbits) is written beside it, for the histogram of a
-// following segmented pass.
+// part_layout(n, ndest).bytes.  The output is two columns, or with `rows_out`
+// Rows<K> at keys_out (pay_out is null).  With dig (n bytes, rows
+// only), every output row's digit_of(h, dshift, dbits) is written beside it,
+// for the histogram of a following segmented pass.
 struct PartArgs {
     const void *keys;
     const int64_t *pay;
@@ -94,11 +117,11 @@ struct PartArgs {
 // Partition 1 or 2 tables (same key width and destinations) with one set of
 // launches.
 hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, int32_t P,
-                            int sbits, int dshift, int dbits, hipStream_t s);
+                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s);
 
 // ---- segmented partition (second split of the join) -------------------------
-// Segment a (rows [segoff[a], segoff[a+1]) of an already partitioned table)
-// is split stably into 2^bits destinations by digit_of(h, shift, bits);
+// Segment a (rows [segoff[a], segoff[a+1]) of an already partitioned table of
+// Rows<K>) // is split stably into 2^bits destinations by digit_of(h, shift, bits);
 // destination (a, q) lands at [outoff[a 2^bits + q], outoff[a 2^bits + q + 1]).
 #ifndef MDX_SEG_ROWS
 #define MDX_SEG_ROWS 8
@@ -136,18 +159,16 @@ inline SegLayout seg_layout(int64_t n, int64_t nseg, int bits)
     return L;
 }
 
-// One table of a segmented launch: dig holds every row's
+// One table of a segmented launch (rows and rows_out: Rows<K>): dig holds every row's
 // digit_of(h, shift, bits), one byte per row (bits <= 8), 4-byte aligned and
 // readable 4 bytes past its end (it is read as words); segoff has nseg + 1
 // entries, outoff nseg 2^bits + 1; ws holds seg_layout(n, nseg, bits).bytes.
 struct SegArgs {
-    const void *keys;
-    const int64_t *pay;
+    const void *rows;
     const uint8_t *dig;
     int64_t n;
     const int64_t *segoff;
-    void *keys_out;
-    int64_t *pay_out;
+    void *rows_out;
     int64_t *outoff;
     void *ws;
 };
@@ -168,8 +189,8 @@ struct BatchStage {
 };
 
 // Record of a merge's first pass over its two tables (tables[0] build,
-// tables[1] probe) with tiles of kBlock R rows, as launch_partition would
-// run it; part_rec_bytes() bytes.
+// tables[1] probe) into rows, with tiles of kBlock R rows, as
+// launch_partition would run it; part_rec_bytes() bytes.
 size_t part_rec_bytes();
 void part_rec(const PartArgs *tables, int key_bytes, int32_t P, int sbits, int R, int dshift,
               int dbits, void *dst);
@@ -448,10 +469,22 @@ int device_fill_blocks();
 void trace_begin(const char *kernel, hipStream_t s);
 void trace_end(const char *kernel, hipStream_t s);
 
+// A table as two columns, and as rows.
+inline Cols cols_of(const void *keys, const int64_t *pay, int key_bytes)
+{
+    return Cols{(const char *)keys, (const char *)pay, key_bytes, 8};
+}
+
+inline Cols cols_of_rows(const void *rows, int64_t n, int key_bytes)
+{
+    const char *b = (const char *)rows;
+    return key_bytes == 8 ? Cols{b, b + 8, 16, 16} : Cols{b, b + row_keys_bytes(n), 4, 8};
+}
+
 // Build a view of `rows` rows: init slots, insert rows, group repeated keys.
 // The grid-stride kernels of build and probe run on a full device, or on
 // max_blocks workgroups when 0 < max_blocks < that.
-hipError_t launch_build(const void *keys, const int64_t *pay, int key_bytes, const TView &v,
+hipError_t launch_build(const Cols &table, int key_bytes, const TView &v,
                         int64_t rows, int32_t *status, int max_blocks, hipStream_t s);
 
 // Copy the build offsets (sanitized, for n build rows) into the table and
@@ -472,7 +505,7 @@ hipError_t launch_fallback_setup(const int64_t *offAL, const int64_t *offAR, int
 // per probe), probe one view (group g), finalize the output offsets.
 hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const ProbeWs &w,
                              const int32_t *skip, hipStream_t s);
-hipError_t launch_probe_group(const void *pkeys, const int64_t *ppay, int key_bytes, int32_t P,
+hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
                               const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
                               int32_t *status, int max_blocks, hipStream_t s);
 hipError_t launch_probe_finalize(int32_t P, const ProbeWs &w, const ProbeOut &o,
@@ -495,8 +528,8 @@ hipError_t launch_join_count(const void *lk, const int64_t *lofs, int64_t n_buil
 // and the join does nothing.
 hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S,
                              const RJoinWs &w, bool chunked, int32_t *status, hipStream_t s);
-hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, const void *rk,
-                        const int64_t *rv, const int64_t *subR, int key_bytes, int32_t P,
+hipError_t launch_rjoin(const void *lrows, int64_t nL, const int64_t *subL, const void *rrows,
+                        int64_t nR, const int64_t *subR, int key_bytes, int32_t P,
                         int qbits, const RJoinWs &w, const ProbeOut &o, int32_t *status,
                         bool chunked, hipStream_t s);
 // Radix join of every merge of a batch (one key width): record m describes
@@ -507,12 +540,11 @@ hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, 
 // an LDS table is joined in table-sized chunks), and writes every merge's
 // output offsets.
 struct JoinRec {
-    const void *lk;
-    const int64_t *lv;
+    const void *lrows;    // Rows<K> of nL rows
     const int64_t *subL;  // [S + 1]
-    const void *rk;
-    const int64_t *rv;
+    const void *rrows;    // Rows<K> of nR rows
     const int64_t *subR;  // [S + 1]
+    int64_t nL, nR;
     uint64_t *jstatus;    // [S]
     uint64_t *jcursor;    // [P]
     int64_t S;

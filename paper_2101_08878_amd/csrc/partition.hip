@@ -39,8 +39,9 @@ struct PartTable {
     const K *keys;
     const int64_t *pay;
     int64_t n, ntiles;
-    K *keys_out;
+    K *keys_out;      // two columns, or
     int64_t *pay_out;
+    Rows<K> rows_out; // rows
     int64_t *off;     // [D + 1]
     uint8_t *dig;     // optional: one digit byte per output row
     int64_t *cnt;     // [D][ntiles]: counts, then exclusive prefixes
@@ -51,6 +52,18 @@ template <typename K>
 struct PartPair {
     PartTable<K> t[2];
 };
+
+__device__ __forceinline__ Rows<int64_t> pick(const Rows<int64_t> &a, const Rows<int64_t> &b,
+                                              bool second)
+{
+    return {second ? b.p : a.p, nullptr};
+}
+
+__device__ __forceinline__ Rows<int32_t> pick(const Rows<int32_t> &a, const Rows<int32_t> &b,
+                                              bool second)
+{
+    return {second ? b.kp : a.kp, second ? b.vp : a.vp};
+}
 
 // Table `second` of a pair, by field-wise selects on the kernel arguments.
 template <typename K>
@@ -64,6 +77,7 @@ __device__ __forceinline__ PartTable<K> pick(const PartPair<K> &T, bool second)
     r.ntiles = second ? b.ntiles : a.ntiles;
     r.keys_out = second ? b.keys_out : a.keys_out;
     r.pay_out = second ? b.pay_out : a.pay_out;
+    r.rows_out = pick(a.rows_out, b.rows_out, second);
     r.off = second ? b.off : a.off;
     r.dig = second ? b.dig : a.dig;
     r.cnt = second ? b.cnt : a.cnt;
@@ -305,6 +319,51 @@ __device__ inline void lds_excl_scan_u32(uint32_t *a, int P, int64_t *scratch)
     __syncthreads();
 }
 
+// A tile's input: two columns (keys first, then payloads, which are needed
+// only for staging), or rows.
+template <typename K>
+struct FromCols {
+    const K *__restrict__ keys;
+    const int64_t *__restrict__ pay;
+    template <int R>
+    __device__ __forceinline__ void load(int64_t r0, int64_t row_end, K *kr, int64_t *vr) const
+    {
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const int64_t r = r0 + (int64_t)c * kWave;
+            kr[c] = r < row_end ? __builtin_nontemporal_load(keys + r) : K(0);
+        }
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const int64_t r = r0 + (int64_t)c * kWave;
+            vr[c] = r < row_end ? __builtin_nontemporal_load(pay + r) : 0;
+        }
+    }
+};
+
+template <typename K>
+struct FromRows {
+    Rows<K> rows;
+    template <int R>
+    __device__ __forceinline__ void load(int64_t r0, int64_t row_end, K *kr, int64_t *vr) const
+    {
+        rows.template load_if<R>([&](int c) { return r0 + (int64_t)c * kWave; },
+                                 [&](int c) { return r0 + (int64_t)c * kWave < row_end; }, kr, vr);
+    }
+};
+
+// A tile's output as two columns (or Rows<K>).
+template <typename K>
+struct ToCols {
+    K *__restrict__ keys;
+    int64_t *__restrict__ pay;
+    __device__ __forceinline__ void store(int64_t r, K k, int64_t v) const
+    {
+        keys[r] = k;
+        pay[r] = v;
+    }
+};
+
 // Stable scatter of one tile, rows [row0, row_end) (at most kBlock R of them).
 // A row's destination in [0, D) is dfn(fmix64(key)); with DIG_OUT every
 // output row's next-pass digit digit_of(h, dshift, dbits) is written beside
@@ -313,13 +372,12 @@ __device__ inline void lds_excl_scan_u32(uint32_t *a, int P, int64_t *scratch)
 // [row0 + 64 R w, row0 + 64 R (w+1)); step c reads 64 consecutive rows.
 // (The second pass hashes its keys again rather than reading the digit
 // bytes: byte loads, 64 bytes per wave instruction, slowed it by a quarter.)
-template <typename K, int R, bool DIG_OUT, typename DestFn, typename BaseFn>
-__device__ __forceinline__ void scatter_tile(const K *__restrict__ keys,
-                                             const int64_t *__restrict__ pay, int64_t row0,
-                                             int64_t row_end, int D, int nbits, DestFn dfn,
-                                             BaseFn base_of, K *__restrict__ keys_out,
-                                             int64_t *__restrict__ pay_out, unsigned char *smem,
-                                             uint8_t *__restrict__ dig_out, int dshift, int dbits)
+template <typename K, int R, bool DIG_OUT, typename From, typename To, typename DestFn,
+          typename BaseFn>
+__device__ __forceinline__ void scatter_tile(const From &from, int64_t row0, int64_t row_end, int D,
+                                             int nbits, DestFn dfn, BaseFn base_of, const To &to,
+                                             unsigned char *smem, uint8_t *__restrict__ dig_out,
+                                             int dshift, int dbits)
 {
     constexpr int T = kBlock * R;
     static_assert(T <= 65535, "per-wave tile counts are 16-bit");
@@ -335,22 +393,12 @@ __device__ __forceinline__ void scatter_tile(const K *__restrict__ keys,
 
     const int tid = threadIdx.x, w = tid / kWave, lane = tid & (kWave - 1);
 
-    // The row loads go first (keys, then payloads, which are needed only
-    // for staging), so that the destination bases' loads and the ranking
-    // overlap them.
+    // The row loads go first, so that the destination bases' loads and the
+    // ranking overlap them.
     const int64_t wrow0 = row0 + (int64_t)w * kWave * R;
     K kr[R];
     int64_t vr[R];
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-        const int64_t r = wrow0 + (int64_t)c * kWave + lane;
-        kr[c] = r < row_end ? __builtin_nontemporal_load(keys + r) : K(0);
-    }
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-        const int64_t r = wrow0 + (int64_t)c * kWave + lane;
-        vr[c] = r < row_end ? __builtin_nontemporal_load(pay + r) : 0;
-    }
+    from.template load<R>(wrow0 + lane, row_end, kr, vr);
     for (int i = tid; i < kWavesPerBlock * D; i += kBlock)
         whist[i] = 0;
     for (int p = tid; p < D; p += kBlock)
@@ -429,33 +477,38 @@ __device__ __forceinline__ void scatter_tile(const K *__restrict__ keys,
         // XCD-contiguous tile order keeps those tiles on one L2).  With
         // streaming stores the partial lines went to HBM separately: 25% more
         // bytes written, 26% slower at a fan-out of 128.
-        keys_out[dst] = stage_k[s];
-        pay_out[dst] = stage_v[s];
+        to.store(dst, stage_k[s], stage_v[s]);
         if (DIG_OUT)
             dig_out[dst] = stage_d[s];
     }
 }
 
 // First-pass scatter of tile `tile` of table tb.
-template <typename K, int R, bool DIG>
+template <typename K, int R, bool ROWS, bool DIG>
 __device__ __forceinline__ void part_scatter_tile(const PartTable<K> &tb, int64_t tile,
                                                   const Dest &d, int dshift, int dbits,
                                                   unsigned char *smem)
 {
-    scatter_tile<K, R, DIG>(
-        tb.keys, tb.pay, tile * (int64_t)(kBlock * R), tb.n, d.ndest, d.nbits,
-        [&](uint64_t h) { return dest_of(h, d); },
-        [&](int p) { return tb.off[p] + tb.cnt[(int64_t)p * tb.ntiles + tile]; }, tb.keys_out,
-        tb.pay_out, smem, tb.dig, dshift, dbits);
+    auto scatter = [&](const auto &to) {
+        scatter_tile<K, R, DIG>(
+            FromCols<K>{tb.keys, tb.pay}, tile * (int64_t)(kBlock * R), tb.n, d.ndest, d.nbits,
+            [&](uint64_t h) { return dest_of(h, d); },
+            [&](int p) { return tb.off[p] + tb.cnt[(int64_t)p * tb.ntiles + tile]; }, to, smem,
+            tb.dig, dshift, dbits);
+    };
+    if constexpr (ROWS)
+        scatter(tb.rows_out);
+    else
+        scatter(ToCols<K>{tb.keys_out, tb.pay_out});
 }
 
-template <typename K, int R, bool DIG>
+template <typename K, int R, bool ROWS, bool DIG>
 __global__ __launch_bounds__(kBlock) void part_scatter(PartPair<K> T, Dest d, int dshift, int dbits)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int64_t g = tile_of_block(blockIdx.x, gridDim.x);
     const bool second = g >= T.t[0].ntiles;
-    part_scatter_tile<K, R, DIG>(pick(T, second), second ? g - T.t[0].ntiles : g, d, dshift,
+    part_scatter_tile<K, R, ROWS, DIG>(pick(T, second), second ? g - T.t[0].ntiles : g, d, dshift,
                                  dbits, smem);
 }
 
@@ -468,8 +521,7 @@ __global__ __launch_bounds__(kBlock) void part_scatter(PartPair<K> T, Dest d, in
 // i.e. the stable counting-sort position inside segment a.
 template <typename K>
 struct SegTable {
-    const K *keys;
-    const int64_t *pay;
+    Rows<K> rows;
     const uint8_t *dig;      // digit byte per row
     const int64_t *segoff;   // [nseg + 1]
     int64_t *tile_start;     // [nseg + 1]
@@ -479,8 +531,7 @@ struct SegTable {
     int64_t *outoff;         // [nseg D + 1]
     uint32_t *tile_seg;      // [max_tiles]: segment of every tile
     uint32_t *chunk_seg;     // [max_chunks]: segment of every chunk
-    K *keys_out;
-    int64_t *pay_out;
+    Rows<K> rows_out;
     int64_t max_tiles, max_chunks;
 };
 
@@ -494,8 +545,7 @@ __device__ __forceinline__ SegTable<K> pick(const SegPair<K> &T, bool second)
 {
     const SegTable<K> &a = T.t[0], &b = T.t[1];
     SegTable<K> r;
-    r.keys = second ? b.keys : a.keys;
-    r.pay = second ? b.pay : a.pay;
+    r.rows = pick(a.rows, b.rows, second);
     r.dig = second ? b.dig : a.dig;
     r.segoff = second ? b.segoff : a.segoff;
     r.tile_start = second ? b.tile_start : a.tile_start;
@@ -505,8 +555,7 @@ __device__ __forceinline__ SegTable<K> pick(const SegPair<K> &T, bool second)
     r.outoff = second ? b.outoff : a.outoff;
     r.tile_seg = second ? b.tile_seg : a.tile_seg;
     r.chunk_seg = second ? b.chunk_seg : a.chunk_seg;
-    r.keys_out = second ? b.keys_out : a.keys_out;
-    r.pay_out = second ? b.pay_out : a.pay_out;
+    r.rows_out = pick(a.rows_out, b.rows_out, second);
     r.max_tiles = second ? b.max_tiles : a.max_tiles;
     r.max_chunks = second ? b.max_chunks : a.max_chunks;
     return r;
@@ -676,13 +725,13 @@ __device__ __forceinline__ void seg_scatter_tile(const SegTable<K> &tb, int64_t 
     const int64_t r0 = tb.segoff[a] + lt * kSegTile;
     const int64_t r1 = r0 + kSegTile < tb.segoff[a + 1] ? r0 + kSegTile : tb.segoff[a + 1];
     scatter_tile<K, kSegRows, false>(
-        tb.keys, tb.pay, r0, r1, D, bits,
+        FromRows<K>{tb.rows}, r0, r1, D, bits,
         [&](uint64_t h) { return digit_of(h, shift, bits); },
         [&](int q) {
             return tb.outoff[(int64_t)a * D + q] + tb.csum[chunk * D + q] +
                    (int64_t)tb.cnt[t * D + q];
         },
-        tb.keys_out, tb.pay_out, smem, nullptr, 0, 0);
+        tb.rows_out, smem, nullptr, 0, 0);
 }
 
 template <typename K>
@@ -709,6 +758,7 @@ PartPair<K> part_pair(const PartArgs *tables, int ntables, int D, int R)
         t.ntiles = L.ntiles;
         t.keys_out = (K *)a.keys_out;
         t.pay_out = a.pay_out;
+        t.rows_out = make_rows<K>(a.keys_out, a.n);
         t.off = a.off;
         t.dig = a.dig;
         t.cnt = (int64_t *)((char *)a.ws + L.cnt_off);
@@ -718,8 +768,8 @@ PartPair<K> part_pair(const PartArgs *tables, int ntables, int D, int R)
 }
 
 template <typename K, int R>
-hipError_t run_partition(const PartArgs *tables, int ntables, int32_t P, int sbits, int dshift,
-                         int dbits, hipStream_t s)
+hipError_t run_partition(const PartArgs *tables, int ntables, int32_t P, int sbits, bool rows_out,
+                         int dshift, int dbits, hipStream_t s)
 {
     const Dest d = make_dest(P, sbits);
     const int D = d.ndest;
@@ -746,18 +796,17 @@ hipError_t run_partition(const PartArgs *tables, int ntables, int32_t P, int sbi
         const size_t lds = scatter_lds(kBlock * R, D, (int)sizeof(K), dig).total;
         if (lds > kMaxLdsBytes)
             return hipErrorInvalidValue;  // cannot happen for D <= MDX_MAX_P
-        const void *fn = dig ? (const void *)part_scatter<K, R, true>
-                             : (const void *)part_scatter<K, R, false>;
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (dig && !rows_out)
+            return hipErrorInvalidValue;  // digits go with rows
+        const auto fn = dig        ? part_scatter<K, R, true, true>
+                        : rows_out ? part_scatter<K, R, true, false>
+                                   : part_scatter<K, R, false, false>;
+        hipError_t e = hipFuncSetAttribute((const void *)fn,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess)
             return e;
         trace_begin("part_scatter", s);
-        if (dig)
-            hipLaunchKernelGGL((part_scatter<K, R, true>), dim3((unsigned)tiles), dim3(kBlock), lds,
-                               s, T, d, dshift, dbits);
-        else
-            hipLaunchKernelGGL((part_scatter<K, R, false>), dim3((unsigned)tiles), dim3(kBlock),
-                               lds, s, T, d, dshift, dbits);
+        hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(kBlock), lds, s, T, d, dshift, dbits);
         trace_end("part_scatter", s);
     }
     return hipGetLastError();
@@ -773,8 +822,7 @@ SegPair<K> seg_pair(const SegArgs *tables, int ntables, int64_t nseg, int bits)
         const SegLayout L = seg_layout(a.n, nseg, bits);
         char *b = (char *)a.ws;
         SegTable<K> &t = T.t[i];
-        t.keys = (const K *)a.keys;
-        t.pay = a.pay;
+        t.rows = make_rows<K>(a.rows, a.n);
         t.dig = a.dig;
         t.segoff = a.segoff;
         t.tile_start = (int64_t *)(b + L.tile_start_off);
@@ -784,8 +832,7 @@ SegPair<K> seg_pair(const SegArgs *tables, int ntables, int64_t nseg, int bits)
         t.outoff = a.outoff;
         t.tile_seg = (uint32_t *)(b + L.tile_seg_off);
         t.chunk_seg = (uint32_t *)(b + L.chunk_seg_off);
-        t.keys_out = (K *)a.keys_out;
-        t.pay_out = a.pay_out;
+        t.rows_out = make_rows<K>(a.rows_out, a.n);
         t.max_tiles = L.max_tiles;
         t.max_chunks = L.max_chunks;
     }
@@ -918,9 +965,9 @@ __global__ __launch_bounds__(kBlock) void part_scatter_batch(const PartRec<K> *_
     const PartTable<K> &t = r.T.t[second];
     const int64_t tile = second ? b - r.T.t[0].ntiles : b;
     if (t.dig)
-        part_scatter_tile<K, R, true>(t, tile, r.d, r.dshift, r.dbits, smem);
+        part_scatter_tile<K, R, true, true>(t, tile, r.d, r.dshift, r.dbits, smem);
     else
-        part_scatter_tile<K, R, false>(t, tile, r.d, r.dshift, r.dbits, smem);
+        part_scatter_tile<K, R, true, false>(t, tile, r.d, r.dshift, r.dbits, smem);
 }
 
 template <typename K>
@@ -1054,20 +1101,17 @@ void write_seg_rec(const SegArgs *tables, int64_t nseg, int shift, int bits, voi
 }  // namespace
 
 hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, int32_t P,
-                            int sbits, int dshift, int dbits, hipStream_t s)
+                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s)
 {
     if (ntables < 1 || ntables > 2)
         return hipErrorInvalidValue;
     const bool small = part_rows_per_thread(P << sbits) == kPartRowsSmall;
+    auto run = [&](auto f) { return f(tables, ntables, P, sbits, rows_out, dshift, dbits, s); };
     if (key_bytes == 8)
-        return small ? run_partition<int64_t, kPartRowsSmall>(tables, ntables, P, sbits, dshift,
-                                                              dbits, s)
-                     : run_partition<int64_t, kPartRowsLarge>(tables, ntables, P, sbits, dshift,
-                                                              dbits, s);
-    return small ? run_partition<int32_t, kPartRowsSmall>(tables, ntables, P, sbits, dshift, dbits,
-                                                          s)
-                 : run_partition<int32_t, kPartRowsLarge>(tables, ntables, P, sbits, dshift, dbits,
-                                                          s);
+        return small ? run(run_partition<int64_t, kPartRowsSmall>)
+                     : run(run_partition<int64_t, kPartRowsLarge>);
+    return small ? run(run_partition<int32_t, kPartRowsSmall>)
+                 : run(run_partition<int32_t, kPartRowsLarge>);
 }
 
 hipError_t launch_seg_partition(const SegArgs *tables, int ntables, int key_bytes, int64_t nseg,

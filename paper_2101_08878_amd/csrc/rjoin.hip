@@ -331,20 +331,18 @@ __global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict_
 // batch's last row instead (no branch per load) and are ignored by the
 // callers, which check r < re.
 template <typename K>
-__device__ __forceinline__ void load_batch(const K *__restrict__ rk, const int64_t *__restrict__ rv,
-                                           int64_t rb, int64_t re, K *kk, int64_t *vv)
+__device__ __forceinline__ void load_batch(Rows<K> rrows, int64_t rb, int64_t re,
+                                           K *kk, int64_t *vv)
 {
-    const K *kb = rk + rb;
-    const int64_t *vb = rv + rb;
+    const Rows<K> b = rrows.from(rb);
     const int64_t left = re - rb;
     const uint32_t last = (uint32_t)((left < kJoinBatch ? left : kJoinBatch) - 1);
-#pragma unroll
-    for (int j = 0; j < kJoinRows; ++j) {
-        uint32_t r = (uint32_t)(j * kJoinThreads) + threadIdx.x;
-        r = r < last ? r : last;
-        kk[j] = __builtin_nontemporal_load(kb + r);
-        vv[j] = __builtin_nontemporal_load(vb + r);
-    }
+    b.template load<kJoinRows>(
+        [&](int j) {
+            const uint32_t r = (uint32_t)(j * kJoinThreads) + threadIdx.x;
+            return r < last ? r : last;
+        },
+        kk, vv);
 }
 
 // Per row: the number of matches (high 16 bits; at most G::cap) and the
@@ -485,28 +483,25 @@ __device__ __forceinline__ void emit_batch(const K *kk, const int64_t *vv, const
 // kBuildBatch rows per thread at a time.  Rows past n load the last row (no
 // branch per load) and are not inserted.
 template <class G, typename K>
-__device__ __forceinline__ void build_table(const K *__restrict__ lk,
-                                            const int64_t *__restrict__ lv, int64_t b0, int64_t n,
-                                            int64_t *tkey, int64_t *tp, uint16_t *tn,
+__device__ __forceinline__ void build_table(Rows<K> lrows, int64_t b0,
+                                            int64_t n, int64_t *tkey, int64_t *tp, uint16_t *tn,
                                             uint32_t *head)
 {
     const int tid = threadIdx.x;
     for (int i = tid; i < G::heads; i += kJoinThreads)
         head[i] = Tab<G>::sent;
     __syncthreads();
-    const K *kb = lk + b0;
-    const int64_t *vb = lv + b0;
+    const Rows<K> b = lrows.from(b0);
     const uint32_t last = (uint32_t)n - 1;
     for (int base = 0; base < (int)n; base += kBuildBatch * kJoinThreads) {
         K bk[kBuildBatch];
         int64_t bv[kBuildBatch];
-#pragma unroll
-        for (int j = 0; j < kBuildBatch; ++j) {
-            uint32_t i = (uint32_t)(base + j * kJoinThreads) + tid;
-            i = i < last ? i : last;
-            bk[j] = __builtin_nontemporal_load(kb + i);
-            bv[j] = __builtin_nontemporal_load(vb + i);
-        }
+        b.template load<kBuildBatch>(
+            [&](int j) {
+                const uint32_t i = (uint32_t)(base + j * kJoinThreads) + tid;
+                return i < last ? i : last;
+            },
+            bk, bv);
 #pragma unroll
         for (int j = 0; j < kBuildBatch; ++j) {
             const int i = base + j * kJoinThreads + tid;
@@ -537,36 +532,25 @@ struct JoinLds {
 // complete in the order they were issued, and waiting for one waits for all
 // issued before it; so they are issued in the order they are needed, with
 // no branch around any of them (so that the compiler counts them exactly):
-// the build rows (the inserts wait for these alone), the probe keys (the
-// match), then, once the table is built, the probe payloads (needed only to
-// write the output, so they arrive during the count and the chained scan).
+// the build rows (the inserts wait for these alone), then the probe rows.
 template <class G, typename K>
-__device__ __forceinline__ void count_one_batch(const K *__restrict__ lk,
-                                                const int64_t *__restrict__ lv, int64_t bL,
-                                                int64_t nb, const K *__restrict__ rk,
-                                                const int64_t *__restrict__ rv, int64_t bR,
-                                                int64_t eR, const JoinLds &L, K *kk, int64_t *vv,
+__device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
+                                                int64_t nb, Rows<K> rrows,
+                                                int64_t bR, int64_t eR, const JoinLds &L, K *kk, int64_t *vv,
                                                 uint32_t *mf)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint32_t blast = (uint32_t)nb - 1, plast = (uint32_t)(eR - bR) - 1;
     K bk[kBuildBatch];
     int64_t bv[kBuildBatch];
-#pragma unroll
-    for (int j = 0; j < kBuildBatch; ++j) {
-        const uint32_t i = (uint32_t)(j * kJoinThreads + tid);
-        bk[j] = __builtin_nontemporal_load(lk + bL + (i < blast ? i : blast));
-    }
-#pragma unroll
-    for (int j = 0; j < kBuildBatch; ++j) {
-        const uint32_t i = (uint32_t)(j * kJoinThreads + tid);
-        bv[j] = __builtin_nontemporal_load(lv + bL + (i < blast ? i : blast));
-    }
-#pragma unroll
-    for (int j = 0; j < kJoinRows; ++j) {
-        const uint32_t r = (uint32_t)(j * kJoinThreads + tid);
-        kk[j] = __builtin_nontemporal_load(rk + bR + (r < plast ? r : plast));
-    }
+    auto clamped = [tid](uint32_t last) {
+        return [tid, last](int j) {
+            const uint32_t i = (uint32_t)(j * kJoinThreads + tid);
+            return i < last ? i : last;
+        };
+    };
+    lrows.from(bL).template load<kBuildBatch>(clamped(blast), bk, bv);
+    rrows.from(bR).template load<kJoinRows>(clamped(plast), kk, vv);
     for (int i = tid; i < G::heads; i += kJoinThreads)
         L.head[i] = Tab<G>::sent;
     __syncthreads();
@@ -581,11 +565,6 @@ __device__ __forceinline__ void count_one_batch(const K *__restrict__ lk,
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kJoinRows; ++j) {
-        const uint32_t r = (uint32_t)(j * kJoinThreads + tid);
-        vv[j] = __builtin_nontemporal_load(rv + bR + (r < plast ? r : plast));
-    }
     match_batch<G>(bR, eR, L.tkey, L.tn, L.head, kk, mf);
     cell_sums(mf, L.cw, lane, wv);
 }
@@ -598,9 +577,8 @@ __device__ __forceinline__ void count_one_batch(const K *__restrict__ lk,
 // batch (each pair of rows meets once), counting first and writing in a
 // second round.
 template <class G, typename K, bool LOOPS>
-__device__ __forceinline__ void join_item(const K *__restrict__ lk, const int64_t *__restrict__ lv,
-                                          int64_t bL, int64_t nb, const K *__restrict__ rk,
-                                          const int64_t *__restrict__ rv, int64_t bR, int64_t eR,
+__device__ __forceinline__ void join_item(Rows<K> lrows, int64_t bL, int64_t nb,
+                                          Rows<K> rrows, int64_t bR, int64_t eR,
                                           const Place &pl, int64_t t, int64_t s, bool first,
                                           int &cp, int64_t &cb, const ProbeOut &o, int32_t *status,
                                           const JoinLds &L)
@@ -617,10 +595,10 @@ __device__ __forceinline__ void join_item(const K *__restrict__ lk, const int64_
     int64_t counted = 0;  // the rows of a looped item
     if (loops) {
         for (int64_t c0 = 0; c0 < nb; c0 += kCap) {
-            build_table<G>(lk, lv, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
+            build_table<G>(lrows, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
                            L.head);
             for (int64_t b = bR; b < eR; b += kJoinBatch) {
-                load_batch(rk, rv, b, eR, kk, vv);
+                load_batch(rrows, b, eR, kk, vv);
                 match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
                 cell_sums(mf, L.cw, lane, wv);
                 __syncthreads();
@@ -634,7 +612,7 @@ __device__ __forceinline__ void join_item(const K *__restrict__ lk, const int64_
             }
         }
     } else if (any) {
-        count_one_batch<G, K>(lk, lv, bL, nb, rk, rv, bR, eR, L, kk, vv, mf);
+        count_one_batch<G, K>(lrows, bL, nb, rrows, bR, eR, L, kk, vv, mf);
         __syncthreads();
     }
     if (wv == 0) {
@@ -661,10 +639,10 @@ __device__ __forceinline__ void join_item(const K *__restrict__ lk, const int64_
     int64_t run = E;
     for (int64_t c0 = 0; c0 < nb; c0 += kCap) {
         __syncthreads();  // s_total has been read, the last chunk's table used
-        build_table<G>(lk, lv, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
+        build_table<G>(lrows, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
                        L.head);
         for (int64_t b = bR; b < eR; b += kJoinBatch) {
-            load_batch(rk, rv, b, eR, kk, vv);
+            load_batch(rrows, b, eR, kk, vv);
             match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
             cell_sums(mf, L.cw, lane, wv);
             __syncthreads();
@@ -718,9 +696,8 @@ __device__ __forceinline__ int64_t take_ticket(uint32_t *ticket, int64_t *s_next
 template <typename K, bool CHUNKED>
 __global__ __launch_bounds__(kJoinThreads)
 __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_join(
-    const K *__restrict__ lk, const int64_t *__restrict__ lv, const int64_t *__restrict__ subL,
-    const K *__restrict__ rk, const int64_t *__restrict__ rv, const int64_t *__restrict__ subR,
-    RJoinWs w, int qbits, int by_part, ProbeOut o, int32_t *status)
+    Rows<K> lrows, const int64_t *__restrict__ subL,
+    Rows<K> rrows, const int64_t *__restrict__ subR, RJoinWs w, int qbits, int by_part, ProbeOut o, int32_t *status)
 {
     MDX_JOIN_LDS(MergeJoin)
     // no items when the plan found a build side too large; the first ticket is
@@ -744,7 +721,7 @@ __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_joi
             bR += c * kJoinBatch;
             eR = nb > 0 && bR + kJoinBatch < eR ? bR + kJoinBatch : eR;
         }
-        join_item<MergeJoin, K, CHUNKED>(lk, lv, bL, nb, rk, rv, bR, eR, pl, t, s, first, cp, cb, o,
+        join_item<MergeJoin, K, CHUNKED>(lrows, bL, nb, rrows, bR, eR, pl, t, s, first, cp, cb, o,
                                          status, L);
         __syncthreads();  // the table is reused by the next item
     }
@@ -778,10 +755,10 @@ __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_joi
         const int64_t s = t - c0;
         const int64_t *subL = r.subL, *subR = r.subR;
         const int64_t bL = subL[s];
+        const Rows<K> lrows = make_rows<K>(r.lrows, r.nL), rrows = make_rows<K>(r.rrows, r.nR);
         const Place pl = {r.jcursor, r.jstatus, nullptr, r.S, r.o.offsets, r.qbits, r.by_part};
-        join_item<BatchJoin, K, true>((const K *)r.lk, r.lv, bL, subL[s + 1] - bL, (const K *)r.rk,
-                                      r.rv, subR[s], subR[s + 1], pl, s, s, true, cp, cb, r.o,
-                                      r.status, L);
+        join_item<BatchJoin, K, true>(lrows, bL, subL[s + 1] - bL, rrows, subR[s], subR[s + 1], pl, s, s, true,
+                                      cp, cb, r.o, r.status, L);
         __syncthreads();  // the table is reused by the next sub-bucket
     }
 }
@@ -878,37 +855,29 @@ hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S
     return hipGetLastError();
 }
 
-template <bool CHUNKED>
-void launch_rjoin_kernel(int G, const void *lk, const int64_t *lv, const int64_t *subL,
-                         const void *rk, const int64_t *rv, const int64_t *subR, int key_bytes,
-                         const RJoinWs &w, int qbits, const ProbeOut &o, int32_t *status,
-                         hipStream_t s)
+template <typename K>
+void launch_rjoin_kernel(int G, const void *lrows, int64_t nL, const int64_t *subL,
+                         const void *rrows, int64_t nR, const int64_t *subR, const RJoinWs &w, int qbits, const ProbeOut &o,
+                         int32_t *status, bool chunked, hipStream_t s)
 {
     const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
-    if (key_bytes == 8)
-        hipLaunchKernelGGL((rj_join<int64_t, CHUNKED>), dim3(G), dim3(kJoinThreads), 0, s,
-                           (const int64_t *)lk, lv, subL, (const int64_t *)rk, rv, subR, w, qbits,
-                           by_part, o, status);
-    else
-        hipLaunchKernelGGL((rj_join<int32_t, CHUNKED>), dim3(G), dim3(kJoinThreads), 0, s,
-                           (const int32_t *)lk, lv, subL, (const int32_t *)rk, rv, subR, w, qbits,
-                           by_part, o, status);
+    const auto fn = chunked ? rj_join<K, true> : rj_join<K, false>;
+    hipLaunchKernelGGL(fn, dim3(G), dim3(kJoinThreads), 0, s, make_rows<K>(lrows, nL), subL,
+                       make_rows<K>(rrows, nR), subR, w, qbits, by_part, o, status);
 }
 
-hipError_t launch_rjoin(const void *lk, const int64_t *lv, const int64_t *subL, const void *rk,
-                        const int64_t *rv, const int64_t *subR, int key_bytes, int32_t P,
-                        int qbits, const RJoinWs &w, const ProbeOut &o, int32_t *status,
-                        bool chunked, hipStream_t s)
+hipError_t launch_rjoin(const void *lrows, int64_t nL, const int64_t *subL, const void *rrows,
+                        int64_t nR, const int64_t *subR, int key_bytes, int32_t P, int qbits,
+                        const RJoinWs &w, const ProbeOut &o, int32_t *status, bool chunked,
+                        hipStream_t s)
 {
     (void)P;
     const int G = rjoin_grid(w.max_items);
     trace_begin("rj_join", s);
-    if (chunked)
-        launch_rjoin_kernel<true>(G, lk, lv, subL, rk, rv, subR, key_bytes, w, qbits, o, status,
-                                  s);
+    if (key_bytes == 8)
+        launch_rjoin_kernel<int64_t>(G, lrows, nL, subL, rrows, nR, subR, w, qbits, o, status, chunked, s);
     else
-        launch_rjoin_kernel<false>(G, lk, lv, subL, rk, rv, subR, key_bytes, w, qbits, o, status,
-                                   s);
+        launch_rjoin_kernel<int32_t>(G, lrows, nL, subL, rrows, nR, subR, w, qbits, o, status, chunked, s);
     trace_end("rj_join", s);
     return hipGetLastError();
 }
