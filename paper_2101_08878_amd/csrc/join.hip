@@ -87,6 +87,79 @@ __device__ __forceinline__ int64_t find_slot(const uint64_t *slots, int64_t sb, 
     return -1;
 }
 
+// A hash's place in the table: the half it walks, [lo, lo + H), is the top
+// bit's half of its partition's slots [sb, sb + 2 H).
+__device__ __forceinline__ int64_t half_of(int64_t sb, int64_t H, uint64_t h)
+{
+    return sb + (int64_t)(h >> 63) * H;
+}
+
+__device__ __forceinline__ int64_t home_slot(int64_t sb, int64_t H, uint64_t h)
+{
+    return half_of(sb, H, h) + (int64_t)__umul64hi(h << 1, (uint64_t)H);
+}
+
+__device__ __forceinline__ int64_t next_slot(int64_t at, int64_t sb, int64_t H, uint64_t h)
+{
+    const int64_t lo = half_of(sb, H, h);
+    return at + 1 == lo + H ? lo : at + 1;
+}
+
+// Slots of a thread's R hashes (-1: absent) and their values, for the rows of
+// mask `open`; the partition of row c owns slots sb(c) on, H(c) per half.  The
+// rows walk together: every round issues the loads of all
+// unfinished rows at once, so a round costs one memory latency whatever R
+// is.  (One row after the other, as first written, a row's two or three
+// dependent loads waited for the row before: the probe of 1E7 rows took 651
+// us.)
+template <int R, typename Sb, typename Hn>
+__device__ __forceinline__ void find_slots(const uint64_t *slots, Sb sb, Hn H, const uint64_t *h,
+                                           uint32_t open, int64_t *slot, uint64_t *val)
+{
+    const u64x2 *s2 = (const u64x2 *)slots;
+    const uint32_t rows = open;
+    uint32_t found = 0;
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        slot[c] = rows >> c & 1 ? home_slot(sb(c), H(c), h[c]) : -1;
+        val[c] = 0;
+    }
+    // a half has 8 empty slots, so the walk ends within H steps
+    for (int64_t k = 0; open; ++k) {
+        u64x2 x[R];
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            x[c] = u64x2(0);
+            if (open >> c & 1)
+                x[c] = s2[slot[c]];
+        }
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            if (open >> c & 1) {
+                if (x[c].x == h[c]) {
+                    val[c] = x[c].y;
+                    found |= 1u << c;
+                    open &= ~(1u << c);
+                } else if (x[c].x == empty_of_half(h[c] >> 63) || k >= H(c)) {
+                    open &= ~(1u << c);
+                } else {
+                    slot[c] = next_slot(slot[c], sb(c), H(c), h[c]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < R; ++c)
+        slot[c] = found >> c & 1 ? slot[c] : -1;
+}
+
+// Partition of every row of [r0, r1) when they share one (r0 < r1), else -1.
+__device__ __forceinline__ int shared_part(const TView &v, int64_t r0, int64_t r1)
+{
+    const int p = upper_index(v.off, v.pb, v.pe, r0);
+    return p + 1 == v.pe || r1 <= v.off[p + 1] ? p : -1;
+}
+
 __device__ __forceinline__ bool skipped(const int32_t *skip)
 {
     return skip && *skip != 0;
@@ -142,14 +215,31 @@ __global__ __launch_bounds__(kBlock) void tbl_init(TView v)
     }
 }
 
+// Inserts rows of the view: with `sample`, every 2^shift-th one; otherwise
+// the others (all of them when shift < 0).  A slot's compare-and-swaps are
+// made one after the other at the memory, 1 to 2 us each when they come from
+// different workgroups, and at the start of a launch every workgroup finds a
+// hot key's slot empty: 4E6 rows of which 10% hold one key took 1.8 ms.  So a
+// few workgroups insert a sample first (sample_shift), which holds every key
+// that repeats often, and its other rows then find it with a load: 0.26 ms.
+// The rest runs at the rate of the device's compare-and-swaps (16E9 a second
+// over distinct slots, in any order); four rows per thread at a time were
+// slower (4E6 distinct keys: 305 against 245 us).
 template <typename K>
-__global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int32_t *status)
+__global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int shift, bool sample,
+                                                     int32_t *status)
 {
     if (skipped(v.skip))
         return;
-    const int64_t o0 = v.off[v.pb], o1 = v.off[v.pe];
+    const int64_t o0 = v.off[v.pb], n = v.off[v.pe] - o0;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t r = o0 + (int64_t)blockIdx.x * kBlock + threadIdx.x; r < o1; r += stride) {
+    const int step = sample ? shift : 0;  // rows o0 + i 2^step
+    const int64_t sampled = !sample && shift >= 0 ? ((int64_t)1 << shift) - 1 : -1;
+    for (int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) << step; i < n;
+         i += stride << step) {
+        if (sampled >= 0 && (i & sampled) == 0)
+            continue;
+        const int64_t r = o0 + i;
         const uint64_t h = fmix64(key_bits(key_at<K>(in, r)));
         const int p = upper_index(v.off, v.pb, v.pe, r);
         if ((int)part_of(h, v.d) != p) {
@@ -158,15 +248,13 @@ __global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int32_t *
         }
         int64_t sb, H;
         part_slots(v, o0, p, sb, H);
-        const uint64_t t = h >> 63;
-        const uint64_t empty = empty_of_half(t);
-        const int64_t base = sb + (int64_t)t * H;
-        uint64_t i = __umul64hi(h << 1, (uint64_t)H);
+        const uint64_t empty = empty_of_half(h >> 63);
+        int64_t at = home_slot(sb, H, h);
         // The half holds at most n_p of its H = n_p + 8 slots, so an empty
         // slot exists and the walk ends within H steps.
         for (int64_t k = 0; k < H; ++k) {
-            uint64_t *sp = v.slots + 2 * (base + (int64_t)i);
-            uint64_t w = __hip_atomic_load(sp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint64_t *sp = v.slots + 2 * at;
+            uint64_t w = ld_agent(sp);
             if (w == empty) {
                 uint64_t expect = empty;
                 if (__hip_atomic_compare_exchange_strong(sp, &expect, h, __ATOMIC_RELAXED,
@@ -184,8 +272,7 @@ __global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int32_t *
                     v.flags[p] = 1;
                 break;
             }
-            if (++i == (uint64_t)H)
-                i = 0;
+            at = next_slot(at, sb, H, h);
         }
     }
 }
@@ -206,24 +293,41 @@ __global__ __launch_bounds__(kBlock) void grp_reset(TView v)
     }
 }
 
-// Slot of row r if r belongs to a repeated-key partition of the view, else -1.
-template <typename K>
-__device__ __forceinline__ int64_t dup_row_slot(const Cols &in, const TView &v, int64_t o0,
-                                                int64_t r, int64_t o1)
+// Slots of a thread's R rows r0, r0 + kBlock, ... (below r1): -1 where the row
+// lies in no repeated-key partition.  pt: shared_part of the workgroup's rows.
+template <typename K, int R>
+__device__ __forceinline__ void dup_row_slots(const Cols &in, const TView &v, int64_t o0,
+                                              int64_t r0, int64_t r1, int pt, int64_t *slot)
 {
-    if (r >= o1)
-        return -1;
-    const uint64_t h = fmix64(key_bits(key_at<K>(in, r)));
-    const int p = upper_index(v.off, v.pb, v.pe, r);
-    if (!v.flags[p] || (int)part_of(h, v.d) != p)
-        return -1;
-    int64_t sb, H;
-    part_slots(v, o0, p, sb, H);
-    return find_slot(v.slots, sb, H, h);
+    uint64_t h[R], val[R];
+    int64_t sb[R], H[R];
+    uint32_t open = 0;
+    K k[R];
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        const int64_t r = r0 + (int64_t)c * kBlock;
+        k[c] = r < r1 ? key_at<K>(in, r) : K(0);
+    }
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        const int64_t r = r0 + (int64_t)c * kBlock;
+        h[c] = fmix64(key_bits(k[c]));
+        if (r >= r1)
+            continue;
+        const int p = pt >= 0 ? pt : upper_index(v.off, v.pb, v.pe, r);
+        if (!v.flags[p] || (int)part_of(h[c], v.d) != p)
+            continue;
+        part_slots(v, o0, p, sb[c], H[c]);
+        open |= 1u << c;
+    }
+    find_slots<R>(
+        v.slots, [&](int c) { return sb[c]; }, [&](int c) { return H[c]; }, h, open, slot, val);
 }
 
 // ---- per-workgroup aggregation of rows by slot ------------------------------------
-constexpr int kAggRows = 16384;  // rows per workgroup of grp_count / grp_scatter
+constexpr int kAggPer = 8;   // rows per thread of grp_count / grp_scatter
+constexpr int kAggWalk = 4;  // of them walking together
+constexpr int kAggRows = kBlock * kAggPer;
 constexpr int kAggMap = 2048;    // LDS map entries: slot -> rows of this workgroup
 constexpr int kAggProbe = 8;     // map probes before a row goes to the slot directly
 constexpr int64_t kAggNone = -1;
@@ -281,16 +385,23 @@ __global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
     __syncthreads();
     int64_t o0, r0, r1;
     agg_rows(v, o0, r0, r1);
-    const int64_t o1 = v.off[v.pe];
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += kBlock) {
-        const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
-        if (s < 0)
+    if (r0 >= r1)
+        return;
+    int64_t slot[kAggPer];
+    const int pt = shared_part(v, r0, r1);
+#pragma unroll
+    for (int c = 0; c < kAggPer; c += kAggWalk)
+        dup_row_slots<K, kAggWalk>(in, v, o0, r0 + threadIdx.x + (int64_t)c * kBlock, r1, pt,
+                                   slot + c);
+#pragma unroll
+    for (int c = 0; c < kAggPer; ++c) {
+        if (slot[c] < 0)
             continue;
-        const int e = agg_insert(mkey, s);
+        const int e = agg_insert(mkey, slot[c]);
         if (e >= 0)
             atomicAdd(&mcnt[e], 1u);
         else
-            atomicAdd((unsigned long long *)&v.slots[2 * s + 1], 1ull);
+            atomicAdd((unsigned long long *)&v.slots[2 * slot[c] + 1], 1ull);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kAggMap; i += kBlock)
@@ -300,18 +411,13 @@ __global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
 
 // Give every key of a repeated-key partition its range of the grouped array:
 // gstart[s] = value[s] = (partition's first row) + running total.  Workgroup b
-// takes the slots [b kAllocSlots, (b+1) kAllocSlots): per partition in it, a
-// sum over its slots, one atomic on the partition's allocator, then the
-// exclusive scan of its slots' counts from there.
-constexpr int64_t kAllocSlots = 65536;
-
-__device__ __forceinline__ int64_t slot_rows(const TView &v, const int64_t *slots2, int64_t s,
-                                             int64_t sb, int64_t H)
-{
-    const uint64_t w = v.slots[2 * s];
-    const uint64_t empty = empty_of_half((s - sb) >= H ? 1 : 0);
-    return w == empty ? 0 : (int64_t)slots2[2 * s + 1];
-}
+// takes the slots [b kAllocSlots, (b+1) kAllocSlots), read once into
+// registers: per partition in it, a scan of the threads' sums, one atomic on
+// the partition's allocator, then every thread places its slots' groups from
+// there.  (65536 slots per workgroup, read twice: 198 us for 8E6 slots, with
+// half the CUs idle.)
+constexpr int kAllocPer = 8;
+constexpr int64_t kAllocSlots = (int64_t)kBlock * kAllocPer;
 
 __global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
 {
@@ -321,13 +427,20 @@ __global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
         return;
     __shared__ int64_t scratch[kWavesPerBlock];
     __shared__ int64_t s_base;
+    const int tid = threadIdx.x;
     const int64_t o0 = v.off[v.pb];
     const int64_t total = 2 * (v.off[v.pe] - o0) + 16 * (int64_t)(v.pe - v.pb);
     const int64_t c0 = (int64_t)blockIdx.x * kAllocSlots;
     const int64_t c1 = c0 + kAllocSlots < total ? c0 + kAllocSlots : total;
     if (c0 >= c1)
         return;
-    const int64_t *sv = (const int64_t *)v.slots;
+    const u64x2 *slots = (const u64x2 *)v.slots;
+    u64x2 x[kAllocPer];
+#pragma unroll
+    for (int k = 0; k < kAllocPer; ++k) {
+        const int64_t s = c0 + k * kBlock + tid;
+        x[k] = slots[s < c1 ? s : c1 - 1];
+    }
     for (int p = slot_part(v, o0, c0); p < v.pe; ++p) {
         int64_t sb, H;
         part_slots(v, o0, p, sb, H);
@@ -336,34 +449,39 @@ __global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
         if (!v.flags[p])
             continue;
         const int64_t a = sb > c0 ? sb : c0, e = sb + 2 * H < c1 ? sb + 2 * H : c1;
+        auto rows = [&](int k) {  // of slot k of this thread, if in p and taken
+            const int64_t s = c0 + k * kBlock + tid;
+            const bool in = s >= a && s < e && x[k].x != empty_of_half(s - sb >= H ? 1 : 0);
+            return in ? (int64_t)x[k].y : 0;
+        };
         int64_t sum = 0;
-        for (int64_t x = a + threadIdx.x; x < e; x += kBlock)
-            sum += slot_rows(v, sv, x, sb, H);
+#pragma unroll
+        for (int k = 0; k < kAllocPer; ++k)
+            sum += rows(k);
         int64_t all;
-        (void)block_excl_scan(sum, scratch, &all);
-        if (threadIdx.x == 0)
+        const int64_t ex = block_excl_scan(sum, scratch, &all);
+        if (tid == 0)
             s_base = (int64_t)atomicAdd((unsigned long long *)&v.bump[p], (unsigned long long)all);
         __syncthreads();
-        int64_t carry = (v.off[p] - o0) + s_base;
-        for (int64_t x0 = a; x0 < e; x0 += kBlock) {
-            const int64_t x = x0 + threadIdx.x;
-            const int64_t c = x < e ? slot_rows(v, sv, x, sb, H) : 0;
-            int64_t tot;
-            const int64_t ex = block_excl_scan(c, scratch, &tot);
-            if (x < e && c > 0) {
-                v.gstart[x] = carry + ex;
-                v.slots[2 * x + 1] = (uint64_t)(carry + ex);
+        int64_t run = (v.off[p] - o0) + s_base + ex;
+#pragma unroll
+        for (int k = 0; k < kAllocPer; ++k) {
+            const int64_t c = rows(k), s = c0 + k * kBlock + tid;
+            if (c > 0) {
+                v.gstart[s] = run;
+                v.slots[2 * s + 1] = (uint64_t)run;
+                run += c;
             }
-            carry += tot;
         }
         __syncthreads();  // s_base is reused by the next partition
     }
 }
 
 // grouped[value[s]++] = payload, for every row of a repeated-key partition.
-// First the workgroup counts its rows per slot in the map and reserves one
-// range per slot; then every row takes the next place of its slot's range
-// (rows the map could not hold take a place from the slot directly).
+// First the workgroup counts its rows per slot in the map (a row's count so
+// far is its rank) and reserves one range per slot; then every row takes its
+// rank's place in its slot's range (rows the map could not hold take a place
+// from the slot directly).  Slots and ranks stay in registers.
 template <typename K>
 __global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
 {
@@ -374,11 +492,6 @@ __global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
     __shared__ int64_t mkey[kAggMap];
     __shared__ int64_t mbase[kAggMap];
     __shared__ uint32_t mcnt[kAggMap];
-    // every row's map entry from the first pass: kRowSkip (no repeated-key
-    // row), kRowDirect (not in the map: takes its place from the slot), or
-    // the entry
-    constexpr int16_t kRowSkip = -2, kRowDirect = -1;
-    __shared__ int16_t rent[kAggRows];
     for (int i = threadIdx.x; i < kAggMap; i += kBlock) {
         mkey[i] = kAggNone;
         mcnt[i] = 0;
@@ -386,42 +499,41 @@ __global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
     __syncthreads();
     int64_t o0, r0, r1;
     agg_rows(v, o0, r0, r1);
-    const int64_t o1 = v.off[v.pe];
-    for (int i = threadIdx.x; i < kAggRows; i += kBlock) {
-        const int64_t r = r0 + i;
-        const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
-        int e = kRowSkip;
-        if (s >= 0) {
-            e = agg_insert(mkey, s);
-            if (e >= 0)
-                atomicAdd(&mcnt[e], 1u);
-            else
-                e = kRowDirect;
-        }
-        rent[i] = (int16_t)e;
+    if (r0 >= r1)
+        return;
+    int64_t slot[kAggPer];
+    const int pt = shared_part(v, r0, r1);
+#pragma unroll
+    for (int c = 0; c < kAggPer; c += kAggWalk)
+        dup_row_slots<K, kAggWalk>(in, v, o0, r0 + threadIdx.x + (int64_t)c * kBlock, r1, pt,
+                                   slot + c);
+    int e[kAggPer];
+    uint32_t rank[kAggPer];
+#pragma unroll
+    for (int c = 0; c < kAggPer; ++c) {
+        e[c] = slot[c] >= 0 ? agg_insert(mkey, slot[c]) : -1;
+        rank[c] = e[c] >= 0 ? atomicAdd(&mcnt[e[c]], 1u) : 0u;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kAggMap; i += kBlock) {
         if (mkey[i] != kAggNone)
             mbase[i] = (int64_t)atomicAdd((unsigned long long *)&v.slots[2 * mkey[i] + 1],
                                           (unsigned long long)mcnt[i]);
-        mcnt[i] = 0;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kAggRows; i += kBlock) {
-        const int e = rent[i];
-        if (e == kRowSkip)
-            continue;
-        const int64_t r = r0 + i;
-        int64_t at;
-        if (e >= 0) {
-            at = mbase[e] + (int64_t)atomicAdd(&mcnt[e], 1u);
-        } else {
-            const int64_t s = dup_row_slot<K>(in, v, o0, r, o1);
-            at = (int64_t)atomicAdd((unsigned long long *)&v.slots[2 * s + 1], 1ull);
-        }
-        v.grouped[at] = pay_at(in, r);
+    int64_t at[kAggPer];
+#pragma unroll
+    for (int c = 0; c < kAggPer; ++c) {
+        at[c] = -1;
+        if (slot[c] >= 0)
+            at[c] = e[c] >= 0 ? mbase[e[c]] + rank[c]
+                              : (int64_t)atomicAdd(
+                                    (unsigned long long *)&v.slots[2 * slot[c] + 1], 1ull);
     }
+#pragma unroll
+    for (int c = 0; c < kAggPer; ++c)
+        if (slot[c] >= 0)
+            v.grouped[at[c]] = pay_at(in, r0 + threadIdx.x + (int64_t)c * kBlock);
 }
 
 // ---- probe -----------------------------------------------------------------
@@ -492,8 +604,11 @@ __global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int grou
     if (skipped(v.skip))
         return;
     constexpr int RP = kProbeRows;
-    __shared__ int64_t s_tile, s_excl;
-    __shared__ int64_t cw[RP][kWavesPerBlock];
+    constexpr int kProbeWalk = 4;  // rows of a thread walking together
+    constexpr int kCells = RP * kWavesPerBlock;  // (row step, wave)
+    static_assert(kCells <= kWave, "one wave scans the cells");
+    __shared__ int64_t s_tile, s_excl, s_total;
+    __shared__ int64_t cw[kCells];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int64_t t_begin = w.tile_start[v.pb], t_end = w.tile_start[v.pe];
     const int64_t o0 = v.off[v.pb];
@@ -515,84 +630,96 @@ __global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int grou
         part_slots(v, o0, p, sb, H);
 
         K kk[RP];
-        int64_t vv[RP], m[RP], lv[RP];
-        bool bad = false;
+        int64_t vv[RP];
 #pragma unroll
         for (int c = 0; c < RP; ++c) {
             const int64_t r = rbeg + (int64_t)c * kBlock + tid;
-            const bool valid = r < rend;
-            kk[c] = valid ? key_at<K>(in, r) : K(0);
-            vv[c] = valid ? pay_at(in, r) : 0;
+            kk[c] = r < rend ? key_at<K>(in, r) : K(0);
         }
 #pragma unroll
         for (int c = 0; c < RP; ++c) {
             const int64_t r = rbeg + (int64_t)c * kBlock + tid;
-            m[c] = 0;
-            lv[c] = 0;
-            if (r < rend) {
-                const uint64_t h = fmix64(key_bits(kk[c]));
-                if ((int)part_of(h, v.d) != p) {
-                    bad = true;
-                } else {
-                    const int64_t s = find_slot(v.slots, sb, H, h);
-                    if (s >= 0) {
-                        const uint64_t val = v.slots[2 * s + 1];
-                        if (!dup) {
-                            m[c] = 1;
-                            lv[c] = (int64_t)val;
-                        } else {
-                            const int64_t g0 = v.gstart[s];
-                            m[c] = (int64_t)val - g0;
-                            lv[c] = g0;
-                        }
-                    }
-                }
+            vv[c] = r < rend ? pay_at(in, r) : 0;
+        }
+        int64_t slot[RP];
+        uint64_t val[RP];
+        bool bad = false;
+#pragma unroll
+        for (int c = 0; c < RP; c += kProbeWalk) {
+            uint64_t h[kProbeWalk];
+            uint32_t open = 0;
+#pragma unroll
+            for (int i = 0; i < kProbeWalk; ++i) {
+                const int64_t r = rbeg + (int64_t)(c + i) * kBlock + tid;
+                h[i] = fmix64(key_bits(kk[c + i]));
+                const bool here = (int)part_of(h[i], v.d) == p;
+                if (r < rend && here)
+                    open |= 1u << i;
+                bad |= r < rend && !here;
             }
+            find_slots<kProbeWalk>(
+                v.slots, [=](int) { return sb; }, [=](int) { return H; }, h, open, slot + c,
+                val + c);
         }
         if (bad)
             or_status(status, MDX_DEV_BAD_PARTITIONING);
 
-        // Output rank of every row: order (c, thread), i.e. row order.
-        int64_t mex[RP];
+        // Matches per (row step, wave) into cw, in row order.  In a
+        // repeated-key partition slot[c] becomes the row's rank among its
+        // wave's output rows of the step, and val[c] its group's start.
+        uint32_t hit = 0;
+        if (!dup) {
 #pragma unroll
-        for (int c = 0; c < RP; ++c) {
-            const int64_t inc = wave_incl_scan(m[c], lane);
-            mex[c] = inc - m[c];
-            if (lane == kWave - 1)
-                cw[c][wv] = inc;
-        }
-        __syncthreads();
-        int64_t run = 0, cbase[RP];
+            for (int c = 0; c < RP; ++c) {
+                const bool x = slot[c] >= 0;
+                hit |= x ? 1u << c : 0u;
+                const uint64_t b = ballot(x);
+                if (lane == 0)
+                    cw[c * kWavesPerBlock + wv] = __popcll(b);
+            }
+        } else {
 #pragma unroll
-        for (int c = 0; c < RP; ++c) {
-#pragma unroll
-            for (int ww = 0; ww < kWavesPerBlock; ++ww) {
-                const int64_t x = cw[c][ww];
-                if (ww == wv)
-                    cbase[c] = run;
-                run += x;
+            for (int c = 0; c < RP; ++c) {
+                int64_t m = 0;
+                if (slot[c] >= 0) {
+                    const int64_t g0 = v.gstart[slot[c]];
+                    m = (int64_t)val[c] - g0;
+                    val[c] = (uint64_t)g0;
+                }
+                const int64_t inc = wave_incl_scan(m, lane);
+                slot[c] = inc - m;
+                if (lane == kWave - 1)
+                    cw[c * kWavesPerBlock + wv] = inc;
             }
         }
-        const int64_t M = run;
-        if (wv == 0) {
+        __syncthreads();
+        if (wv == 0) {  // cw := exclusive prefix; the tile's rows placed
+            const int64_t x = lane < kCells ? cw[lane] : 0;
+            const int64_t inc = wave_incl_scan(x, lane);
+            if (lane < kCells)
+                cw[lane] = inc - x;
+            const int64_t M = __shfl(inc, kWave - 1, kWave);
             const int64_t ex = lookback(w.status, tile, M, lane, status);
             if (lane == 0) {
                 s_excl = ex;
+                s_total = M;
                 w.tile_base[tile] = ex;
             }
         }
         __syncthreads();
-        const int64_t E = s_excl;
+        const int64_t E = s_excl, M = s_total;
         if (E + M > o.cap) {
             if (tid == 0 && M > 0)
                 or_status(status, MDX_DEV_OUTPUT_OVERFLOW);
         } else if (!dup) {
 #pragma unroll
             for (int c = 0; c < RP; ++c) {
-                if (m[c]) {
-                    const int64_t at = E + cbase[c] + mex[c];
+                const bool x = hit >> c & 1;
+                const uint64_t b = ballot(x);
+                if (x) {
+                    const int64_t at = E + cw[c * kWavesPerBlock + wv] + mbcnt(b);
                     out_key[at] = kk[c];
-                    o.lpay[at] = lv[c];
+                    o.lpay[at] = (int64_t)val[c];
                     o.rpay[at] = vv[c];
                 }
             }
@@ -601,8 +728,8 @@ __global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int grou
             for (int c = 0; c < RP; ++c) {
                 const int64_t r = rbeg + (int64_t)c * kBlock + tid;
                 if (r < rend) {
-                    w.row_pre[r] = cbase[c] + mex[c];
-                    w.row_gs[r] = lv[c];
+                    w.row_pre[r] = cw[c * kWavesPerBlock + wv] + slot[c];
+                    w.row_gs[r] = (int64_t)val[c];
                 }
             }
             if (tid == 0 && M > 0) {
@@ -625,44 +752,61 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
 {
     if (skipped(v.skip))
         return;
+    // The deferred tiles' outputs are cut into chunks, numbered tile by tile;
+    // workgroup b takes the chunks b, b + G, ...  The tiles' chunk counts are
+    // read kBlock at a time (one after the other, 105 tiles took each
+    // workgroup 100 us).
     constexpr int64_t CH = 4096;  // output rows per chunk
     __shared__ int64_t pre[kProbeTile];
+    __shared__ int64_t first[kBlock];  // first chunk of tile e0 + i
+    __shared__ int64_t scratch[kWavesPerBlock];
     const uint32_t nd = *w.ndefer;
     const int64_t G = gridDim.x;
     K *out_key = (K *)o.key;
-    int64_t acc = 0;  // global index of the current entry's first chunk
-    for (uint32_t e = 0; e < nd; ++e) {
-        const Deferred D = w.defer[e];
-        if (D.group != group)
-            continue;
-        const int64_t nch = (D.count + CH - 1) / CH;
-        int64_t j = (((int64_t)blockIdx.x - acc) % G + G) % G;
-        if (j < nch) {
-            const int rows = (int)(D.rend - D.rbeg);
-            for (int i = threadIdx.x; i < rows; i += kBlock)
-                pre[i] = w.row_pre[D.rbeg + i];
-            __syncthreads();
-            for (; j < nch; j += G) {
-                const int64_t lim = (j + 1) * CH < D.count ? (j + 1) * CH : D.count;
-                for (int64_t q = j * CH + threadIdx.x; q < lim; q += kBlock) {
-                    int l = 0, h = rows - 1;  // last row whose prefix <= q
-                    while (l < h) {
-                        const int mid = (l + h + 1) >> 1;
-                        if (pre[mid] <= q)
-                            l = mid;
-                        else
-                            h = mid - 1;
-                    }
-                    const int64_t r = D.rbeg + l;
-                    const int64_t at = D.base + q;
-                    out_key[at] = key_at<K>(in, r);
-                    o.lpay[at] = v.grouped[w.row_gs[r] + (q - pre[l])];
-                    o.rpay[at] = pay_at(in, r);
-                }
+    int64_t acc = 0;  // chunks of the tiles before e0
+    for (uint32_t e0 = 0; e0 < nd; e0 += kBlock) {
+        const uint32_t e = e0 + threadIdx.x;
+        int64_t nch = 0, all;
+        if (e < nd && w.defer[e].group == group)
+            nch = (w.defer[e].count + CH - 1) / CH;
+        const int64_t ex = block_excl_scan(nch, scratch, &all);
+        __syncthreads();  // `first` is no longer read
+        first[threadIdx.x] = acc + ex;
+        __syncthreads();
+        const int ne = (int)(nd - e0 < (uint32_t)kBlock ? nd - e0 : (uint32_t)kBlock);
+        int held = -1;  // the tile whose row prefixes are in pre
+        Deferred D = {};
+        for (int64_t j = acc + (((int64_t)blockIdx.x - acc) % G + G) % G; j < acc + all; j += G) {
+            const int te = upper_index(first, 0, ne, j);  // the last tile that starts at or before j
+            if (te != held) {
+                __syncthreads();  // pre is no longer read
+                D = w.defer[e0 + te];
+                const int rows = (int)(D.rend - D.rbeg);
+                for (int i = threadIdx.x; i < rows; i += kBlock)
+                    pre[i] = w.row_pre[D.rbeg + i];
+                __syncthreads();
+                held = te;
             }
-            __syncthreads();
+            const int rows = (int)(D.rend - D.rbeg);
+            const int64_t q0 = (j - first[te]) * CH;
+            const int64_t lim = q0 + CH < D.count ? q0 + CH : D.count;
+            for (int64_t q = q0 + threadIdx.x; q < lim; q += kBlock) {
+                int l = 0, h = rows - 1;  // last row whose prefix <= q
+                while (l < h) {
+                    const int mid = (l + h + 1) >> 1;
+                    if (pre[mid] <= q)
+                        l = mid;
+                    else
+                        h = mid - 1;
+                }
+                const int64_t r = D.rbeg + l;
+                const int64_t at = D.base + q;
+                out_key[at] = key_at<K>(in, r);
+                o.lpay[at] = v.grouped[w.row_gs[r] + (q - pre[l])];
+                o.rpay[at] = pay_at(in, r);
+            }
         }
-        acc += nch;
+        acc += all;
     }
 }
 
@@ -912,6 +1056,19 @@ static int table_grid(int max_blocks)
     return max_blocks > 0 && max_blocks < full ? max_blocks : full;
 }
 
+// Rows of a build's sample, every 2^shift-th; -1: no sample (few workgroups
+// insert the rows at all).
+constexpr int kSampleBlocks = 16;
+constexpr int64_t kSampleRows = 32768;
+
+static int sample_shift(int64_t rows)
+{
+    int shift = 0;
+    while (rows >> shift > kSampleRows)
+        ++shift;
+    return rows <= 4 * kSampleRows ? -1 : shift;
+}
+
 template <typename K>
 hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *status, int max_blocks, hipStream_t s)
 {
@@ -925,8 +1082,12 @@ hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *stat
     trace_begin("tbl_init", s);
     hipLaunchKernelGGL(tbl_init, dim3(G), dim3(kBlock), 0, s, v);
     trace_end("tbl_init", s);
+    const int shift = sample_shift(rows);
     trace_begin("tbl_insert", s);
-    hipLaunchKernelGGL((tbl_insert<K>), dim3(G), dim3(kBlock), 0, s, in, v, status);
+    if (shift >= 0)
+        hipLaunchKernelGGL((tbl_insert<K>), dim3(kSampleBlocks), dim3(kBlock), 0, s, in, v, shift,
+                           true, status);
+    hipLaunchKernelGGL((tbl_insert<K>), dim3(G), dim3(kBlock), 0, s, in, v, shift, false, status);
     trace_end("tbl_insert", s);
     hipLaunchKernelGGL(grp_reset, dim3(G), dim3(kBlock), 0, s, v);
     trace_begin("grp_count", s);

@@ -406,8 +406,8 @@ int32_t mdx_join_build(const void *d_keys, const int64_t *d_payload, const int64
     hipError_t e = launch_table_setup(d_offsets, n, t.d_offsets, t.d_flags, t.d_bump, P, stream);
     if (e != hipSuccess)
         return hip_fail(e, W);
-    e = launch_build(cols_of(d_keys, d_payload, key_type), key_type, make_view(t, t.d_offsets, 0, P), n, d_status, 0,
-                     stream);
+    e = launch_build(cols_of(d_keys, d_payload, key_type), key_type,
+                     make_view(t, t.d_offsets, 0, P), n, d_status, 0, stream);
     if (e != hipSuccess)
         return hip_fail(e, W);
     *h_table = t;
@@ -485,8 +485,8 @@ int32_t mdx_join_probe(const mdx_table *h_table, const void *d_keys, const int64
     o.offsets = d_out_offsets;
     hipError_t e = launch_probe_plan(d_offsets, n, P, w, nullptr, stream);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o,
-                               d_status, 0, stream);
+        e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt, P,
+                               make_view(t, t.d_offsets, 0, P), 0, w, o, d_status, 0, stream);
     if (e == hipSuccess)
         e = launch_probe_finalize(P, w, o, nullptr, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
@@ -793,8 +793,8 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     if (e == hipSuccess)
         e = launch_rjoin_plan(subL, subR, M.S, jw, chunked, d_status, stream);
     if (e == hipSuccess)
-        e = launch_rjoin(lrows, n_left, subL, rrows, n_right, subR, key_type, P, pl.qbits, jw, o, d_status, chunked,
-                         stream);
+        e = launch_rjoin(lrows, n_left, subL, rrows, n_right, subR, key_type, P, pl.qbits, jw, o,
+                         d_status, chunked, stream);
 
     // 4. otherwise (a sub-bucket too large for LDS: heavy key repetition),
     // the global-table join over the first-pass output; its kernels do
@@ -814,14 +814,18 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
                                   (const int32_t *)jw.plan_out + 1, stream);
     TView v = make_view(t, t.d_offsets, 0, P);
     v.skip = (const int32_t *)jw.plan_out + 1;
-    // grids sized to the rows (~16K per workgroup): these launches mostly
-    // return at once, and return sooner with fewer workgroups
-    auto blocks = [](int64_t rows) { return (int)std::min<int64_t>((rows >> 14) + 1, 1 << 20); };
+    // grids sized to the rows (2048 per workgroup; 16384 left most of the
+    // device idle at 4E6 rows: 725 against 567 us); the launches mostly
+    // return at once
+    auto blocks = [](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, 1 << 20); };
     if (e == hipSuccess)
-        e = launch_build(cols_of_rows(l1, n_left, key_type), key_type, v, n_left, d_status, blocks(n_left), stream);
+        // the final rows: of a hot key's, and of a sub-bucket's slots, all are
+        // together
+        e = launch_build(cols_of_rows(lrows, n_left, key_type), key_type, v, n_left, d_status,
+                         blocks(n_left), stream);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of_rows(r1, n_right, key_type), key_type, P, v, 0, w, o, d_status, blocks(n_right),
-                               stream);
+        e = launch_probe_group(cols_of_rows(r1, n_right, key_type), key_type, P, v, 0, w, o,
+                               d_status, blocks(n_right), stream);
     if (e == hipSuccess)
         e = launch_merge_finalize(pl.qbits, jw, &w, o, stream);
     return e;
@@ -1734,8 +1738,8 @@ int32_t mdx_server_submit_probe(mdx_server *srv, const mdx_table *h_table,
     if (e == hipSuccess)
         e = launch_probe_plan(poff, d.n, P, w, nullptr, st);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of(pk, pv, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w, o, d.d_status,
-                               0, st);
+        e = launch_probe_group(cols_of(pk, pv, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w,
+                               o, d.d_status, 0, st);
     if (e == hipSuccess)
         e = launch_probe_finalize(P, w, o, nullptr, st);
     if (e == hipSuccess)

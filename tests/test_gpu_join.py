@@ -198,3 +198,35 @@ def test_join_count_bad_partitioning_is_reported():
     assert int(status.item()) & mdx.MDX_DEV_BAD_PARTITIONING
     assert got[-1] <= oracle.join(kl, np.zeros(kl.size, np.int64), kr, np.zeros(kr.size, np.int64),
                                   materialize=False)["total"]
+
+
+@pytest.mark.parametrize("n", [131_072, 131_073, 262_145])
+@pytest.mark.parametrize("hot", [0, 40_000])
+def test_join_build_sampled_rows(n, hot):
+    """Build sides around the size from which a sample of the rows is inserted
+    first (131072), of distinct keys and with one key repeated 40000 times."""
+    announce(f"staged join, build of {n}, hot key x {hot}")
+    rng = np.random.default_rng(n + hot)
+    kl = rng.permutation(n).astype(np.int64)
+    kl[:hot] = 5_000_000
+    kl = kl[rng.permutation(n)]
+    kr = np.concatenate([rng.integers(0, 2 * n, 50_000), np.full(3 if hot else 0, 5_000_000)])
+    vl, vr = np.arange(n, dtype=np.int64), np.arange(kr.size, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    got = run_staged_join(kl, vl, kr, vr, 3, cap=max(total, 1))
+    assert_join_equals_oracle(kl, vl, kr, vr, 3, got)
+
+
+@pytest.mark.parametrize("P,dtype", [(1, np.int64), (64, np.int32)])
+def test_join_repeated_keys_many_probe_tiles(P, dtype):
+    """2.2E6 probe rows in repeated-key partitions: more deferred probe tiles
+    (537 and more) than the expansion reads at once, over groups of slots
+    that cross the allocation's chunks."""
+    announce(f"staged join, many deferred tiles, P={P}")
+    rng = np.random.default_rng(P)
+    kl = np.repeat(np.arange(6000, dtype=dtype), 2)[rng.permutation(12_000)]
+    kr = rng.integers(0, 24_000, 2_200_000).astype(dtype)
+    vl, vr = np.arange(kl.size, dtype=np.int64), np.arange(kr.size, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    got = run_staged_join(kl, vl, kr, vr, P, cap=total)
+    assert_join_equals_oracle(kl, vl, kr, vr, P, got)
