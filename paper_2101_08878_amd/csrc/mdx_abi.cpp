@@ -202,7 +202,7 @@ int32_t mdx_hash_partition_workspace_bytes(int64_t n, int32_t P, int32_t key_typ
         return e;
     if (!h_bytes)
         return fail(MDX_ERR_INVALID, "mdx_hash_partition_workspace_bytes: h_bytes is null");
-    *h_bytes = part_layout(n, P).bytes;
+    *h_bytes = part_workspace_bytes(n, P, key_type);
     return MDX_OK;
 }
 
@@ -242,12 +242,12 @@ int32_t mdx_hash_partition(const void *d_keys, const int64_t *d_payload, int64_t
     if (int32_t e = check_partition(d_keys, d_payload, n, key_type, P, d_keys_out, d_payload_out,
                                     d_offsets, W))
         return e;
-    const PartLayout L = part_layout(n, P);
+    const size_t need = part_workspace_bytes(n, P, key_type);
     if (!d_ws || !aligned(d_ws, kAlign))
         return fail(MDX_ERR_INVALID, "mdx_hash_partition: workspace null or not 256-byte aligned");
-    if (ws_bytes < L.bytes)
+    if (ws_bytes < need)
         return fail(MDX_ERR_WORKSPACE, "mdx_hash_partition: workspace needs " +
-                                           std::to_string(L.bytes) + " bytes");
+                                           std::to_string(need) + " bytes");
     const PartArgs t = {d_keys, d_payload, n, d_keys_out, d_payload_out, d_offsets, nullptr, d_ws};
     hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
@@ -309,10 +309,10 @@ int32_t mdx_hash_partition_noalloc(const void *d_keys, const int64_t *d_payload,
     if (int32_t e = check_partition(d_keys, d_payload, n, key_type, P, d_keys_out, d_payload_out,
                                     d_offsets, W))
         return e;
-    const PartLayout L = part_layout(n, P);
-    if (L.bytes > (size_t)MDX_NOALLOC_SCRATCH_BYTES)
+    const size_t need = part_workspace_bytes(n, P, key_type);
+    if (need > (size_t)MDX_NOALLOC_SCRATCH_BYTES)
         return fail(MDX_ERR_WORKSPACE,
-                    std::string(W) + ": needs " + std::to_string(L.bytes) +
+                    std::string(W) + ": needs " + std::to_string(need) +
                         " bytes of scratch, more than the library's " +
                         std::to_string((size_t)MDX_NOALLOC_SCRATCH_BYTES) +
                         "; call mdx_hash_partition with a workspace instead");
@@ -602,7 +602,12 @@ namespace {
 // probe side would leave a few workgroups looping over many batches each).
 // The first pass partitions by (p, top q1bits) with a fan-out of at most 128
 // (long, coalesced output runs); the segmented second pass splits each of
-// those buckets by the next q2bits (at most 256 ways).
+// those buckets by the next q2bits (at most 256 ways).  Merges of at most
+// kOnePass sub-buckets are split by the first pass alone: its shorter runs
+// cost them less than a second pass over the rows and its four launches
+// (int64, P = 8: 5E5 x 5E5 rows, 256 sub-buckets, 103 us with two passes, 65
+// with one; 1.5E6, 512: 139 and 101; 3E6, 1024: 196 and 183, int32 182 and
+// 187; 6E6, 2048: 308 and 586).
 struct MergePlan {
     int qbits, q1bits, q2bits;
 };
@@ -610,8 +615,10 @@ struct MergePlan {
 // fill: average rows of the larger side per sub-bucket, as a fraction of a
 // table of `cap` rows (the join's table: the fused batch's holds more rows);
 // fanout: the first pass's largest number of destinations.
+constexpr int kOnePass = 512;
+
 MergePlan merge_plan(int64_t nL, int64_t nR, int32_t P, double fill = kJoinFill, int fanout = 128,
-                     int cap = kJoinCap)
+                     int cap = kJoinCap, int one_pass = kOnePass)
 {
     MergePlan m;
     const double per = fill * cap;
@@ -622,7 +629,7 @@ MergePlan merge_plan(int64_t nL, int64_t nR, int32_t P, double fill = kJoinFill,
     while (m.qbits > 0 && ((int64_t)P << m.qbits) > (int64_t)1 << 22)
         --m.qbits;
     for (;; --m.qbits) {
-        m.q1bits = 0;
+        m.q1bits = ((int64_t)P << m.qbits) <= one_pass ? m.qbits : 0;
         while (m.q1bits < m.qbits && ((int64_t)P << (m.q1bits + 1)) <= fanout)
             ++m.q1bits;
         m.q2bits = m.qbits - m.q1bits;
@@ -657,8 +664,8 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     M.plan = merge_plan(nL, nR, P);
     M.nA = (int64_t)P << M.plan.q1bits;
     M.S = (int64_t)P << M.plan.qbits;
-    M.pl = part_layout(nL, (int32_t)M.nA);
-    M.pr = part_layout(nR, (int32_t)M.nA);
+    M.pl = part_layout(nL, (int32_t)M.nA, kt);
+    M.pr = part_layout(nR, (int32_t)M.nA, kt);
     M.sl = seg_layout(nL, M.nA, M.plan.q2bits);
     M.sr = seg_layout(nR, M.nA, M.plan.q2bits);
     M.jl = rjoin_layout(P, M.plan.qbits, nR);
@@ -1090,15 +1097,15 @@ FusedMerge fused_merge(const mdx_merge_desc &d, int32_t idx, const Tuned &t)
     FusedMerge F;
     F.idx = idx;
     F.kt = d.key_type;
-    F.plan = merge_plan(d.n_left, d.n_right, d.P, t.fill, t.fanout, kBatchJoinCap);
+    F.plan = merge_plan(d.n_left, d.n_right, d.P, t.fill, t.fanout, kBatchJoinCap, 0);
     F.nA = (int64_t)d.P << F.plan.q1bits;
     F.S = (int64_t)d.P << F.plan.qbits;
-    const int deflt = part_rows_per_thread((int32_t)F.nA);
+    const int deflt = F.nA <= kPartSmallMaxP ? kPartRowsSmall : kPartRowsLarge;
     F.R = t.rows == 2 ? kPartRowsLarge
                       : (t.rows == 8 ? (F.nA <= kPartSmallMaxP ? kPartRowsSmall : kPartRowsLarge)
                                      : deflt);
-    F.pl = part_layout(d.n_left, (int32_t)F.nA, F.R);
-    F.pr = part_layout(d.n_right, (int32_t)F.nA, F.R);
+    F.pl = part_layout(d.n_left, (int32_t)F.nA, F.kt, F.R);
+    F.pr = part_layout(d.n_right, (int32_t)F.nA, F.kt, F.R);
     const bool two = F.plan.q2bits > 0;
     if (two) {
         F.sl = seg_layout(d.n_left, F.nA, F.plan.q2bits);
@@ -1522,7 +1529,7 @@ struct ProbeJobLayout {
 ProbeJobLayout probe_job_layout(int64_t n, int32_t P, int32_t kt)
 {
     ProbeJobLayout L;
-    L.pl = part_layout(n, P);
+    L.pl = part_layout(n, P, kt);
     L.ql = probe_layout(n, P);
     const size_t k = (size_t)(n > 0 ? n : 1);
     size_t o = 0;

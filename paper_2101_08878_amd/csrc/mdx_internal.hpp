@@ -61,18 +61,55 @@ inline Dest make_dest(int32_t P, int sbits = 0)
 }
 
 // ---- partition ------------------------------------------------------------
-// Rows per tile of the partition kernels: kBlock threads x R rows.  Small P
-// keeps one tile's rows staged in LDS; large P needs LDS for its counters.
-#ifndef MDX_PART_ROWS
-#define MDX_PART_ROWS 8
-#endif
-constexpr int kPartRowsSmall = MDX_PART_ROWS;  // tile kBlock R rows, P <= kPartSmallMaxP
-constexpr int kPartRowsLarge = 2;    // tile 1024 rows (LDS holds 16-bit counts per wave and P)
+// Rows per tile of the partition kernels: kBlock threads x R rows, R = 8, 4 or
+// 2: the largest whose tile is staged in half a CU's LDS, so that two
+// workgroups share a CU (else 2).  A tile's rows and its destinations' counts
+// share that LDS, so many destinations take smaller tiles.
+constexpr int kPartRowsSmall = 8;      // fused batches, D <= kPartSmallMaxP
+constexpr int kPartRowsLarge = 2;      // fused batches beyond
 constexpr int kPartSmallMaxP = 256;
 
-inline int part_rows_per_thread(int32_t P)
+// LDS carve-up of part_scatter (bytes, 16-byte aligned pieces).
+struct ScatterLds {
+    size_t stage_v, stage_k, stage_p, stage_d, whist, tstart, gbase, scratch, total;
+};
+
+__host__ __device__ inline size_t al16(size_t x)
 {
-    return P <= kPartSmallMaxP ? kPartRowsSmall : kPartRowsLarge;
+    return (x + 15) & ~(size_t)15;
+}
+
+// dig: the tile also stages every row's next-pass digit byte.
+__host__ __device__ inline ScatterLds scatter_lds(int T, int P, int key_bytes, bool dig)
+{
+    ScatterLds L;
+    size_t o = 0;
+    L.stage_v = o;
+    o = al16(o + (size_t)T * 8);
+    L.stage_k = o;
+    o = al16(o + (size_t)T * key_bytes);
+    L.stage_p = o;
+    o = al16(o + (size_t)T * 2);
+    L.stage_d = o;  // next-pass digit bytes (when they are written)
+    o = al16(o + (dig ? (size_t)T : 0));
+    L.whist = o;  // 16-bit counts: a tile holds at most 4096 rows
+    o = al16(o + (size_t)kWavesPerBlock * P * 2);
+    L.tstart = o;
+    o = al16(o + (size_t)P * 4);
+    L.gbase = o;
+    o = al16(o + (size_t)P * 8);
+    L.scratch = o;
+    o = al16(o + (size_t)kWavesPerBlock * 8);
+    L.total = o;
+    return L;
+}
+
+inline int part_rows_per_thread(int32_t ndest, int key_bytes)
+{
+    for (int R : {8, 4})
+        if (scatter_lds(kBlock * R, ndest, key_bytes, false).total <= kMaxLdsBytes / 2)
+            return R;
+    return 2;
 }
 
 struct PartLayout {
@@ -81,25 +118,33 @@ struct PartLayout {
     size_t cnt_off, totals_off, bytes;
 };
 
-// R: rows per thread of the tiles (0: part_rows_per_thread(P)).
-inline PartLayout part_layout(int64_t n, int32_t P, int R = 0)
+// Tiles of R rows per thread (0: part_rows_per_thread).
+inline PartLayout part_layout(int64_t n, int32_t ndest, int key_bytes, int R = 0)
 {
     PartLayout L;
-    L.rows_per_thread = R > 0 ? R : part_rows_per_thread(P);
+    L.rows_per_thread = R > 0 ? R : part_rows_per_thread(ndest, key_bytes);
     const int64_t tile = (int64_t)kBlock * L.rows_per_thread;
     L.ntiles = (n + tile - 1) / tile;
     size_t o = 0;
     L.cnt_off = o;
-    o += align_up((size_t)P * (size_t)L.ntiles * sizeof(int64_t));
+    o += align_up((size_t)ndest * (size_t)L.ntiles * sizeof(int64_t));
     L.totals_off = o;
-    o += align_up((size_t)P * sizeof(int64_t));
+    o += align_up((size_t)ndest * sizeof(int64_t));
     L.bytes = o;
     return L;
 }
 
+// What a partition asks of its caller: the layout with 1024-row tiles beyond
+// 256 destinations (at least what the tiles taken need), so that the sizes
+// mdx_hash_partition_noalloc accepts do not depend on the tiling.
+inline size_t part_workspace_bytes(int64_t n, int32_t P, int key_bytes)
+{
+    return part_layout(n, P, key_bytes, P <= 256 ? 8 : 2).bytes;
+}
+
 // One table of a partition launch: stable partition into
 // make_dest(P, sbits).ndest destinations; off has ndest + 1 entries; ws holds
-// part_layout(n, ndest).bytes.  The output is two columns, or with `rows_out`
+// part_layout(n, ndest, key bytes).bytes.  The output is two columns, or with `rows_out`
 // Rows<K> at keys_out (pay_out is null).  With dig (n bytes, rows
 // only), every output row's digit_of(h, dshift, dbits) is written beside it,
 // for the histogram of a following segmented pass.

@@ -4,7 +4,8 @@
 // "Shuffle: True"): each row goes to destination p = fmix64(key) mod P, and
 // destination p's rows are packed, in input order, into [off[p], off[p+1]).
 //
-// Three passes over tiles of T = kBlock * R rows (512 x 8 = 4096):
+// Three passes over tiles of T = kBlock * R rows (512 x 8 = 4096, fewer with
+// many destinations):
 //   part_hist       keys only: per-tile counts per destination (LDS atomics;
 //                   a wave's ballots when there are at most 4 destinations)
 //   part_scan_tiles per destination, exclusive prefix over tiles (in place)
@@ -266,41 +267,6 @@ __global__ __launch_bounds__(kBlock) void part_offsets(const int64_t *totals0, i
                                                        const int64_t *totals1, int64_t *off1, int P)
 {
     offsets_of(blockIdx.x ? totals1 : totals0, blockIdx.x ? off1 : off0, P);
-}
-
-// LDS carve-up of part_scatter (bytes, 16-byte aligned pieces).
-struct ScatterLds {
-    size_t stage_v, stage_k, stage_p, stage_d, whist, tstart, gbase, scratch, total;
-};
-
-__host__ __device__ inline size_t al16(size_t x)
-{
-    return (x + 15) & ~(size_t)15;
-}
-
-// dig: the tile also stages every row's next-pass digit byte.
-__host__ __device__ inline ScatterLds scatter_lds(int T, int P, int key_bytes, bool dig)
-{
-    ScatterLds L;
-    size_t o = 0;
-    L.stage_v = o;
-    o = al16(o + (size_t)T * 8);
-    L.stage_k = o;
-    o = al16(o + (size_t)T * key_bytes);
-    L.stage_p = o;
-    o = al16(o + (size_t)T * 2);
-    L.stage_d = o;  // next-pass digit bytes (when they are written)
-    o = al16(o + (dig ? (size_t)T : 0));
-    L.whist = o;  // 16-bit counts: a tile holds at most 4096 rows
-    o = al16(o + (size_t)kWavesPerBlock * P * 2);
-    L.tstart = o;
-    o = al16(o + (size_t)P * 4);
-    L.gbase = o;
-    o = al16(o + (size_t)P * 8);
-    L.scratch = o;
-    o = al16(o + (size_t)kWavesPerBlock * 8);
-    L.total = o;
-    return L;
 }
 
 // Exclusive prefix over a[0..P) in LDS, in place (all threads call).
@@ -750,7 +716,7 @@ PartPair<K> part_pair(const PartArgs *tables, int ntables, int D, int R)
     PartPair<K> T = {};
     for (int i = 0; i < ntables; ++i) {
         const PartArgs &a = tables[i];
-        const PartLayout L = part_layout(a.n, D, R);
+        const PartLayout L = part_layout(a.n, D, (int)sizeof(K), R);
         PartTable<K> &t = T.t[i];
         t.keys = (const K *)a.keys;
         t.pay = a.pay;
@@ -1105,13 +1071,15 @@ hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, 
 {
     if (ntables < 1 || ntables > 2)
         return hipErrorInvalidValue;
-    const bool small = part_rows_per_thread(P << sbits) == kPartRowsSmall;
+    const int R = part_rows_per_thread(P << sbits, key_bytes);
     auto run = [&](auto f) { return f(tables, ntables, P, sbits, rows_out, dshift, dbits, s); };
     if (key_bytes == 8)
-        return small ? run(run_partition<int64_t, kPartRowsSmall>)
-                     : run(run_partition<int64_t, kPartRowsLarge>);
-    return small ? run(run_partition<int32_t, kPartRowsSmall>)
-                 : run(run_partition<int32_t, kPartRowsLarge>);
+        return R == 8   ? run(run_partition<int64_t, 8>)
+               : R == 4 ? run(run_partition<int64_t, 4>)
+                        : run(run_partition<int64_t, 2>);
+    return R == 8   ? run(run_partition<int32_t, 8>)
+           : R == 4 ? run(run_partition<int32_t, 4>)
+                    : run(run_partition<int32_t, 2>);
 }
 
 hipError_t launch_seg_partition(const SegArgs *tables, int ntables, int key_bytes, int64_t nseg,

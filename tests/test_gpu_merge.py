@@ -281,3 +281,13 @@ def test_merge_batch_chunked_hot_items():
     got = dict(key=host(job.out[0]), lpay=host(job.out[1]), rpay=host(job.out[2]),
                off=host(job.out_offsets), status=int(status.item()), cap=total)
     assert_join_equals_oracle(kl, vl, kr, vr, 4, got)
+
+
+@pytest.mark.parametrize("n", [1_590_000, 1_600_000])
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+def test_merge_one_and_two_passes(n, dtype):
+    """512 sub-buckets (split by the first pass alone) and 1024 (two passes)."""
+    announce(f"merge passes {n} {np.dtype(dtype).name}")
+    kl, vl, kr, vr = match_fraction_tables(n, n // 2, 0.3, seed=n, key_dtype=dtype)
+    got = run_merge(kl, vl, kr, vr, 1)
+    assert_join_equals_oracle(kl, vl, kr, vr, 1, got)

@@ -136,3 +136,16 @@ def test_partition_key_column_not_16_byte_aligned(dtype, shift):
         want = oracle.hash_partition(keys[skip:], pay, P)
         for g, w in zip((host(ko), host(vo), host(off)), want):
             assert np.array_equal(g, w)
+
+
+@pytest.mark.parametrize("P", [290, 291, 875, 876, 1606, 1607, 1899, 1900])
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+def test_partition_tile_sizes(P, dtype):
+    """Destination counts on both sides of each tile size's limit (int64: 4096
+    rows to 290 destinations, 2048 to 1606; int32: to 875 and 1899), over
+    several tiles and a ragged tail."""
+    announce(f"partition tile sizes P={P} dtype={np.dtype(dtype).name}")
+    info = np.iinfo(dtype)
+    keys = np.random.default_rng(P).integers(info.min, info.max, N_RAGGED, dtype=np.int64,
+                                             endpoint=True).astype(dtype)
+    _assert_same(keys, np.arange(N_RAGGED, dtype=np.int64), P)
