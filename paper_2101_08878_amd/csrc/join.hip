@@ -33,6 +33,7 @@
 
 #include "mdx.h"
 #include "mdx_internal.hpp"
+#include "mdx_partition.hpp"
 
 namespace mdx {
 namespace {
@@ -160,12 +161,23 @@ __device__ __forceinline__ int shared_part(const TView &v, int64_t r0, int64_t r
     return p + 1 == v.pe || r1 <= v.off[p + 1] ? p : -1;
 }
 
+// A workgroup's number and how many there are: of a launch, or of a step
+// inside global_join's.
+struct Blk {
+    int64_t id, n;
+};
+
+__device__ __forceinline__ Blk this_block()
+{
+    return {(int64_t)blockIdx.x, (int64_t)gridDim.x};
+}
+
 __device__ __forceinline__ bool skipped(const int32_t *skip)
 {
     return skip && *skip != 0;
 }
 
-__device__ bool block_any_dup(const TView &v)
+__device__ __forceinline__ bool block_any_dup(const TView &v)
 {
     int any = 0;
     for (int p = v.pb + (int)threadIdx.x; p < v.pe; p += kBlock)
@@ -176,7 +188,7 @@ __device__ bool block_any_dup(const TView &v)
 // ---- build -----------------------------------------------------------------
 
 // One block: the table's sanitized build offsets, cleared per-partition flags.
-__device__ void table_setup_block(const int64_t *off_in, int64_t n, int64_t *off_tab,
+__device__ __forceinline__ void table_setup_block(const int64_t *off_in, int64_t n, int64_t *off_tab,
                                   int32_t *flags, int64_t *bump, int P, int64_t *scratch)
 {
     if (off_in)
@@ -196,15 +208,13 @@ __global__ __launch_bounds__(kBlock) void table_setup(const int64_t *__restrict_
     table_setup_block(off_in, n, off_tab, flags, bump, P, scratch);
 }
 
-__global__ __launch_bounds__(kBlock) void tbl_init(TView v)
+__device__ __forceinline__ void tbl_init_by(const Blk &b, const TView &v)
 {
-    if (skipped(v.skip))
-        return;
     const int64_t o0 = v.off[v.pb];
     const int64_t total = 2 * (v.off[v.pe] - o0) + 16 * (int64_t)(v.pe - v.pb);
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    const int64_t stride = (int64_t)b.n * kBlock;
     u64x2 *slots = (u64x2 *)v.slots;
-    for (int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x; s < total; s += stride) {
+    for (int64_t s = (int64_t)b.id * kBlock + threadIdx.x; s < total; s += stride) {
         const int p = slot_part(v, o0, s);
         int64_t sb, H;
         part_slots(v, o0, p, sb, H);
@@ -213,6 +223,13 @@ __global__ __launch_bounds__(kBlock) void tbl_init(TView v)
         e.y = 0;
         slots[s] = e;
     }
+}
+
+__global__ __launch_bounds__(kBlock) void tbl_init(TView v)
+{
+    if (skipped(v.skip))
+        return;
+    tbl_init_by(this_block(), v);
 }
 
 // Inserts rows of the view: with `sample`, every 2^shift-th one; otherwise
@@ -226,16 +243,14 @@ __global__ __launch_bounds__(kBlock) void tbl_init(TView v)
 // over distinct slots, in any order); four rows per thread at a time were
 // slower (4E6 distinct keys: 305 against 245 us).
 template <typename K>
-__global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int shift, bool sample,
-                                                     int32_t *status)
+__device__ __forceinline__ void tbl_insert_by(const Blk &b, const Cols &in, const TView &v, int shift,
+                                              bool sample, int32_t *status)
 {
-    if (skipped(v.skip))
-        return;
     const int64_t o0 = v.off[v.pb], n = v.off[v.pe] - o0;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    const int64_t stride = (int64_t)b.n * kBlock;
     const int step = sample ? shift : 0;  // rows o0 + i 2^step
     const int64_t sampled = !sample && shift >= 0 ? ((int64_t)1 << shift) - 1 : -1;
-    for (int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) << step; i < n;
+    for (int64_t i = ((int64_t)b.id * kBlock + threadIdx.x) << step; i < n;
          i += stride << step) {
         if (sampled >= 0 && (i & sampled) == 0)
             continue;
@@ -277,20 +292,34 @@ __global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int shift
     }
 }
 
-// Repeated-key partitions: value := 0 on every slot.
-__global__ __launch_bounds__(kBlock) void grp_reset(TView v)
+template <typename K>
+__global__ __launch_bounds__(kBlock) void tbl_insert(Cols in, TView v, int shift, bool sample,
+                                                     int32_t *status)
 {
     if (skipped(v.skip))
         return;
+    tbl_insert_by<K>(this_block(), in, v, shift, sample, status);
+}
+
+// Repeated-key partitions: value := 0 on every slot.
+__device__ __forceinline__ void grp_reset_by(const Blk &b, const TView &v)
+{
     if (!block_any_dup(v))
         return;
     const int64_t o0 = v.off[v.pb];
     const int64_t total = 2 * (v.off[v.pe] - o0) + 16 * (int64_t)(v.pe - v.pb);
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x; s < total; s += stride) {
+    const int64_t stride = (int64_t)b.n * kBlock;
+    for (int64_t s = (int64_t)b.id * kBlock + threadIdx.x; s < total; s += stride) {
         if (v.flags[slot_part(v, o0, s)])
             v.slots[2 * s + 1] = 0;
     }
+}
+
+__global__ __launch_bounds__(kBlock) void grp_reset(TView v)
+{
+    if (skipped(v.skip))
+        return;
+    grp_reset_by(this_block(), v);
 }
 
 // Slots of a thread's R rows r0, r0 + kBlock, ... (below r1): -1 where the row
@@ -332,6 +361,12 @@ constexpr int kAggMap = 2048;    // LDS map entries: slot -> rows of this workgr
 constexpr int kAggProbe = 8;     // map probes before a row goes to the slot directly
 constexpr int64_t kAggNone = -1;
 
+struct AggLds {
+    int64_t mkey[kAggMap];   // slot
+    int64_t mbase[kAggMap];  // grp_scatter: first place of this workgroup's rows
+    uint32_t mcnt[kAggMap];  // rows of this workgroup
+};
+
 __device__ __forceinline__ uint32_t agg_home(int64_t s)
 {
     return ((uint32_t)s * 0x9E3779B1u) >> (32 - 11);
@@ -360,31 +395,29 @@ __device__ __forceinline__ int agg_insert(int64_t *mkey, int64_t s)
 }
 
 // Rows of workgroup b: [o0 + b kAggRows, ...) of the view's rows.
-__device__ __forceinline__ void agg_rows(const TView &v, int64_t &o0, int64_t &r0, int64_t &r1)
+__device__ __forceinline__ void agg_rows(const Blk &b, const TView &v, int64_t &o0, int64_t &r0, int64_t &r1)
 {
     o0 = v.off[v.pb];
     const int64_t o1 = v.off[v.pe];
-    r0 = o0 + (int64_t)blockIdx.x * kAggRows;
+    r0 = o0 + b.id * kAggRows;
     r1 = r0 + kAggRows < o1 ? r0 + kAggRows : o1;
 }
 
 // value[s] += rows of the slot's key.
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
+__device__ __forceinline__ void grp_count_by(const Blk &b, AggLds &lds, const Cols &in, const TView &v)
 {
-    if (skipped(v.skip))
-        return;
     if (!block_any_dup(v))
         return;
-    __shared__ int64_t mkey[kAggMap];
-    __shared__ uint32_t mcnt[kAggMap];
+    int64_t *mkey = lds.mkey;
+    uint32_t *mcnt = lds.mcnt;
     for (int i = threadIdx.x; i < kAggMap; i += kBlock) {
         mkey[i] = kAggNone;
         mcnt[i] = 0;
     }
     __syncthreads();
     int64_t o0, r0, r1;
-    agg_rows(v, o0, r0, r1);
+    agg_rows(b, v, o0, r0, r1);
     if (r0 >= r1)
         return;
     int64_t slot[kAggPer];
@@ -409,6 +442,15 @@ __global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
             atomicAdd((unsigned long long *)&v.slots[2 * mkey[i] + 1], (unsigned long long)mcnt[i]);
 }
 
+template <typename K>
+__global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
+{
+    if (skipped(v.skip))
+        return;
+    __shared__ AggLds lds;
+    grp_count_by<K>(this_block(), lds, in, v);
+}
+
 // Give every key of a repeated-key partition its range of the grouped array:
 // gstart[s] = value[s] = (partition's first row) + running total.  Workgroup b
 // takes the slots [b kAllocSlots, (b+1) kAllocSlots), read once into
@@ -419,18 +461,15 @@ __global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
 constexpr int kAllocPer = 8;
 constexpr int64_t kAllocSlots = (int64_t)kBlock * kAllocPer;
 
-__global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
+__device__ __forceinline__ void grp_alloc_by(const Blk &b, int64_t *scratch, int64_t &s_base,
+                                             const TView &v)
 {
-    if (skipped(v.skip))
-        return;
     if (!block_any_dup(v))
         return;
-    __shared__ int64_t scratch[kWavesPerBlock];
-    __shared__ int64_t s_base;
     const int tid = threadIdx.x;
     const int64_t o0 = v.off[v.pb];
     const int64_t total = 2 * (v.off[v.pe] - o0) + 16 * (int64_t)(v.pe - v.pb);
-    const int64_t c0 = (int64_t)blockIdx.x * kAllocSlots;
+    const int64_t c0 = (int64_t)b.id * kAllocSlots;
     const int64_t c1 = c0 + kAllocSlots < total ? c0 + kAllocSlots : total;
     if (c0 >= c1)
         return;
@@ -477,28 +516,34 @@ __global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
     }
 }
 
+__global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
+{
+    if (skipped(v.skip))
+        return;
+    __shared__ int64_t scratch[kWavesPerBlock];
+    __shared__ int64_t s_base;
+    grp_alloc_by(this_block(), scratch, s_base, v);
+}
+
 // grouped[value[s]++] = payload, for every row of a repeated-key partition.
 // First the workgroup counts its rows per slot in the map (a row's count so
 // far is its rank) and reserves one range per slot; then every row takes its
 // rank's place in its slot's range (rows the map could not hold take a place
 // from the slot directly).  Slots and ranks stay in registers.
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
+__device__ __forceinline__ void grp_scatter_by(const Blk &b, AggLds &lds, const Cols &in, const TView &v)
 {
-    if (skipped(v.skip))
-        return;
     if (!block_any_dup(v))
         return;
-    __shared__ int64_t mkey[kAggMap];
-    __shared__ int64_t mbase[kAggMap];
-    __shared__ uint32_t mcnt[kAggMap];
+    int64_t *mkey = lds.mkey, *mbase = lds.mbase;
+    uint32_t *mcnt = lds.mcnt;
     for (int i = threadIdx.x; i < kAggMap; i += kBlock) {
         mkey[i] = kAggNone;
         mcnt[i] = 0;
     }
     __syncthreads();
     int64_t o0, r0, r1;
-    agg_rows(v, o0, r0, r1);
+    agg_rows(b, v, o0, r0, r1);
     if (r0 >= r1)
         return;
     int64_t slot[kAggPer];
@@ -536,14 +581,23 @@ __global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
             v.grouped[at[c]] = pay_at(in, r0 + threadIdx.x + (int64_t)c * kBlock);
 }
 
+template <typename K>
+__global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
+{
+    if (skipped(v.skip))
+        return;
+    __shared__ AggLds lds;
+    grp_scatter_by<K>(this_block(), lds, in, v);
+}
+
 // ---- probe -----------------------------------------------------------------
 
 // Block 0 plans the probe tiles; every block clears its share of the
 // chained-scan status.
-__device__ void probe_plan_blocks(const int64_t *offR, int64_t n, int P, const ProbeWs &w,
-                                  int64_t *scratch)
+__device__ __forceinline__ void probe_plan_blocks(const Blk &b, const int64_t *offR, int64_t n, int P,
+                                  const ProbeWs &w, int64_t *scratch)
 {
-    if (blockIdx.x == 0) {
+    if (b.id == 0) {
         sanitize_offsets(offR, w.off, P, n, scratch);
         int64_t carry = 0;
         for (int base = 0; base < P; base += kBlock) {
@@ -563,8 +617,8 @@ __device__ void probe_plan_blocks(const int64_t *offR, int64_t n, int P, const P
             *w.ndefer = 0;
         }
     }
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < w.max_tiles; i += stride)
+    const int64_t stride = (int64_t)b.n * kBlock;
+    for (int64_t i = (int64_t)b.id * kBlock + threadIdx.x; i < w.max_tiles; i += stride)
         w.status[i] = 0;
 }
 
@@ -574,41 +628,54 @@ __global__ __launch_bounds__(kBlock) void probe_plan(const int64_t *__restrict__
     if (skipped(skip))
         return;
     __shared__ int64_t scratch[kWavesPerBlock];
-    probe_plan_blocks(offR, n, P, w, scratch);
+    probe_plan_blocks(this_block(), offR, n, P, w, scratch);
 }
 
 // Set-up of a merge's global-table join in one block: per-partition build
 // and probe offsets taken from the first-pass offsets (every stride-th
 // entry), the table's offsets and flags, the probe plan.
-__global__ __launch_bounds__(kBlock) void fallback_setup(
-    const int64_t *__restrict__ offAL, const int64_t *__restrict__ offAR, int stride, int P,
-    int64_t n_build, int64_t n_probe, int64_t *offPL, int64_t *offPR, int64_t *off_tab,
-    int32_t *flags, int64_t *bump, ProbeWs w, const int32_t *skip)
+__device__ __forceinline__ void fallback_setup_by(const GlobalJoin &g, int64_t *scratch)
 {
-    if (skipped(skip))
-        return;
-    __shared__ int64_t scratch[kWavesPerBlock];
+    const int P = g.w_P;
     for (int p = threadIdx.x; p <= P; p += kBlock) {
-        offPL[p] = offAL[(int64_t)p * stride];
-        offPR[p] = offAR[(int64_t)p * stride];
+        g.offPL[p] = g.offAL[(int64_t)p * g.stride];
+        g.offPR[p] = g.offAR[(int64_t)p * g.strideR];
     }
     __syncthreads();
-    table_setup_block(offPL, n_build, off_tab, flags, bump, P, scratch);
-    probe_plan_blocks(offPR, n_probe, P, w, scratch);
+    table_setup_block(g.offPL, g.n_build, g.off_tab, g.v.flags, g.v.bump, P, scratch);
+    probe_plan_blocks(Blk{0, 1}, g.offPR, g.n_probe, P, g.w, scratch);
 }
 
-template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int group, ProbeWs w, ProbeOut o,
-                                                      int32_t *status)
+__global__ __launch_bounds__(kBlock) void fallback_setup(GlobalJoin g)
 {
-    if (skipped(v.skip))
+    if (skipped(g.v.skip))
         return;
+    __shared__ int64_t scratch[kWavesPerBlock];
+    fallback_setup_by(g, scratch);
+}
+
+// LDS of probe_chain and probe_expand.
+struct ChainLds {
+    int64_t tile, excl, total, cw[kProbeRows * kWavesPerBlock];
+};
+
+struct ExpandLds {
+    int64_t pre[kProbeTile];  // row prefixes of the tile
+    int64_t first[kBlock];    // first chunk of every tile of a batch
+};
+
+
+template <typename K>
+__device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, const TView &v,
+                                               int group, const ProbeWs &w, const ProbeOut &o,
+                                               int32_t *status)
+{
     constexpr int RP = kProbeRows;
     constexpr int kProbeWalk = 4;  // rows of a thread walking together
     constexpr int kCells = RP * kWavesPerBlock;  // (row step, wave)
     static_assert(kCells <= kWave, "one wave scans the cells");
-    __shared__ int64_t s_tile, s_excl, s_total;
-    __shared__ int64_t cw[kCells];
+    static_assert(sizeof(lds.cw) == kCells * 8, "one sum per cell");
+    int64_t &s_tile = lds.tile, &s_excl = lds.excl, &s_total = lds.total, *cw = lds.cw;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int64_t t_begin = w.tile_start[v.pb], t_end = w.tile_start[v.pe];
     const int64_t o0 = v.off[v.pb];
@@ -748,20 +815,28 @@ __global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int grou
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int group, ProbeWs w, ProbeOut o)
+__global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int group, ProbeWs w, ProbeOut o,
+                                                      int32_t *status)
 {
     if (skipped(v.skip))
         return;
+    __shared__ ChainLds lds;
+    probe_chain_by<K>(lds, in, v, group, w, o, status);
+}
+
+template <typename K>
+__device__ __forceinline__ void probe_expand_by(const Blk &b, ExpandLds &lds, int64_t *scratch,
+                                                const Cols &in, const TView &v, int group,
+                                                const ProbeWs &w, const ProbeOut &o)
+{
     // The deferred tiles' outputs are cut into chunks, numbered tile by tile;
     // workgroup b takes the chunks b, b + G, ...  The tiles' chunk counts are
     // read kBlock at a time (one after the other, 105 tiles took each
     // workgroup 100 us).
     constexpr int64_t CH = 4096;  // output rows per chunk
-    __shared__ int64_t pre[kProbeTile];
-    __shared__ int64_t first[kBlock];  // first chunk of tile e0 + i
-    __shared__ int64_t scratch[kWavesPerBlock];
+    int64_t *pre = lds.pre, *first = lds.first;
     const uint32_t nd = *w.ndefer;
-    const int64_t G = gridDim.x;
+    const int64_t G = b.n;
     K *out_key = (K *)o.key;
     int64_t acc = 0;  // chunks of the tiles before e0
     for (uint32_t e0 = 0; e0 < nd; e0 += kBlock) {
@@ -776,7 +851,7 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
         const int ne = (int)(nd - e0 < (uint32_t)kBlock ? nd - e0 : (uint32_t)kBlock);
         int held = -1;  // the tile whose row prefixes are in pre
         Deferred D = {};
-        for (int64_t j = acc + (((int64_t)blockIdx.x - acc) % G + G) % G; j < acc + all; j += G) {
+        for (int64_t j = acc + (((int64_t)b.id - acc) % G + G) % G; j < acc + all; j += G) {
             const int te = upper_index(first, 0, ne, j);  // the last tile that starts at or before j
             if (te != held) {
                 __syncthreads();  // pre is no longer read
@@ -810,16 +885,159 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
     }
 }
 
+template <typename K>
+__global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int group, ProbeWs w, ProbeOut o)
+{
+    if (skipped(v.skip))
+        return;
+    __shared__ ExpandLds lds;
+    __shared__ int64_t scratch[kWavesPerBlock];
+    probe_expand_by<K>(this_block(), lds, scratch, in, v, group, w, o);
+}
+
+// One block: the output offsets from the probe's chained scan.
+__device__ __forceinline__ void probe_offsets(const ProbeWs &w, int P, int64_t *offsets)
+{
+    const int64_t TT = w.tile_start[P];
+    const int64_t total = TT > 0 ? (int64_t)(ld_agent(w.status + TT - 1) & kValMask) : 0;
+    for (int p = threadIdx.x; p <= P; p += kBlock) {
+        const int64_t t = w.tile_start[p];
+        offsets[p] = t < TT ? w.tile_base[t] : total;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void probe_finalize(int P, ProbeWs w, ProbeOut o,
                                                          const int32_t *skip)
 {
     if (skipped(skip))
         return;
-    const int64_t TT = w.tile_start[P];
-    const int64_t total = TT > 0 ? (int64_t)(ld_agent(w.status + TT - 1) & kValMask) : 0;
-    for (int p = threadIdx.x; p <= P; p += kBlock) {
-        const int64_t t = w.tile_start[p];
-        o.offsets[p] = t < TT ? w.tile_base[t] : total;
+    probe_offsets(w, P, o.offsets);
+}
+
+// ---- the whole global-table join in one launch --------------------------------
+// A merge launches its global-table join always and almost never needs it:
+// eleven launches that return at once cost it 20 to 25 us of 62 (1E5 x 1E5)
+// to 88 (1E6 x 1E6).  Up to kOneLaunchRows they are one launch, which costs
+// merges that do need it up to 1.7 times the time of several (1E6 x 1E5 with
+// hot build keys: 260 us with eleven launches, 442 with one; 4E6 x 4E5: 565
+// and 903): a step's workgroups are items, handed out in order by
+// a ticket counter, and an item of a step first waits until every item of the
+// steps before it is done (they were all handed out before, to running
+// workgroups, so the wait ends).
+enum JoinStep { kPartHist, kPartScan, kPartOffsets, kPartScatter, kSetup, kInit, kSample, kInsert, kReset, kCount, kAlloc, kScatter, kProbe, kExpand,
+                kFinal, kJoinSteps };
+
+struct JoinSteps {
+    uint32_t first[kJoinSteps + 1];  // first item of every step
+    uint32_t *sync;                  // ticket, items done (zero before the launch)
+    // workgroups' shares of the rows (kCount, kScatter) and slots (kAlloc)
+    int64_t shares_rows, shares_slots;
+};
+
+template <typename K>
+__global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols build, Cols probe,
+                                                         int shift, PartTable<K> pt, Dest pd,
+                                                         JoinSteps t)
+{
+    if (skipped(g.v.skip))
+        return;
+    __shared__ union {
+        AggLds agg;
+        ChainLds chain;
+        ExpandLds expand;
+        uint32_t hist[kProbePartMax];
+        alignas(16) unsigned char tile[scatter_lds(kBlock * kProbePartRows, kProbePartMax,
+                                                   (int)sizeof(K), false)
+                                           .total];
+    } lds;
+    __shared__ int64_t scratch[kWavesPerBlock];
+    __shared__ int64_t s_base;
+    __shared__ uint32_t s_item;
+    __shared__ int s_ok;
+    int ready = 0;  // the steps before this one are done
+    for (;;) {
+        if (threadIdx.x == 0)
+            s_item = atomicAdd(t.sync, 1u);
+        __syncthreads();
+        const uint32_t item = s_item;
+        if (item >= t.first[kJoinSteps])
+            return;
+        int step = 0;
+        while (item >= t.first[step + 1])
+            ++step;
+        if (step > ready) {
+            if (threadIdx.x == 0) {
+                s_ok = 1;
+                int64_t polls = 0;
+                while (__hip_atomic_load(t.sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                       t.first[step]) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (++polls > kSpinLimit) {
+                        or_status(g.status, MDX_DEV_SCAN_TIMEOUT);
+                        s_ok = 0;
+                        break;
+                    }
+                }
+            }
+            // what the steps before wrote is read afresh
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __syncthreads();
+            if (!s_ok)
+                return;
+            ready = step;
+        }
+        const Blk b = {(int64_t)(item - t.first[step]),
+                       (int64_t)(t.first[step + 1] - t.first[step])};
+        switch (step) {
+        case kPartHist:
+            for (int64_t k = b.id; k < pt.ntiles; k += b.n, __syncthreads())
+                hist_tile<K, kProbePartRows, false>(pt, k, pd, lds.hist);
+            break;
+        case kPartScan: {
+            const int lane = threadIdx.x & (kWave - 1);
+            for (int64_t d = b.id * kWavesPerBlock + threadIdx.x / kWave; d < pd.ndest;
+                 d += b.n * kWavesPerBlock) {
+                const int64_t total = wave_scan_row(pt.cnt + d * pt.ntiles, pt.ntiles, lane);
+                if (lane == 0)
+                    pt.totals[d] = total;
+            }
+            break;
+        }
+        case kPartOffsets: offsets_of(pt.totals, pt.off, pd.ndest, scratch); break;
+        case kPartScatter:
+            for (int64_t k = b.id; k < pt.ntiles; k += b.n, __syncthreads())
+                part_scatter_tile<K, kProbePartRows, true, false>(pt, k, pd, 0, 0, lds.tile);
+            break;
+        case kSetup: fallback_setup_by(g, scratch); break;
+        case kInit: tbl_init_by(b, g.v); break;
+        case kSample: tbl_insert_by<K>(b, build, g.v, shift, true, g.status); break;
+        case kInsert: tbl_insert_by<K>(b, build, g.v, shift, false, g.status); break;
+        case kReset: grp_reset_by(b, g.v); break;
+        case kCount:
+            for (Blk k = b; k.id < t.shares_rows; k.id += b.n, __syncthreads())
+                grp_count_by<K>(k, lds.agg, build, g.v);
+            break;
+        case kAlloc:
+            for (Blk k = b; k.id < t.shares_slots; k.id += b.n, __syncthreads())
+                grp_alloc_by(k, scratch, s_base, g.v);
+            break;
+        case kScatter:
+            for (Blk k = b; k.id < t.shares_rows; k.id += b.n, __syncthreads())
+                grp_scatter_by<K>(k, lds.agg, build, g.v);
+            break;
+        case kProbe: probe_chain_by<K>(lds.chain, probe, g.v, 0, g.w, g.o, g.status); break;
+        case kExpand: probe_expand_by<K>(b, lds.expand, scratch, probe, g.v, 0, g.w, g.o); break;
+        default: probe_offsets(g.w, g.w_P, g.o.offsets); break;
+        }
+        // every wave's writes have reached the L2, then they are written
+        // back, before the item counts as done
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(t.sync + 1, 1u);
+        }
     }
 }
 
@@ -1181,14 +1399,69 @@ hipError_t launch_build(const Cols &table, int key_bytes, const TView &v, int64_
     return run_build<int32_t>(table, v, rows, status, max_blocks, s);
 }
 
-hipError_t launch_fallback_setup(const int64_t *offAL, const int64_t *offAR, int stride,
-                                 int32_t P, int64_t n_build, int64_t n_probe, int64_t *offPL,
-                                 int64_t *offPR, int64_t *off_tab, int32_t *flags, int64_t *bump,
-                                 const ProbeWs &w, const int32_t *skip, hipStream_t s)
+template <typename K>
+hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoin &g,
+                           const ProbePart &pp, bool one, uint32_t *sync, hipStream_t s)
 {
-    hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, offAL, offAR, stride, P,
-                       n_build, n_probe, offPL, offPR, off_tab, flags, bump, w, skip);
+    // workgroups of 2048 rows (16384 left most of the device idle at 4E6
+    // rows: 725 against 567 us), at most a full device
+    const int full = table_grid(0);
+    auto blocks = [&](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, full); };
+    const int shift = sample_shift(g.n_build);
+    if (!one) {
+        hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, g);
+        hipError_t e = run_build<K>(build, g.v, g.n_build, g.status, blocks(g.n_build), s);
+        if (e != hipSuccess)
+            return e;
+        return run_probe_group<K>(probe, g.v, 0, g.w, g.o, g.status, blocks(g.n_probe), s);
+    }
+    const int64_t slots = 2 * g.n_build + 16 * (int64_t)g.w_P;
+    JoinSteps t;
+    t.sync = sync;
+    t.shares_rows = std::max<int64_t>(1, (g.n_build + kAggRows - 1) / kAggRows);
+    t.shares_slots = std::max<int64_t>(1, (slots + kAllocSlots - 1) / kAllocSlots);
+    // The ticket and the count of done items are one address each, so more
+    // workgroups make every step's end longer (1E6 rows: 634 us with 512 of
+    // them, 442 with 256, 591 with 64).
+    const int64_t G = std::min<int64_t>(256, blocks(g.n_build));
+    auto most = [&](int64_t items) { return std::min<int64_t>(items, G); };
+    // (the expansion's work is the output rows, which can be many for few
+    // probe rows)
+    PartTable<K> pt = {};
+    if (pp.off) {
+        const PartLayout L = part_layout(pp.n, pp.d.ndest, (int)sizeof(K), kProbePartRows);
+        pt.keys = (const K *)pp.keys;
+        pt.pay = pp.pay;
+        pt.n = pp.n;
+        pt.ntiles = L.ntiles;
+        pt.rows_out = make_rows<K>(pp.rows_out, pp.n);
+        pt.off = pp.off;
+        pt.cnt = (int64_t *)((char *)pp.ws + L.cnt_off);
+        pt.totals = (int64_t *)((char *)pp.ws + L.totals_off);
+    }
+    const int64_t ptiles = std::min<int64_t>(pt.ntiles, 256);
+    const int64_t n[kJoinSteps] = {ptiles, pp.off ? (pp.d.ndest + kWavesPerBlock - 1) / kWavesPerBlock : 0,
+                                   pp.off ? 1 : 0, ptiles,
+                                   1, G, shift >= 0 ? kSampleBlocks : 0, most(blocks(g.n_build)), G,
+                                   most(t.shares_rows), most(t.shares_slots), most(t.shares_rows),
+                                   most(blocks(g.n_probe)), 256, 1};
+    t.first[0] = 0;
+    for (int i = 0; i < kJoinSteps; ++i)
+        t.first[i + 1] = t.first[i] + (uint32_t)n[i];
+    hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
+                       shift, pt, pp.d, t);
     return hipGetLastError();
+}
+
+
+hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_bytes,
+                              const GlobalJoin &g, const ProbePart &pp, bool one, uint32_t *sync,
+                              hipStream_t s)
+{
+    if (pp.off && (!one || pp.d.ndest > kProbePartMax))
+        return hipErrorInvalidValue;
+    return key_bytes == 8 ? run_global_join<int64_t>(build, probe, g, pp, one, sync, s)
+                          : run_global_join<int32_t>(build, probe, g, pp, one, sync, s);
 }
 
 hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const ProbeWs &w,

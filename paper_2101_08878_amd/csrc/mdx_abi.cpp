@@ -610,6 +610,7 @@ namespace {
 // 187; 6E6, 2048: 308 and 586).
 struct MergePlan {
     int qbits, q1bits, q2bits;
+    int qpbits;  // q1bits of a two-pass split: the order of the global-table join's output
 };
 
 // fill: average rows of the larger side per sub-bucket, as a fraction of a
@@ -629,13 +630,17 @@ MergePlan merge_plan(int64_t nL, int64_t nR, int32_t P, double fill = kJoinFill,
     while (m.qbits > 0 && ((int64_t)P << m.qbits) > (int64_t)1 << 22)
         --m.qbits;
     for (;; --m.qbits) {
-        m.q1bits = ((int64_t)P << m.qbits) <= one_pass ? m.qbits : 0;
+        m.q1bits = 0;
         while (m.q1bits < m.qbits && ((int64_t)P << (m.q1bits + 1)) <= fanout)
             ++m.q1bits;
+        m.qpbits = m.q1bits;
+        if (((int64_t)P << m.qbits) <= one_pass)
+            m.q1bits = m.qbits;
         m.q2bits = m.qbits - m.q1bits;
         while (m.q2bits > 8) {  // the segmented pass splits at most 256 ways
             ++m.q1bits;
             --m.q2bits;
+            m.qpbits = m.q1bits;
         }
         // the first pass handles at most MDX_MAX_P destinations
         if (m.qbits == 0 || ((int64_t)P << m.q1bits) <= MDX_MAX_P)
@@ -646,6 +651,7 @@ MergePlan merge_plan(int64_t nL, int64_t nR, int32_t P, double fill = kJoinFill,
 
 struct MergeLayout {
     MergePlan plan;
+    bool again;     // the global-table join partitions the probe table again
     int64_t nA, S;  // first-pass destinations, sub-buckets
     PartLayout pl, pr;
     SegLayout sl, sr;
@@ -653,7 +659,7 @@ struct MergeLayout {
     TableLayout tl;
     ProbeLayout ql;
     size_t partL_off, partR_off, l1_off, r1_off, offAL_off, offAR_off, offPL_off, offPR_off,
-        digL_off, digR_off, segL_off, segR_off, l2_off, r2_off, subL_off, subR_off, rjoin_off, table_off, probe_off, bytes;
+        digL_off, digR_off, segL_off, segR_off, l2_off, r2_off, partP_off, offP_off, subL_off, subR_off, rjoin_off, table_off, probe_off, bytes;
 };
 
 // chunked: the merge joins oversized build sub-buckets in chunks and has no
@@ -691,7 +697,13 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     take(M.segL_off, two ? M.sl.bytes : 0);
     take(M.segR_off, two ? M.sr.bytes : 0);
     take(M.l2_off, two ? rows_bytes((int64_t)kL, kt) : 0);
-    take(M.r2_off, two ? rows_bytes((int64_t)kR, kt) : 0);
+    // the probe table in a two-pass split's order, for the global-table join
+    // of a one-pass merge
+    M.again = !chunked && M.plan.qpbits != M.plan.q1bits;
+    const int32_t nP = P << M.plan.qpbits;
+    take(M.r2_off, two || M.again ? rows_bytes((int64_t)kR, kt) : 0);
+    take(M.partP_off, M.again ? part_layout(nR, nP, kt, kProbePartRows).bytes : 0);
+    take(M.offP_off, M.again ? (size_t)(nP + 1) * 8 : 0);
     take(M.subL_off, two ? (size_t)(M.S + 1) * 8 : 0);
     take(M.subR_off, two ? (size_t)(M.S + 1) * 8 : 0);
     take(M.rjoin_off, M.jl.bytes);
@@ -815,26 +827,32 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     int64_t *offPL = (int64_t *)(b + M.offPL_off), *offPR = (int64_t *)(b + M.offPR_off);
     mdx_table t = carve_table(b + M.table_off, M.tl.bytes, n_left, P, key_type);
     const ProbeWs w = probe_ws(b + M.probe_off, M.ql);
-    if (e == hipSuccess)
-        e = launch_fallback_setup(offAL, offAR, 1 << pl.q1bits, P, n_left, n_right, offPL, offPR,
-                                  t.d_offsets, t.d_flags, t.d_bump, w,
-                                  (const int32_t *)jw.plan_out + 1, stream);
     TView v = make_view(t, t.d_offsets, 0, P);
     v.skip = (const int32_t *)jw.plan_out + 1;
-    // grids sized to the rows (2048 per workgroup; 16384 left most of the
-    // device idle at 4E6 rows: 725 against 567 us); the launches mostly
-    // return at once
-    auto blocks = [](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, 1 << 20); };
+    GlobalJoin g = {offAL,   offAR, offPL, offPR, t.d_offsets, n_left,
+                    n_right, 1 << pl.q1bits, 1 << pl.q1bits, P, v, w,
+                    o,       d_status};
+    // A merge split in one pass has its probe rows in another order than one
+    // split in two passes; its global-table join partitions them again, so
+    // that its output order does not depend on the split.
+    ProbePart pp = {};
+    const void *probe = r1;
+    if (M.again) {
+        probe = b + M.r2_off;
+        pp = {d.d_right_keys, d.d_right_payload, n_right, b + M.r2_off,
+              (int64_t *)(b + M.offP_off), b + M.partP_off, make_dest(P, pl.qpbits)};
+        g.offAR = pp.off;
+        g.strideR = 1 << pl.qpbits;
+    }
+    const bool one = M.again || n_left + n_right <= kOneLaunchRows;
+    // built from the final rows: a hot key's rows, and those of neighbouring
+    // slots, are together there
     if (e == hipSuccess)
-        // the final rows: of a hot key's, and of a sub-bucket's slots, all are
-        // together
-        e = launch_build(cols_of_rows(lrows, n_left, key_type), key_type, v, n_left, d_status,
-                         blocks(n_left), stream);
+        e = launch_global_join(cols_of_rows(lrows, n_left, key_type),
+                               cols_of_rows(probe, n_right, key_type), key_type, g, pp, one,
+                               jw.join_sync, stream);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of_rows(r1, n_right, key_type), key_type, P, v, 0, w, o,
-                               d_status, blocks(n_right), stream);
-    if (e == hipSuccess)
-        e = launch_merge_finalize(pl.qbits, jw, &w, o, stream);
+        e = launch_merge_finalize(pl.qbits, jw, one ? nullptr : &w, o, stream);
     return e;
 }
 

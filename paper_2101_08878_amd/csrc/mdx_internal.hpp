@@ -74,15 +74,15 @@ struct ScatterLds {
     size_t stage_v, stage_k, stage_p, stage_d, whist, tstart, gbase, scratch, total;
 };
 
-__host__ __device__ inline size_t al16(size_t x)
+__host__ __device__ constexpr size_t al16(size_t x)
 {
     return (x + 15) & ~(size_t)15;
 }
 
 // dig: the tile also stages every row's next-pass digit byte.
-__host__ __device__ inline ScatterLds scatter_lds(int T, int P, int key_bytes, bool dig)
+__host__ __device__ constexpr ScatterLds scatter_lds(int T, int P, int key_bytes, bool dig)
 {
-    ScatterLds L;
+    ScatterLds L = {};
     size_t o = 0;
     L.stage_v = o;
     o = al16(o + (size_t)T * 8);
@@ -355,6 +355,7 @@ struct RJoinWs {
     uint64_t *plan;         // chained scan of the planning workgroups
     uint32_t *ticket;
     uint32_t *plan_ticket;
+    uint32_t *join_sync;    // [2] of the global-table join
     // the plan's results: the number of items, and 1 if every build
     // sub-bucket fits an LDS table, else 0 (together, for one load)
     uint32_t *plan_out;
@@ -373,6 +374,7 @@ inline RJoinWs rjoin_ws(void *base, const RJoinLayout &L, int32_t P)
     w.plan = (uint64_t *)(b + L.plan_off);
     w.ticket = (uint32_t *)(b + L.misc_off);
     w.plan_ticket = w.ticket + 1;
+    w.join_sync = w.ticket + 16;
     w.plan_out = w.ticket + 32;  // not on the tickets' cache line
     w.S = L.S;
     w.max_items = L.max_items;
@@ -537,14 +539,45 @@ hipError_t launch_build(const Cols &table, int key_bytes, const TView &v,
 hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab, int32_t *flags,
                               int64_t *bump, int32_t P, hipStream_t s);
 
-// A merge's global-table join set-up, in one launch (nothing when *skip):
-// offPL / offPR[p] = offAL / offAR[p stride] (per-partition offsets from the
-// first pass's), then launch_table_setup(offPL, n_build, ...) and
-// launch_probe_plan(offPR, n_probe, ...).
-hipError_t launch_fallback_setup(const int64_t *offAL, const int64_t *offAR, int stride,
-                                 int32_t P, int64_t n_build, int64_t n_probe, int64_t *offPL,
-                                 int64_t *offPR, int64_t *off_tab, int32_t *flags, int64_t *bump,
-                                 const ProbeWs &w, const int32_t *skip, hipStream_t s);
+// A merge's global-table join: nothing when *v.skip, else per-partition
+// offsets from the first pass's (offPL[p] = offAL[p stride], offPR[p] =
+// offAR[p strideR]),
+// the table built from `build`, probed with `probe`, the output and its
+// offsets (those by merge_finalize when it takes several launches).  one: in
+// one launch.  sync: two zeroed counters.
+constexpr int64_t kOneLaunchRows = (int64_t)1 << 21;
+
+struct GlobalJoin {
+    const int64_t *offAL, *offAR;
+    int64_t *offPL, *offPR, *off_tab;
+    int64_t n_build, n_probe;
+    int32_t stride, strideR, w_P;
+    TView v;
+    ProbeWs w;
+    ProbeOut o;
+    int32_t *status;
+};
+
+// The probe table's partition as a two-pass merge's first pass makes it, for
+// a merge split in one pass: the global-table join's output rows follow this
+// order whatever the split.  pay null: not needed, `probe` has it already.
+// ws: part_layout(n, d.ndest, key_bytes, kProbePartRows).bytes.
+constexpr int kProbePartRows = 4;
+constexpr int kProbePartMax = 256;  // destinations
+
+struct ProbePart {
+    const void *keys;
+    const int64_t *pay;
+    int64_t n;
+    void *rows_out;  // Rows<K>: what `probe` reads
+    int64_t *off;    // [d.ndest + 1]: g.offAR with g.strideR
+    void *ws;
+    Dest d;
+};
+
+hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_bytes,
+                              const GlobalJoin &g, const ProbePart &pp, bool one,
+                              uint32_t *sync, hipStream_t s);
 
 // Probe: plan tiles from the probe offsets (sanitized for n probe rows, once
 // per probe), probe one view (group g), finalize the output offsets.

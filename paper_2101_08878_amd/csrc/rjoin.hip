@@ -301,6 +301,7 @@ __global__ __launch_bounds__(kBlock) void rj_plan_init(RJoinWs w, int chunks)
         w.plan_out[1] = 1;
         *w.ticket = 0;
         *w.plan_ticket = 0;
+        w.join_sync[0] = w.join_sync[1] = 0;
     }
 }
 
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict_
     if (threadIdx.x == 0) {
         w.plan_out[1] = over && !chunked ? 0 : 1;
         *w.ticket = 0;
+        w.join_sync[0] = w.join_sync[1] = 0;
         w.plan_out[0] = (uint32_t)total;
         w.istart[m] = (uint32_t)total;
     }

@@ -40,7 +40,7 @@ KERNEL_FILES = {
     "seg_scatter": "partition.hip", "rj_join": "rjoin.hip", "transpose_sum": "transpose.hip",
     "transpose_sum_tiles": "transpose.hip",
 }
-SHARED_FILES = ("mdx_device.hpp", "mdx_internal.hpp")
+SHARED_FILES = ("mdx_device.hpp", "mdx_internal.hpp", "mdx_partition.hpp")
 
 
 _CODE_TOKENS = re.compile(r'"(?:\\.|[^"\\])*"|\'(?:\\.|[^\'\\])*\'|//[^\n]*|/\*.*?\*/|\s+', re.S)

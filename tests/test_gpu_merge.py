@@ -291,3 +291,41 @@ def test_merge_one_and_two_passes(n, dtype):
     kl, vl, kr, vr = match_fraction_tables(n, n // 2, 0.3, seed=n, key_dtype=dtype)
     got = run_merge(kl, vl, kr, vr, 1)
     assert_join_equals_oracle(kl, vl, kr, vr, 1, got)
+
+
+@pytest.mark.parametrize("n,hot,P", [
+    (3457, 3457, 1),           # smallest merge that launches it, one key
+    (20_000, 5_000, 7),
+    (140_000, 9_000, 300),     # a sampled build; more partitions than workgroups
+    (1_000_000, 60_000, 8),
+    (2_097_152 - 50_000, 4_000, 3),  # the most rows one launch takes
+    (2_097_153 - 50_000, 4_000, 3),  # several launches
+])
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+def test_merge_global_join_launches(n, hot, P, dtype):
+    """The global-table join as one launch and as several: one build key
+    repeated `hot` times (more than an LDS table's rows), the other build keys
+    twice each, 50000 probe rows, the hot key among them 5 times.  Run
+    twice: the second call finds the first one's workspace contents."""
+    announce(f"global-table join {n} rows, hot key x {hot}, P={P} {np.dtype(dtype).name}")
+    import torch
+
+    import paper_2101_08878_amd as mdx
+    rng = np.random.default_rng(n + P)
+    kl = np.concatenate([np.full(hot, -7), np.repeat(np.arange((n - hot + 1) // 2), 2)[:n - hot]])
+    kl = kl[rng.permutation(n)].astype(dtype)
+    kr = np.concatenate([np.full(5, -7), rng.integers(0, max(n, 2), 49_995)])
+    kr = kr[rng.permutation(kr.size)].astype(dtype)
+    vl, vr = np.arange(n, dtype=np.int64), np.arange(kr.size, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    kt = mdx.MDX_KEY_I64 if dtype == np.int64 else mdx.MDX_KEY_I32
+    ws = torch.full((mdx.mdx_merge_workspace_bytes(n, kr.size, P, kt),), 0xa5, dtype=torch.uint8,
+                    device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ins = [dev(a) for a in (kl, vl, kr, vr)]
+    for _ in range(2):
+        ok, ol, orr, off = mdx.mdx_merge(*ins, P, out_capacity=total, workspace=ws, status=status)
+        torch.cuda.synchronize()
+        got = dict(key=host(ok), lpay=host(ol), rpay=host(orr), off=host(off),
+                   status=int(status.item()), cap=total)
+        assert_join_equals_oracle(kl, vl, kr, vr, P, got)
