@@ -443,12 +443,13 @@ __device__ __forceinline__ void grp_count_by(const Blk &b, AggLds &lds, const Co
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v)
+__global__ __launch_bounds__(kBlock) void grp_count(Cols in, TView v, int64_t shares)
 {
     if (skipped(v.skip))
         return;
     __shared__ AggLds lds;
-    grp_count_by<K>(this_block(), lds, in, v);
+    for (Blk b = this_block(); b.id < shares; b.id += b.n, __syncthreads())
+        grp_count_by<K>(b, lds, in, v);
 }
 
 // Give every key of a repeated-key partition its range of the grouped array:
@@ -516,13 +517,14 @@ __device__ __forceinline__ void grp_alloc_by(const Blk &b, int64_t *scratch, int
     }
 }
 
-__global__ __launch_bounds__(kBlock) void grp_alloc(TView v)
+__global__ __launch_bounds__(kBlock) void grp_alloc(TView v, int64_t shares)
 {
     if (skipped(v.skip))
         return;
     __shared__ int64_t scratch[kWavesPerBlock];
     __shared__ int64_t s_base;
-    grp_alloc_by(this_block(), scratch, s_base, v);
+    for (Blk b = this_block(); b.id < shares; b.id += b.n, __syncthreads())
+        grp_alloc_by(b, scratch, s_base, v);
 }
 
 // grouped[value[s]++] = payload, for every row of a repeated-key partition.
@@ -582,20 +584,22 @@ __device__ __forceinline__ void grp_scatter_by(const Blk &b, AggLds &lds, const 
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v)
+__global__ __launch_bounds__(kBlock) void grp_scatter(Cols in, TView v, int64_t shares)
 {
     if (skipped(v.skip))
         return;
     __shared__ AggLds lds;
-    grp_scatter_by<K>(this_block(), lds, in, v);
+    for (Blk b = this_block(); b.id < shares; b.id += b.n, __syncthreads())
+        grp_scatter_by<K>(b, lds, in, v);
 }
 
 // ---- probe -----------------------------------------------------------------
 
 // Block 0 plans the probe tiles; every block clears its share of the
 // chained-scan status.
-__device__ __forceinline__ void probe_plan_blocks(const Blk &b, const int64_t *offR, int64_t n, int P,
-                                  const ProbeWs &w, int64_t *scratch)
+__device__ __forceinline__ void probe_plan_blocks(const Blk &b, const int64_t *offR, int64_t n,
+                                                  int P, const ProbeWs &w, int64_t *offsets,
+                                                  int64_t *scratch)
 {
     if (b.id == 0) {
         sanitize_offsets(offR, w.off, P, n, scratch);
@@ -616,6 +620,9 @@ __device__ __forceinline__ void probe_plan_blocks(const Blk &b, const int64_t *o
             w.tile_start[P] = carry;
             *w.ndefer = 0;
         }
+        if (carry == 0)  // no tile will write the output offsets
+            for (int p = threadIdx.x; p <= P; p += kBlock)
+                offsets[p] = 0;
     }
     const int64_t stride = (int64_t)b.n * kBlock;
     for (int64_t i = (int64_t)b.id * kBlock + threadIdx.x; i < w.max_tiles; i += stride)
@@ -623,12 +630,10 @@ __device__ __forceinline__ void probe_plan_blocks(const Blk &b, const int64_t *o
 }
 
 __global__ __launch_bounds__(kBlock) void probe_plan(const int64_t *__restrict__ offR, int64_t n,
-                                                     int P, ProbeWs w, const int32_t *skip)
+                                                     int P, ProbeWs w, int64_t *offsets)
 {
-    if (skipped(skip))
-        return;
     __shared__ int64_t scratch[kWavesPerBlock];
-    probe_plan_blocks(this_block(), offR, n, P, w, scratch);
+    probe_plan_blocks(this_block(), offR, n, P, w, offsets, scratch);
 }
 
 // Set-up of a merge's global-table join in one block: per-partition build
@@ -643,7 +648,7 @@ __device__ __forceinline__ void fallback_setup_by(const GlobalJoin &g, int64_t *
     }
     __syncthreads();
     table_setup_block(g.offPL, g.n_build, g.off_tab, g.v.flags, g.v.bump, P, scratch);
-    probe_plan_blocks(Blk{0, 1}, g.offPR, g.n_probe, P, g.w, scratch);
+    probe_plan_blocks(Blk{0, 1}, g.offPR, g.n_probe, P, g.w, g.o.offsets, scratch);
 }
 
 __global__ __launch_bounds__(kBlock) void fallback_setup(GlobalJoin g)
@@ -664,6 +669,20 @@ struct ExpandLds {
     int64_t first[kBlock];    // first chunk of every tile of a batch
 };
 
+
+// One wave: the output offsets that tile `tile` of partition p settles, whose
+// M output rows start at ex: its partition's and those of empty ones right
+// before it when it starts p, those after p when it is the last tile.
+__device__ __forceinline__ void tile_offsets(const ProbeWs &w, int P, int p, int64_t tile,
+                                             int64_t ex, int64_t M, int lane, int64_t *offsets)
+{
+    if (tile == w.tile_start[p])
+        for (int q = p - lane; q >= 0 && w.tile_start[q] == tile; q -= kWave)
+            offsets[q] = ex;
+    if (tile + 1 == w.tile_start[P])
+        for (int q = p + 1 + lane; q <= P; q += kWave)
+            offsets[q] = ex + M;
+}
 
 template <typename K>
 __device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, const TView &v,
@@ -770,8 +789,8 @@ __device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, co
             if (lane == 0) {
                 s_excl = ex;
                 s_total = M;
-                w.tile_base[tile] = ex;
             }
+            tile_offsets(w, v.pe, p, tile, ex, M, lane, o.offsets);
         }
         __syncthreads();
         const int64_t E = s_excl, M = s_total;
@@ -895,41 +914,24 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
     probe_expand_by<K>(this_block(), lds, scratch, in, v, group, w, o);
 }
 
-// One block: the output offsets from the probe's chained scan.
-__device__ __forceinline__ void probe_offsets(const ProbeWs &w, int P, int64_t *offsets)
-{
-    const int64_t TT = w.tile_start[P];
-    const int64_t total = TT > 0 ? (int64_t)(ld_agent(w.status + TT - 1) & kValMask) : 0;
-    for (int p = threadIdx.x; p <= P; p += kBlock) {
-        const int64_t t = w.tile_start[p];
-        offsets[p] = t < TT ? w.tile_base[t] : total;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void probe_finalize(int P, ProbeWs w, ProbeOut o,
-                                                         const int32_t *skip)
-{
-    if (skipped(skip))
-        return;
-    probe_offsets(w, P, o.offsets);
-}
-
 // ---- the whole global-table join in one launch --------------------------------
 // A merge launches its global-table join always and almost never needs it:
-// eleven launches that return at once cost it 20 to 25 us of 62 (1E5 x 1E5)
-// to 88 (1E6 x 1E6).  Up to kOneLaunchRows they are one launch, which costs
-// merges that do need it up to 1.7 times the time of several (1E6 x 1E5 with
-// hot build keys: 260 us with eleven launches, 442 with one; 4E6 x 4E5: 565
-// and 903): a step's workgroups are items, handed out in order by
-// a ticket counter, and an item of a step first waits until every item of the
-// steps before it is done (they were all handed out before, to running
-// workgroups, so the wait ends).
+// ten launches that return at once cost it 20 to 25 us of 62 (1E5 x 1E5) to 88
+// (1E6 x 1E6).  Up to kOneLaunchRows they are one launch: a step's workgroups
+// are items, handed out in order by a ticket counter, and an item of a step
+// first waits until every item of the steps before it is done (they were all
+// handed out before, to running workgroups, so the wait ends).  Merges that do
+// need the join then take up to 1.6 times as long (1E6 x 1E5 with hot build
+// keys: 260 us with ten launches, 406 with one; 4E6 x 4E5: 565 and 846): every
+// item writes its L2 back.
 enum JoinStep { kPartHist, kPartScan, kPartOffsets, kPartScatter, kSetup, kInit, kSample, kInsert, kReset, kCount, kAlloc, kScatter, kProbe, kExpand,
-                kFinal, kJoinSteps };
+                kJoinSteps };
 
 struct JoinSteps {
     uint32_t first[kJoinSteps + 1];  // first item of every step
-    uint32_t *sync;                  // ticket, items done (zero before the launch)
+    // ticket, items done, items done at the end of the last finished step
+    // (zero before the launch; kSyncStride apart)
+    uint32_t *sync;
     // workgroups' shares of the rows (kCount, kScatter) and slots (kAlloc)
     int64_t shares_rows, shares_slots;
 };
@@ -969,9 +971,10 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
             if (threadIdx.x == 0) {
                 s_ok = 1;
                 int64_t polls = 0;
-                while (__hip_atomic_load(t.sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                       t.first[step]) {
-                    __builtin_amdgcn_s_sleep(1);
+                // (not the count itself: reads of it would slow its additions)
+                while (__hip_atomic_load(t.sync + 2 * kSyncStride, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) < t.first[step]) {
+                    __builtin_amdgcn_s_sleep(8);
                     if (++polls > kSpinLimit) {
                         or_status(g.status, MDX_DEV_SCAN_TIMEOUT);
                         s_ok = 0;
@@ -1026,8 +1029,7 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
                 grp_scatter_by<K>(k, lds.agg, build, g.v);
             break;
         case kProbe: probe_chain_by<K>(lds.chain, probe, g.v, 0, g.w, g.o, g.status); break;
-        case kExpand: probe_expand_by<K>(b, lds.expand, scratch, probe, g.v, 0, g.w, g.o); break;
-        default: probe_offsets(g.w, g.w_P, g.o.offsets); break;
+        default: probe_expand_by<K>(b, lds.expand, scratch, probe, g.v, 0, g.w, g.o); break;
         }
         // every wave's writes have reached the L2, then they are written
         // back, before the item counts as done
@@ -1036,7 +1038,9 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
         __syncthreads();
         if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            atomicAdd(t.sync + 1, 1u);
+            if (atomicAdd(t.sync + kSyncStride, 1u) + 1 == t.first[step + 1])
+                __hip_atomic_store(t.sync + 2 * kSyncStride, t.first[step + 1], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -1266,18 +1270,10 @@ __global__ __launch_bounds__(kBlock) void cnt_finalize(const uint64_t *__restric
         out_offsets[P] = carry;
 }
 
-// Workgroups of the grid-stride build and probe kernels: a full device, or
-// fewer when the caller sizes the grid to its rows (max_blocks > 0).
-static int table_grid(int max_blocks)
-{
-    const int full = device_fill_blocks();
-    return max_blocks > 0 && max_blocks < full ? max_blocks : full;
-}
-
 // Rows of a build's sample, every 2^shift-th; -1: no sample (few workgroups
 // insert the rows at all).
-constexpr int kSampleBlocks = 16;
 constexpr int64_t kSampleRows = 32768;
+constexpr int kSampleBlocks = kSampleRows / kBlock;
 
 static int sample_shift(int64_t rows)
 {
@@ -1287,20 +1283,22 @@ static int sample_shift(int64_t rows)
     return rows <= 4 * kSampleRows ? -1 : shift;
 }
 
+// G: workgroups of the grid-stride kernels.
 template <typename K>
-hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *status, int max_blocks, hipStream_t s)
+hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *status, int G,
+                     hipStream_t s)
 {
-    const int G = table_grid(max_blocks);
-    // the grouping kernels' workgroups each take a fixed share of the rows
-    // (of the slots: 2 rows + 16 P)
+    // the grouping kernels take fixed shares of the rows and of the slots
     const int64_t P = v.pe - v.pb;
-    const unsigned Gr = (unsigned)std::max<int64_t>(1, (rows + kAggRows - 1) / kAggRows);
-    const unsigned Gs = (unsigned)std::max<int64_t>(1, (2 * rows + 16 * P + kAllocSlots - 1) /
-                                                           kAllocSlots);
+    const int64_t rshares = std::max<int64_t>(1, (rows + kAggRows - 1) / kAggRows);
+    const int64_t sshares =
+        std::max<int64_t>(1, (2 * rows + 16 * P + kAllocSlots - 1) / kAllocSlots);
+    const unsigned Gr = (unsigned)std::min<int64_t>(rshares, device_fill_blocks());
+    const unsigned Gs = (unsigned)std::min<int64_t>(sshares, device_fill_blocks());
+    const int shift = sample_shift(rows);
     trace_begin("tbl_init", s);
     hipLaunchKernelGGL(tbl_init, dim3(G), dim3(kBlock), 0, s, v);
     trace_end("tbl_init", s);
-    const int shift = sample_shift(rows);
     trace_begin("tbl_insert", s);
     if (shift >= 0)
         hipLaunchKernelGGL((tbl_insert<K>), dim3(kSampleBlocks), dim3(kBlock), 0, s, in, v, shift,
@@ -1309,23 +1307,22 @@ hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *stat
     trace_end("tbl_insert", s);
     hipLaunchKernelGGL(grp_reset, dim3(G), dim3(kBlock), 0, s, v);
     trace_begin("grp_count", s);
-    hipLaunchKernelGGL((grp_count<K>), dim3(Gr), dim3(kBlock), 0, s, in, v);
+    hipLaunchKernelGGL((grp_count<K>), dim3(Gr), dim3(kBlock), 0, s, in, v, rshares);
     trace_end("grp_count", s);
     trace_begin("grp_alloc", s);
-    hipLaunchKernelGGL(grp_alloc, dim3(Gs), dim3(kBlock), 0, s, v);
+    hipLaunchKernelGGL(grp_alloc, dim3(Gs), dim3(kBlock), 0, s, v, sshares);
     trace_end("grp_alloc", s);
     trace_begin("grp_scatter", s);
-    hipLaunchKernelGGL((grp_scatter<K>), dim3(Gr), dim3(kBlock), 0, s, in, v);
+    hipLaunchKernelGGL((grp_scatter<K>), dim3(Gr), dim3(kBlock), 0, s, in, v, rshares);
     trace_end("grp_scatter", s);
     return hipGetLastError();
 }
 
 template <typename K>
 hipError_t run_probe_group(const Cols &in, const TView &v, int group,
-                           const ProbeWs &w, const ProbeOut &o, int32_t *status, int max_blocks,
+                           const ProbeWs &w, const ProbeOut &o, int32_t *status, int G,
                            hipStream_t s)
 {
-    const int G = table_grid(max_blocks);
     trace_begin("probe_chain", s);
     hipLaunchKernelGGL((probe_chain<K>), dim3(G), dim3(kBlock), 0, s, in, v, group, w, o,
                        status);
@@ -1334,7 +1331,7 @@ hipError_t run_probe_group(const Cols &in, const TView &v, int group,
     // probe row: it always gets a full device (it returns at once when no
     // tile deferred rows).
     trace_begin("probe_expand", s);
-    hipLaunchKernelGGL((probe_expand<K>), dim3(table_grid(0)), dim3(kBlock), 0, s, in, v, group,
+    hipLaunchKernelGGL((probe_expand<K>), dim3(device_fill_blocks()), dim3(kBlock), 0, s, in, v, group,
                        w, o);
     trace_end("probe_expand", s);
     return hipGetLastError();
@@ -1349,7 +1346,7 @@ hipError_t run_count(const K *lk, const int64_t *lofs, int64_t n_build, const K 
     hipLaunchKernelGGL(cnt_setup, dim3(1), dim3(kBlock), 0, s, lofs, n_build, rofs, n_probe,
                        (int64_t *)v.off, off_probe, pcount, P);
     trace_begin("tbl_init", s);
-    hipLaunchKernelGGL(tbl_init, dim3(table_grid(0)), dim3(kBlock), 0, s, v);
+    hipLaunchKernelGGL(tbl_init, dim3(device_fill_blocks()), dim3(kBlock), 0, s, v);
     trace_end("tbl_init", s);
     if (n_build > 0) {
         trace_begin("cnt_insert", s);
@@ -1392,11 +1389,11 @@ hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab
 }
 
 hipError_t launch_build(const Cols &table, int key_bytes, const TView &v, int64_t rows,
-                        int32_t *status, int max_blocks, hipStream_t s)
+                        int32_t *status, hipStream_t s)
 {
     if (key_bytes == 8)
-        return run_build<int64_t>(table, v, rows, status, max_blocks, s);
-    return run_build<int32_t>(table, v, rows, status, max_blocks, s);
+        return run_build<int64_t>(table, v, rows, status, device_fill_blocks(), s);
+    return run_build<int32_t>(table, v, rows, status, device_fill_blocks(), s);
 }
 
 template <typename K>
@@ -1405,31 +1402,13 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
 {
     // workgroups of 2048 rows (16384 left most of the device idle at 4E6
     // rows: 725 against 567 us), at most a full device
-    const int full = table_grid(0);
+    const int full = device_fill_blocks();
     auto blocks = [&](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, full); };
     const int shift = sample_shift(g.n_build);
-    if (!one) {
-        hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, g);
-        hipError_t e = run_build<K>(build, g.v, g.n_build, g.status, blocks(g.n_build), s);
-        if (e != hipSuccess)
-            return e;
-        return run_probe_group<K>(probe, g.v, 0, g.w, g.o, g.status, blocks(g.n_probe), s);
-    }
     const int64_t slots = 2 * g.n_build + 16 * (int64_t)g.w_P;
-    JoinSteps t;
-    t.sync = sync;
-    t.shares_rows = std::max<int64_t>(1, (g.n_build + kAggRows - 1) / kAggRows);
-    t.shares_slots = std::max<int64_t>(1, (slots + kAllocSlots - 1) / kAllocSlots);
-    // The ticket and the count of done items are one address each, so more
-    // workgroups make every step's end longer (1E6 rows: 634 us with 512 of
-    // them, 442 with 256, 591 with 64).
-    const int64_t G = std::min<int64_t>(256, blocks(g.n_build));
-    auto most = [&](int64_t items) { return std::min<int64_t>(items, G); };
-    // (the expansion's work is the output rows, which can be many for few
-    // probe rows)
     PartTable<K> pt = {};
     if (pp.off) {
-        const PartLayout L = part_layout(pp.n, pp.d.ndest, (int)sizeof(K), kProbePartRows);
+        const PartLayout L = part_layout(pp.n, pp.d.ndest, kProbePartRows);
         pt.keys = (const K *)pp.keys;
         pt.pay = pp.pay;
         pt.n = pp.n;
@@ -1439,20 +1418,49 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
         pt.cnt = (int64_t *)((char *)pp.ws + L.cnt_off);
         pt.totals = (int64_t *)((char *)pp.ws + L.totals_off);
     }
-    const int64_t ptiles = std::min<int64_t>(pt.ntiles, 256);
-    const int64_t n[kJoinSteps] = {ptiles, pp.off ? (pp.d.ndest + kWavesPerBlock - 1) / kWavesPerBlock : 0,
-                                   pp.off ? 1 : 0, ptiles,
-                                   1, G, shift >= 0 ? kSampleBlocks : 0, most(blocks(g.n_build)), G,
-                                   most(t.shares_rows), most(t.shares_slots), most(t.shares_rows),
-                                   most(blocks(g.n_probe)), 256, 1};
-    t.first[0] = 0;
-    for (int i = 0; i < kJoinSteps; ++i)
-        t.first[i + 1] = t.first[i] + (uint32_t)n[i];
-    hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
-                       shift, pt, pp.d, t);
-    return hipGetLastError();
+    JoinSteps t;
+    t.shares_rows = std::max<int64_t>(1, (g.n_build + kAggRows - 1) / kAggRows);
+    t.shares_slots = std::max<int64_t>(1, (slots + kAllocSlots - 1) / kAllocSlots);
+    // All steps in one launch on at most `most` workgroups.  The ticket and
+    // the count of done items are one address each, so more workgroups make
+    // every step's end longer (1E6 rows: 506 us with 512 of them, 406 with
+    // 256, 445 with 128).
+    auto run = [&](int64_t most) {
+        auto cap = [&](int64_t items) { return std::min<int64_t>(items, most); };
+        const int64_t again = pp.off ? 1 : 0;
+        // (the expansion's work is the output rows, which can be many for few
+        // probe rows)
+        const int64_t n[kJoinSteps] = {cap(pt.ntiles),
+                                       again * ((pp.d.ndest + kWavesPerBlock - 1) / kWavesPerBlock),
+                                       again,
+                                       cap(pt.ntiles),
+                                       1,
+                                       cap(blocks(slots)),
+                                       shift >= 0 ? kSampleBlocks : 0,
+                                       cap(blocks(g.n_build)),
+                                       cap(blocks(slots)),
+                                       cap(t.shares_rows),
+                                       cap(t.shares_slots),
+                                       cap(t.shares_rows),
+                                       cap(blocks(g.n_probe)),
+                                       most};
+        t.sync = sync;
+        t.first[0] = 0;
+        for (int i = 0; i < kJoinSteps; ++i)
+            t.first[i + 1] = t.first[i] + (uint32_t)n[i];
+        const int64_t G = cap(std::max(blocks(g.n_build), blocks(g.n_probe)));
+        hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
+                           shift, pt, pp.d, t);
+        return hipGetLastError();
+    };
+    if (one)
+        return run(256);
+    hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, g);
+    hipError_t e = run_build<K>(build, g.v, g.n_build, g.status, blocks(g.n_build), s);
+    if (e != hipSuccess)
+        return e;
+    return run_probe_group<K>(probe, g.v, 0, g.w, g.o, g.status, blocks(g.n_probe), s);
 }
-
 
 hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_bytes,
                               const GlobalJoin &g, const ProbePart &pp, bool one, uint32_t *sync,
@@ -1465,28 +1473,21 @@ hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_byte
 }
 
 hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const ProbeWs &w,
-                             const int32_t *skip, hipStream_t s)
+                             int64_t *offsets, hipStream_t s)
 {
     const int G = device_fill_blocks() / 4 > 0 ? device_fill_blocks() / 4 : 1;
-    hipLaunchKernelGGL(probe_plan, dim3(G), dim3(kBlock), 0, s, offR, n, P, w, skip);
+    hipLaunchKernelGGL(probe_plan, dim3(G), dim3(kBlock), 0, s, offR, n, P, w, offsets);
     return hipGetLastError();
 }
 
 hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
                               const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
-                              int32_t *status, int max_blocks, hipStream_t s)
+                              int32_t *status, hipStream_t s)
 {
     (void)P;
     if (key_bytes == 8)
-        return run_probe_group<int64_t>(table, v, group, w, o, status, max_blocks, s);
-    return run_probe_group<int32_t>(table, v, group, w, o, status, max_blocks, s);
-}
-
-hipError_t launch_probe_finalize(int32_t P, const ProbeWs &w, const ProbeOut &o,
-                                 const int32_t *skip, hipStream_t s)
-{
-    hipLaunchKernelGGL(probe_finalize, dim3(1), dim3(kBlock), 0, s, P, w, o, skip);
-    return hipGetLastError();
+        return run_probe_group<int64_t>(table, v, group, w, o, status, device_fill_blocks(), s);
+    return run_probe_group<int32_t>(table, v, group, w, o, status, device_fill_blocks(), s);
 }
 
 }  // namespace mdx

@@ -407,7 +407,7 @@ int32_t mdx_join_build(const void *d_keys, const int64_t *d_payload, const int64
     if (e != hipSuccess)
         return hip_fail(e, W);
     e = launch_build(cols_of(d_keys, d_payload, key_type), key_type,
-                     make_view(t, t.d_offsets, 0, P), n, d_status, 0, stream);
+                     make_view(t, t.d_offsets, 0, P), n, d_status, stream);
     if (e != hipSuccess)
         return hip_fail(e, W);
     *h_table = t;
@@ -483,12 +483,10 @@ int32_t mdx_join_probe(const mdx_table *h_table, const void *d_keys, const int64
     o.rpay = d_out_rpay;
     o.cap = out_capacity;
     o.offsets = d_out_offsets;
-    hipError_t e = launch_probe_plan(d_offsets, n, P, w, nullptr, stream);
+    hipError_t e = launch_probe_plan(d_offsets, n, P, w, d_out_offsets, stream);
     if (e == hipSuccess)
         e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt, P,
-                               make_view(t, t.d_offsets, 0, P), 0, w, o, d_status, 0, stream);
-    if (e == hipSuccess)
-        e = launch_probe_finalize(P, w, o, nullptr, stream);
+                               make_view(t, t.d_offsets, 0, P), 0, w, o, d_status, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
 
@@ -670,8 +668,9 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     M.plan = merge_plan(nL, nR, P);
     M.nA = (int64_t)P << M.plan.q1bits;
     M.S = (int64_t)P << M.plan.qbits;
-    M.pl = part_layout(nL, (int32_t)M.nA, kt);
-    M.pr = part_layout(nR, (int32_t)M.nA, kt);
+    const int R = part_rows_per_thread(nL + nR, (int32_t)M.nA, kt);
+    M.pl = part_layout(nL, (int32_t)M.nA, R);
+    M.pr = part_layout(nR, (int32_t)M.nA, R);
     M.sl = seg_layout(nL, M.nA, M.plan.q2bits);
     M.sr = seg_layout(nR, M.nA, M.plan.q2bits);
     M.jl = rjoin_layout(P, M.plan.qbits, nR);
@@ -702,7 +701,7 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     M.again = !chunked && M.plan.qpbits != M.plan.q1bits;
     const int32_t nP = P << M.plan.qpbits;
     take(M.r2_off, two || M.again ? rows_bytes((int64_t)kR, kt) : 0);
-    take(M.partP_off, M.again ? part_layout(nR, nP, kt, kProbePartRows).bytes : 0);
+    take(M.partP_off, M.again ? part_layout(nR, nP, kProbePartRows).bytes : 0);
     take(M.offP_off, M.again ? (size_t)(nP + 1) * 8 : 0);
     take(M.subL_off, two ? (size_t)(M.S + 1) * 8 : 0);
     take(M.subR_off, two ? (size_t)(M.S + 1) * 8 : 0);
@@ -821,7 +820,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     // when the whole build side fits it: then they are not launched.
     if (chunked || n_left <= kJoinCap) {
         if (e == hipSuccess)
-            e = launch_merge_finalize(pl.qbits, jw, nullptr, o, stream);
+            e = launch_merge_finalize(pl.qbits, jw, o, stream);
         return e;
     }
     int64_t *offPL = (int64_t *)(b + M.offPL_off), *offPR = (int64_t *)(b + M.offPR_off);
@@ -852,7 +851,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
                                cols_of_rows(probe, n_right, key_type), key_type, g, pp, one,
                                jw.join_sync, stream);
     if (e == hipSuccess)
-        e = launch_merge_finalize(pl.qbits, jw, one ? nullptr : &w, o, stream);
+        e = launch_merge_finalize(pl.qbits, jw, o, stream);
     return e;
 }
 
@@ -1122,8 +1121,8 @@ FusedMerge fused_merge(const mdx_merge_desc &d, int32_t idx, const Tuned &t)
     F.R = t.rows == 2 ? kPartRowsLarge
                       : (t.rows == 8 ? (F.nA <= kPartSmallMaxP ? kPartRowsSmall : kPartRowsLarge)
                                      : deflt);
-    F.pl = part_layout(d.n_left, (int32_t)F.nA, F.kt, F.R);
-    F.pr = part_layout(d.n_right, (int32_t)F.nA, F.kt, F.R);
+    F.pl = part_layout(d.n_left, (int32_t)F.nA, F.R);
+    F.pr = part_layout(d.n_right, (int32_t)F.nA, F.R);
     const bool two = F.plan.q2bits > 0;
     if (two) {
         F.sl = seg_layout(d.n_left, F.nA, F.plan.q2bits);
@@ -1547,7 +1546,7 @@ struct ProbeJobLayout {
 ProbeJobLayout probe_job_layout(int64_t n, int32_t P, int32_t kt)
 {
     ProbeJobLayout L;
-    L.pl = part_layout(n, P, kt);
+    L.pl = part_layout_alone(n, P, kt);
     L.ql = probe_layout(n, P);
     const size_t k = (size_t)(n > 0 ? n : 1);
     size_t o = 0;
@@ -1761,12 +1760,10 @@ int32_t mdx_server_submit_probe(mdx_server *srv, const mdx_table *h_table,
     if (e == hipSuccess)
         e = launch_partition(&pa, 1, kt, P, 0, false, 0, 0, st);
     if (e == hipSuccess)
-        e = launch_probe_plan(poff, d.n, P, w, nullptr, st);
+        e = launch_probe_plan(poff, d.n, P, w, o.offsets, st);
     if (e == hipSuccess)
         e = launch_probe_group(cols_of(pk, pv, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w,
-                               o, d.d_status, 0, st);
-    if (e == hipSuccess)
-        e = launch_probe_finalize(P, w, o, nullptr, st);
+                               o, d.d_status, st);
     if (e == hipSuccess)
         e = hipEventRecord(srv->done[(size_t)sl], st);
     if (e != hipSuccess)

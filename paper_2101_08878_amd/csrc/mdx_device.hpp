@@ -65,6 +65,16 @@ struct Rows<int64_t> {
             v[j] = x[1];
         }
     }
+    // The same in two parts: what holds the keys, then what is left.
+    template <int N, typename Index>
+    __device__ __forceinline__ void load_keys(Index index, int64_t *k, int64_t *v) const
+    {
+        load<N>(index, k, v);
+    }
+    template <int N, typename Index>
+    __device__ __forceinline__ void load_rest(Index, int64_t *) const
+    {
+    }
     // Likewise for the j with ok(j); zeros for the others.
     template <int N, typename Index, typename Ok>
     __device__ __forceinline__ void load_if(Index index, Ok ok, int64_t *k, int64_t *v) const
@@ -94,9 +104,19 @@ struct Rows<int32_t> {
     template <int N, typename Index>
     __device__ __forceinline__ void load(Index index, int32_t *k, int64_t *v) const
     {
+        load_keys<N>(index, k, v);
+        load_rest<N>(index, v);
+    }
+    template <int N, typename Index>
+    __device__ __forceinline__ void load_keys(Index index, int32_t *k, int64_t *) const
+    {
 #pragma unroll
         for (int j = 0; j < N; ++j)
             k[j] = __builtin_nontemporal_load(kp + index(j));
+    }
+    template <int N, typename Index>
+    __device__ __forceinline__ void load_rest(Index index, int64_t *v) const
+    {
 #pragma unroll
         for (int j = 0; j < N; ++j)
             v[j] = __builtin_nontemporal_load(vp + index(j));

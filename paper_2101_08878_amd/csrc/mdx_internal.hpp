@@ -104,10 +104,15 @@ __host__ __device__ constexpr ScatterLds scatter_lds(int T, int P, int key_bytes
     return L;
 }
 
-inline int part_rows_per_thread(int32_t ndest, int key_bytes)
+// Few rows take smaller tiles too, so that there are two workgroups for
+// every CU (1E5 x 1E5, P = 4: 50 tiles of 4096 rows leave most CUs idle).
+constexpr int64_t kFillTiles = 512;
+
+inline int part_rows_per_thread(int64_t rows, int32_t ndest, int key_bytes)
 {
     for (int R : {8, 4})
-        if (scatter_lds(kBlock * R, ndest, key_bytes, false).total <= kMaxLdsBytes / 2)
+        if (rows >= kFillTiles * kBlock * R &&
+            scatter_lds(kBlock * R, ndest, key_bytes, false).total <= kMaxLdsBytes / 2)
             return R;
     return 2;
 }
@@ -118,11 +123,11 @@ struct PartLayout {
     size_t cnt_off, totals_off, bytes;
 };
 
-// Tiles of R rows per thread (0: part_rows_per_thread).
-inline PartLayout part_layout(int64_t n, int32_t ndest, int key_bytes, int R = 0)
+// Tiles of R rows per thread.
+inline PartLayout part_layout(int64_t n, int32_t ndest, int R)
 {
     PartLayout L;
-    L.rows_per_thread = R > 0 ? R : part_rows_per_thread(ndest, key_bytes);
+    L.rows_per_thread = R;
     const int64_t tile = (int64_t)kBlock * L.rows_per_thread;
     L.ntiles = (n + tile - 1) / tile;
     size_t o = 0;
@@ -134,17 +139,26 @@ inline PartLayout part_layout(int64_t n, int32_t ndest, int key_bytes, int R = 0
     return L;
 }
 
-// What a partition asks of its caller: the layout with 1024-row tiles beyond
-// 256 destinations (at least what the tiles taken need), so that the sizes
-// mdx_hash_partition_noalloc accepts do not depend on the tiling.
+// The layout of one table partitioned alone.
+inline PartLayout part_layout_alone(int64_t n, int32_t ndest, int key_bytes)
+{
+    return part_layout(n, ndest, part_rows_per_thread(n, ndest, key_bytes));
+}
+
+// What a partition asks of its caller: at least the layout with 4096-row
+// tiles to 256 destinations and 1024-row ones beyond, so that the sizes
+// mdx_hash_partition_noalloc accepts do not depend on the tiles taken (which
+// need more only for few rows).
 inline size_t part_workspace_bytes(int64_t n, int32_t P, int key_bytes)
 {
-    return part_layout(n, P, key_bytes, P <= 256 ? 8 : 2).bytes;
+    const size_t a = part_layout(n, P, P <= 256 ? 8 : 2).bytes;
+    const size_t b = part_layout_alone(n, P, key_bytes).bytes;
+    return a > b ? a : b;
 }
 
 // One table of a partition launch: stable partition into
 // make_dest(P, sbits).ndest destinations; off has ndest + 1 entries; ws holds
-// part_layout(n, ndest, key bytes).bytes.  The output is two columns, or with `rows_out`
+// part_layout(n, ndest, R).bytes, R = part_rows_per_thread of all the tables' rows.  The output is two columns, or with `rows_out`
 // Rows<K> at keys_out (pay_out is null).  With dig (n bytes, rows
 // only), every output row's digit_of(h, dshift, dbits) is written beside it,
 // for the histogram of a following segmented pass.
@@ -323,7 +337,12 @@ struct RJoinLayout {
     size_t status_off, cursor_off, istart_off, isub_off, plan_off, misc_off, bytes;
 };
 
-constexpr int64_t kPlanChunk = 4096;  // sub-buckets planned per workgroup
+// Counters of the global-table join's one launch, each on a cache line of its
+// own.
+constexpr int kSyncStride = 32;
+constexpr int kJoinSync = 3;
+
+constexpr int64_t kPlanChunk = 1024;  // sub-buckets planned per workgroup of rj_plan
 
 inline RJoinLayout rjoin_layout(int32_t P, int qbits, int64_t n_probe)
 {
@@ -341,8 +360,8 @@ inline RJoinLayout rjoin_layout(int32_t P, int qbits, int64_t n_probe)
     o += align_up((size_t)L.max_items * sizeof(uint32_t));
     L.plan_off = o;
     o += align_up((size_t)((L.S + kPlanChunk - 1) / kPlanChunk) * sizeof(uint64_t));
-    L.misc_off = o;  // ticket, plan ticket, then the plan's results
-    o += align_up(256);
+    L.misc_off = o;  // ticket, plan ticket, the plan's results; then join_sync
+    o += align_up(256 + kJoinSync * kSyncStride * sizeof(uint32_t));
     L.bytes = o;
     return L;
 }
@@ -355,7 +374,7 @@ struct RJoinWs {
     uint64_t *plan;         // chained scan of the planning workgroups
     uint32_t *ticket;
     uint32_t *plan_ticket;
-    uint32_t *join_sync;    // [2] of the global-table join
+    uint32_t *join_sync;    // kJoinSync counters of the global-table join
     // the plan's results: the number of items, and 1 if every build
     // sub-bucket fits an LDS table, else 0 (together, for one load)
     uint32_t *plan_out;
@@ -374,7 +393,7 @@ inline RJoinWs rjoin_ws(void *base, const RJoinLayout &L, int32_t P)
     w.plan = (uint64_t *)(b + L.plan_off);
     w.ticket = (uint32_t *)(b + L.misc_off);
     w.plan_ticket = w.ticket + 1;
-    w.join_sync = w.ticket + 16;
+    w.join_sync = w.ticket + 64;
     w.plan_out = w.ticket + 32;  // not on the tickets' cache line
     w.S = L.S;
     w.max_items = L.max_items;
@@ -429,7 +448,7 @@ struct TView {
 
 // ---- probe ------------------------------------------------------------------
 constexpr int kProbeRows = 8;                       // rows per thread
-constexpr int kProbeTile = kBlock * kProbeRows;     // 2048 rows per tile
+constexpr int kProbeTile = kBlock * kProbeRows;     // 4096 rows per tile
 
 struct Deferred {
     int64_t rbeg, rend;  // probe rows of the tile
@@ -439,7 +458,7 @@ struct Deferred {
 
 struct ProbeLayout {
     int64_t max_tiles;
-    size_t off_off, tile_start_off, status_off, tile_base_off, ticket_off, ndefer_off, defer_off,
+    size_t off_off, tile_start_off, status_off, ticket_off, ndefer_off, defer_off,
         row_pre_off, row_gs_off, bytes;
 };
 
@@ -454,8 +473,6 @@ inline ProbeLayout probe_layout(int64_t n, int32_t P)
     o += align_up((size_t)(P + 1) * sizeof(int64_t));
     L.status_off = o;
     o += align_up((size_t)L.max_tiles * sizeof(uint64_t));
-    L.tile_base_off = o;
-    o += align_up((size_t)L.max_tiles * sizeof(int64_t));
     L.ticket_off = o;
     o += align_up((size_t)P * sizeof(uint32_t));
     L.ndefer_off = o;
@@ -474,7 +491,6 @@ struct ProbeWs {
     int64_t *off;  // [P+1] sanitized probe offsets
     int64_t *tile_start;
     uint64_t *status;
-    int64_t *tile_base;
     uint32_t *ticket;
     uint32_t *ndefer;
     Deferred *defer;
@@ -490,7 +506,6 @@ inline ProbeWs probe_ws(void *base, const ProbeLayout &L)
     w.off = (int64_t *)(b + L.off_off);
     w.tile_start = (int64_t *)(b + L.tile_start_off);
     w.status = (uint64_t *)(b + L.status_off);
-    w.tile_base = (int64_t *)(b + L.tile_base_off);
     w.ticket = (uint32_t *)(b + L.ticket_off);
     w.ndefer = (uint32_t *)(b + L.ndefer_off);
     w.defer = (Deferred *)(b + L.defer_off);
@@ -529,10 +544,8 @@ inline Cols cols_of_rows(const void *rows, int64_t n, int key_bytes)
 }
 
 // Build a view of `rows` rows: init slots, insert rows, group repeated keys.
-// The grid-stride kernels of build and probe run on a full device, or on
-// max_blocks workgroups when 0 < max_blocks < that.
 hipError_t launch_build(const Cols &table, int key_bytes, const TView &v,
-                        int64_t rows, int32_t *status, int max_blocks, hipStream_t s);
+                        int64_t rows, int32_t *status, hipStream_t s);
 
 // Copy the build offsets (sanitized, for n build rows) into the table and
 // clear per-partition flags.  off_in may be null (flags only).
@@ -543,8 +556,8 @@ hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab
 // offsets from the first pass's (offPL[p] = offAL[p stride], offPR[p] =
 // offAR[p strideR]),
 // the table built from `build`, probed with `probe`, the output and its
-// offsets (those by merge_finalize when it takes several launches).  one: in
-// one launch.  sync: two zeroed counters.
+// offsets.  one: in one launch.  sync: kJoinSync zeroed counters, kSyncStride
+// apart.
 constexpr int64_t kOneLaunchRows = (int64_t)1 << 21;
 
 struct GlobalJoin {
@@ -561,7 +574,7 @@ struct GlobalJoin {
 // The probe table's partition as a two-pass merge's first pass makes it, for
 // a merge split in one pass: the global-table join's output rows follow this
 // order whatever the split.  pay null: not needed, `probe` has it already.
-// ws: part_layout(n, d.ndest, key_bytes, kProbePartRows).bytes.
+// ws: part_layout(n, d.ndest, kProbePartRows).bytes.
 constexpr int kProbePartRows = 4;
 constexpr int kProbePartMax = 256;  // destinations
 
@@ -579,15 +592,14 @@ hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_byte
                               const GlobalJoin &g, const ProbePart &pp, bool one,
                               uint32_t *sync, hipStream_t s);
 
-// Probe: plan tiles from the probe offsets (sanitized for n probe rows, once
-// per probe), probe one view (group g), finalize the output offsets.
+// Probe: plan tiles from the probe offsets (sanitized for n probe rows; zero
+// output offsets when there are none), then probe and write the output and
+// its offsets.
 hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const ProbeWs &w,
-                             const int32_t *skip, hipStream_t s);
+                             int64_t *offsets, hipStream_t s);
 hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
                               const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
-                              int32_t *status, int max_blocks, hipStream_t s);
-hipError_t launch_probe_finalize(int32_t P, const ProbeWs &w, const ProbeOut &o,
-                                 const int32_t *skip, hipStream_t s);
+                              int32_t *status, hipStream_t s);
 
 // Count-only join of two partitioned tables (full views, pb = 0, pe = P):
 // per-partition output counts into out_offsets (exclusive prefix, total at
@@ -645,11 +657,9 @@ bool rjoin_by_partition(int qbits, int64_t G);
 hipError_t launch_rjoin_batch(const JoinRec *recs, int M, const uint32_t *Spre, uint32_t S,
                               uint32_t *ticket, int key_bytes, bool by_part, hipStream_t s);
 
-// A merge's output offsets where the radix join did not write them itself:
-// its partition cursors', or (pw non-null) the global-table probe's when that
-// ran.  Nothing is launched when neither can be.
-hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeWs *pw,
-                                 const ProbeOut &o, hipStream_t s);
+// A merge's output offsets from the partition cursors, if the radix join ran
+// and placed its rows by partition (otherwise nothing is launched).
+hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeOut &o, hipStream_t s);
 
 
 // ---- transpose sum (y = x + x^T, float64) -------------------------------------------

@@ -406,7 +406,7 @@ PartPair<K> part_pair(const PartArgs *tables, int ntables, int D, int R)
     PartPair<K> T = {};
     for (int i = 0; i < ntables; ++i) {
         const PartArgs &a = tables[i];
-        const PartLayout L = part_layout(a.n, D, (int)sizeof(K), R);
+        const PartLayout L = part_layout(a.n, D, R);
         PartTable<K> &t = T.t[i];
         t.keys = (const K *)a.keys;
         t.pay = a.pay;
@@ -741,7 +741,10 @@ hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, 
 {
     if (ntables < 1 || ntables > 2)
         return hipErrorInvalidValue;
-    const int R = part_rows_per_thread(P << sbits, key_bytes);
+    int64_t rows = 0;
+    for (int i = 0; i < ntables; ++i)
+        rows += tables[i].n;
+    const int R = part_rows_per_thread(rows, P << sbits, key_bytes);
     auto run = [&](auto f) { return f(tables, ntables, P, sbits, rows_out, dshift, dbits, s); };
     if (key_bytes == 8)
         return R == 8   ? run(run_partition<int64_t, 8>)

@@ -167,20 +167,24 @@ __device__ __forceinline__ uint32_t items_of(int64_t nb, int64_t nr)
     return nb > 0 && nr > kJoinBatch ? (uint32_t)((nr + kJoinBatch - 1) / kJoinBatch) : 1u;
 }
 
-constexpr int kPlanPerThread = 8;
-static_assert(kPlanChunk == (int64_t)kBlock * kPlanPerThread, "a thread plans 8 sub-buckets");
+// Sub-buckets per thread of a planning workgroup: rj_plan_one's does up to
+// kPlanOneMax alone, rj_plan's kPlanChunk each.
+constexpr int kPlanOnePer = 8, kPlanPer = 2;
+constexpr int64_t kPlanOneMax = (int64_t)kBlock * kPlanOnePer;
+static_assert(kPlanChunk == (int64_t)kBlock * kPlanPer, "chunks of rj_plan");
 
-// Block: sub-buckets [s0, s0 + m), m <= kPlanChunk: exclusive prefix of their
+// Block: sub-buckets [s0, s0 + m), m <= kBlock PER: exclusive prefix of their
 // items into pre[0..m] (LDS); over: some build side exceeds a table.  Returns
 // the items.  The items are counted with consecutive lanes on consecutive
 // sub-buckets; the prefix is formed only when some sub-bucket has several.
-__device__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t s0, int m,
+template <int PER>
+__device__ __forceinline__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t s0, int m,
                                uint32_t *pre, int64_t *scratch, bool &over)
 {
     const int tid = threadIdx.x;
-    int64_t nb[kPlanPerThread], nr[kPlanPerThread];
+    int64_t nb[PER], nr[PER];
 #pragma unroll
-    for (int k = 0; k < kPlanPerThread; ++k) {
+    for (int k = 0; k < PER; ++k) {
         // indices past the end are clamped: no load behind a branch
         const int i = k * kBlock + tid;
         const int64_t c = s0 + (i < m ? i : m - 1);
@@ -189,7 +193,7 @@ __device__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t
     }
     int big = 0, over_ = 0;
 #pragma unroll
-    for (int k = 0; k < kPlanPerThread; ++k) {
+    for (int k = 0; k < PER; ++k) {
         const int i = k * kBlock + tid;
         const uint32_t ni = items_of(nb[k], nr[k]);
         big |= ni > 1;
@@ -204,18 +208,18 @@ __device__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t
         __syncthreads();
         return m;
     }
-    uint32_t ni[kPlanPerThread], sum = 0;
+    uint32_t ni[PER], sum = 0;
 #pragma unroll
-    for (int k = 0; k < kPlanPerThread; ++k) {
-        const int i = tid * kPlanPerThread + k;
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid * PER + k;
         ni[k] = i < m ? pre[i] : 0u;
         sum += ni[k];
     }
     int64_t total;  // (the scan's barriers: every item count has been read)
     uint32_t run = (uint32_t)block_excl_scan((int64_t)sum, scratch, &total);
 #pragma unroll
-    for (int k = 0; k < kPlanPerThread; ++k) {
-        const int i = tid * kPlanPerThread + k;
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid * PER + k;
         if (i < m)
             pre[i] = run;
         run += ni[k];
@@ -277,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void rj_plan(const int64_t *__restrict__ su
         return;  // a workgroup that only clears
     const int m = (int)(w.S - s0 < kPlanChunk ? w.S - s0 : kPlanChunk);
     bool over;
-    const int64_t total = plan_prefix(subL, subR, s0, m, pre, scratch, over);
+    const int64_t total = plan_prefix<kPlanPer>(subL, subR, s0, m, pre, scratch, over);
     if (over && !chunked)
         w.plan_out[1] = 0;  // rj_plan_init set it to 1 before this kernel
     if (threadIdx.x < kWave) {
@@ -297,11 +301,12 @@ __global__ __launch_bounds__(kBlock) void rj_plan_init(RJoinWs w, int chunks)
 {
     for (int i = threadIdx.x; i < chunks; i += kBlock)
         w.plan[i] = 0;
+    if (threadIdx.x < kJoinSync)
+        w.join_sync[threadIdx.x * kSyncStride] = 0;
     if (threadIdx.x == 0) {
         w.plan_out[1] = 1;
         *w.ticket = 0;
         *w.plan_ticket = 0;
-        w.join_sync[0] = w.join_sync[1] = 0;
     }
 }
 
@@ -311,15 +316,16 @@ __global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict_
                                                       const int64_t *__restrict__ subR, RJoinWs w,
                                                       int chunked)
 {
-    __shared__ uint32_t pre[kPlanChunk + 1];
+    __shared__ uint32_t pre[kPlanOneMax + 1];
     __shared__ int64_t scratch[kWavesPerBlock];
     const int m = (int)w.S;
     bool over;
-    const int64_t total = plan_prefix(subL, subR, 0, m, pre, scratch, over);
+    const int64_t total = plan_prefix<kPlanOnePer>(subL, subR, 0, m, pre, scratch, over);
+    if (threadIdx.x < kJoinSync)
+        w.join_sync[threadIdx.x * kSyncStride] = 0;
     if (threadIdx.x == 0) {
         w.plan_out[1] = over && !chunked ? 0 : 1;
         *w.ticket = 0;
-        w.join_sync[0] = w.join_sync[1] = 0;
         w.plan_out[0] = (uint32_t)total;
         w.istart[m] = (uint32_t)total;
     }
@@ -534,7 +540,9 @@ struct JoinLds {
 // complete in the order they were issued, and waiting for one waits for all
 // issued before it; so they are issued in the order they are needed, with
 // no branch around any of them (so that the compiler counts them exactly):
-// the build rows (the inserts wait for these alone), then the probe rows.
+// the build rows (the inserts wait for these alone), the probe rows' keys
+// (the match), then, once the table is built, payloads that do not come with
+// their keys (needed only to write the output).
 template <class G, typename K>
 __device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
                                                 int64_t nb, Rows<K> rrows,
@@ -552,7 +560,7 @@ __device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
         };
     };
     lrows.from(bL).template load<kBuildBatch>(clamped(blast), bk, bv);
-    rrows.from(bR).template load<kJoinRows>(clamped(plast), kk, vv);
+    rrows.from(bR).template load_keys<kJoinRows>(clamped(plast), kk, vv);
     for (int i = tid; i < G::heads; i += kJoinThreads)
         L.head[i] = Tab<G>::sent;
     __syncthreads();
@@ -567,6 +575,7 @@ __device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
         }
     }
     __syncthreads();
+    rrows.from(bR).template load_rest<kJoinRows>(clamped(plast), vv);
     match_batch<G>(bR, eR, L.tkey, L.tn, L.head, kk, mf);
     cell_sums(mf, L.cw, lane, wv);
 }
@@ -806,24 +815,11 @@ __global__ __launch_bounds__(kBlock) void rj_finalize_batch(const JoinRec *__res
         offsets_from_cursors(r.jcursor, r.P, r.o.offsets);
 }
 
-// Output offsets of a merge that rj_join did not write: from the partition
-// cursors, or from the global-table probe's chained scan (probe tiles,
-// partition-major) when that ran (use flag 0).
-__global__ __launch_bounds__(kBlock) void merge_finalize(int by_part, RJoinWs w, ProbeWs pw,
-                                                         bool fallback, ProbeOut o)
+// Output offsets of a merge placed by partition, if the radix join ran.
+__global__ __launch_bounds__(kBlock) void merge_finalize(RJoinWs w, ProbeOut o)
 {
-    const int P = w.P;
-    if (w.plan_out[1] != 0) {
-        if (by_part)
-            offsets_from_cursors(w.cursor, P, o.offsets);
-    } else if (fallback) {
-        const int64_t TT = pw.tile_start[P];
-        const int64_t total = TT > 0 ? (int64_t)(ld_agent(pw.status + TT - 1) & kValMask) : 0;
-        for (int p = threadIdx.x; p <= P; p += kBlock) {
-            const int64_t t = pw.tile_start[p];
-            o.offsets[p] = t < TT ? pw.tile_base[t] : total;
-        }
-    }
+    if (w.plan_out[1] != 0)
+        offsets_from_cursors(w.cursor, w.P, o.offsets);
 }
 
 }  // namespace
@@ -845,7 +841,7 @@ bool rjoin_by_partition(int qbits, int64_t G)
 hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S,
                              const RJoinWs &w, bool chunked, int32_t *status, hipStream_t s)
 {
-    if (S <= kPlanChunk) {
+    if (S <= kPlanOneMax) {
         hipLaunchKernelGGL(rj_plan_one, dim3(1), dim3(kBlock), 0, s, subL, subR, w, (int)chunked);
         return hipGetLastError();
     }
@@ -904,15 +900,11 @@ hipError_t launch_rjoin_batch(const JoinRec *recs, int M, const uint32_t *Spre, 
     return hipGetLastError();
 }
 
-hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeWs *pw,
-                                 const ProbeOut &o, hipStream_t s)
+hipError_t launch_merge_finalize(int qbits, const RJoinWs &w, const ProbeOut &o, hipStream_t s)
 {
-    const ProbeWs none = {};
-    const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
-    if (!by_part && !pw)
+    if (!rjoin_by_partition(qbits, rjoin_grid(w.S)))
         return hipSuccess;
-    hipLaunchKernelGGL(merge_finalize, dim3(1), dim3(kBlock), 0, s, by_part, w, pw ? *pw : none,
-                       pw != nullptr, o);
+    hipLaunchKernelGGL(merge_finalize, dim3(1), dim3(kBlock), 0, s, w, o);
     return hipGetLastError();
 }
 
