@@ -690,7 +690,6 @@ __device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, co
                                                int32_t *status)
 {
     constexpr int RP = kProbeRows;
-    constexpr int kProbeWalk = 4;  // rows of a thread walking together
     constexpr int kCells = RP * kWavesPerBlock;  // (row step, wave)
     static_assert(kCells <= kWave, "one wave scans the cells");
     static_assert(sizeof(lds.cw) == kCells * 8, "one sum per cell");
@@ -730,23 +729,19 @@ __device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, co
         int64_t slot[RP];
         uint64_t val[RP];
         bool bad = false;
+        uint64_t h[RP];
+        uint32_t open = 0;
 #pragma unroll
-        for (int c = 0; c < RP; c += kProbeWalk) {
-            uint64_t h[kProbeWalk];
-            uint32_t open = 0;
-#pragma unroll
-            for (int i = 0; i < kProbeWalk; ++i) {
-                const int64_t r = rbeg + (int64_t)(c + i) * kBlock + tid;
-                h[i] = fmix64(key_bits(kk[c + i]));
-                const bool here = (int)part_of(h[i], v.d) == p;
-                if (r < rend && here)
-                    open |= 1u << i;
-                bad |= r < rend && !here;
-            }
-            find_slots<kProbeWalk>(
-                v.slots, [=](int) { return sb; }, [=](int) { return H; }, h, open, slot + c,
-                val + c);
+        for (int c = 0; c < RP; ++c) {
+            const int64_t r = rbeg + (int64_t)c * kBlock + tid;
+            h[c] = fmix64(key_bits(kk[c]));
+            const bool here = (int)part_of(h[c], v.d) == p;
+            if (r < rend && here)
+                open |= 1u << c;
+            bad |= r < rend && !here;
         }
+        find_slots<RP>(
+            v.slots, [=](int) { return sb; }, [=](int) { return H; }, h, open, slot, val);
         if (bad)
             or_status(status, MDX_DEV_BAD_PARTITIONING);
 
