@@ -3,21 +3,20 @@
 // chunked cuPy array to its transpose).
 //
 // HBM-bound: every element of x is read once and every element of y written
-// once.  The matrix is cut into 32 x 32 tiles; a workgroup takes one tile
-// pair (I, J) with I <= J, stages tiles x[I, J] and x[J, I] in LDS (rows
-// padded by one element, so that reading a column touches consecutive
-// banks), then writes y[I, J] = x[I, J] + x[J, I]^T and y[J, I] = x[J, I] +
-// x[I, J]^T.  Both tiles are read before either is written, so y may be x.
-// Each element is one IEEE-754 addition, the same on any device.
+// once.  The matrix is cut into square tiles; a workgroup takes one tile pair
+// (I, J) with I <= J and writes y[I, J] = x[I, J] + x[J, I]^T and y[J, I] =
+// x[J, I] + x[I, J]^T.  Tiles are transposed through LDS (rows padded by one
+// element, so that reading a column touches consecutive banks).  Each element
+// is one IEEE-754 addition, the same on any device.
 #include "mdx.h"
 #include "mdx_internal.hpp"
 
 namespace mdx {
 namespace {
 
-// 32 x 32 tiles, 256 threads: 17 KB of LDS per workgroup, so many
-// workgroups share a CU and keep loads in flight (4.9 TB/s at 16K x 16K,
-// against 2.6 TB/s for 64 x 64 tiles at two workgroups per CU).
+// Small, odd and unaligned matrices: 32 x 32 tiles, 256 threads, both tiles of
+// the pair in LDS before either is written (so y may be x).  17 KB of LDS, so
+// many workgroups share a CU and keep loads in flight.
 constexpr int kTT = 32;                    // tile edge
 constexpr int kTThreads = 256;
 constexpr int kTRows = kTThreads / kTT;    // rows a workgroup moves per step
@@ -71,12 +70,98 @@ __global__ __launch_bounds__(kTThreads) void transpose_sum_tiles(const double *x
     }
 }
 
+// Large matrices: 128 x 128 tiles, 1024 threads, so that a tile's row is 1 KB
+// of the matrix in one piece (32 x 32 tiles: 256 bytes, which the memory
+// serves at 4.9 TB/s; 64 x 64: 5.2; 128 x 128: 5.4; float64, 16384 x 16384: 863,
+// 826 and 793 us).  A thread holds its elements of both tiles in registers;
+// one tile at a time passes through the 132 KB of LDS.  An element of y is
+// written by the thread that read it from x, so y may be x.  Stores stream past
+// the caches; loads do when the matrix is well beyond the 256 MB Infinity
+// Cache (5120 x 5120: 64 us, with streaming loads 81; 16384 x 16384: 806 and
+// 793).
+constexpr int kBT = 128;
+constexpr int kBThreads = 1024;
+constexpr int kBCols = kBT / 2;             // threads per row, two elements each
+constexpr int kBRows = kBThreads / kBCols;  // rows a workgroup moves per step
+constexpr int kBSteps = kBT / kBRows;
+constexpr int64_t kBigPairs = 768;                 // three workgroups for every CU
+constexpr int64_t kStreamBytes = (int64_t)384 << 20;
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+template <bool STREAM>
+__global__ __launch_bounds__(kBThreads) void transpose_sum_big(const double *x, double *y, int64_t n,
+                                                               int64_t T)
+{
+    __shared__ double t[kBT][kBT + 1];
+    int64_t I, J;
+    pair_of(blockIdx.x, T, I, J);
+    const int c = (threadIdx.x % kBCols) * 2, r0 = threadIdx.x / kBCols;
+    const int64_t i0 = I * kBT, j0 = J * kBT;
+    // rows r0 + k kBRows, columns c and c + 1 of the tile at (row, col); n is
+    // even, so the two columns lie in the matrix or both outside
+    auto load = [&](int64_t row, int64_t col, f64x2 *v) {
+#pragma unroll
+        for (int k = 0; k < kBSteps; ++k) {
+            const int64_t r = row + r0 + k * kBRows;
+            v[k] = f64x2(0);
+            if (r < n && col + c < n) {
+                const f64x2 *p = (const f64x2 *)(x + r * n + col + c);
+                v[k] = STREAM ? __builtin_nontemporal_load(p) : *p;
+            }
+        }
+    };
+    auto stage = [&](const f64x2 *v) {
+#pragma unroll
+        for (int k = 0; k < kBSteps; ++k) {
+            t[r0 + k * kBRows][c] = v[k][0];
+            t[r0 + k * kBRows][c + 1] = v[k][1];
+        }
+    };
+    auto store = [&](int64_t row, int64_t col, const f64x2 *v) {  // v + the staged tile^T
+#pragma unroll
+        for (int k = 0; k < kBSteps; ++k) {
+            const int64_t r = row + r0 + k * kBRows;
+            if (r < n && col + c < n) {
+                f64x2 o;
+                o[0] = v[k][0] + t[c][r0 + k * kBRows];
+                o[1] = v[k][1] + t[c + 1][r0 + k * kBRows];
+                __builtin_nontemporal_store(o, (f64x2 *)(y + r * n + col + c));
+            }
+        }
+    };
+    f64x2 a[kBSteps], b[kBSteps];
+    load(i0, j0, a);
+    if (I == J) {
+        stage(a);
+        __syncthreads();
+        store(i0, j0, a);
+        return;
+    }
+    load(j0, i0, b);
+    stage(b);
+    __syncthreads();
+    store(i0, j0, a);
+    __syncthreads();
+    stage(a);
+    __syncthreads();
+    store(j0, i0, b);
+}
+
 }  // namespace
 
 hipError_t launch_transpose_sum(const double *x, double *y, int64_t n, hipStream_t s)
 {
     if (n == 0)
         return hipSuccess;
+    const int64_t B = (n + kBT - 1) / kBT, big = B * (B + 1) / 2;
+    if (big >= kBigPairs && n % 2 == 0 && ((uintptr_t)x | (uintptr_t)y) % 16 == 0) {
+        const auto fn = 8 * n * n > kStreamBytes ? transpose_sum_big<true> : transpose_sum_big<false>;
+        trace_begin("transpose_sum", s);
+        hipLaunchKernelGGL(fn, dim3((unsigned)big), dim3(kBThreads), 0, s, x, y, n, B);
+        trace_end("transpose_sum", s);
+        return hipGetLastError();
+    }
     const int64_t T = (n + kTT - 1) / kTT;
     const int64_t pairs = T * (T + 1) / 2;
     trace_begin("transpose_sum", s);

@@ -61,3 +61,24 @@ def test_transpose_sum_benchmark_size():
     y = mdx.mdx_transpose_sum(dev(x))
     torch.cuda.synchronize()
     assert _same_bits(host(y), oracle.transpose_sum(x))
+
+
+@pytest.mark.parametrize("n", [4864, 4994, 5000, 5120, 7094, 7096])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_transpose_sum_large_tiles(n, shift):
+    """Around the sizes from which 128 x 128 tiles are used (38 tiles a side do
+    not, 39 do) and loads stream (n > 7094), whole and partial tiles; with
+    the matrices 8 bytes past a 16-byte boundary the small tiles run.  In
+    place and not, against x + x.T bit for bit."""
+    announce(f"transpose sum n={n} shift={shift}")
+    import paper_2101_08878_amd as mdx
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    buf = torch.rand(n * n + 1, generator=g, device="cuda", dtype=torch.float64)
+    x = buf[shift:shift + n * n].view(n, n)
+    want = x + x.t()
+    out = torch.empty(n * n + 1, device="cuda", dtype=torch.float64)[shift:shift + n * n].view(n, n)
+    mdx.mdx_transpose_sum(x, out=out)
+    assert torch.equal(out, want)
+    mdx.mdx_transpose_sum(x, out=x)
+    assert torch.equal(x, want)
