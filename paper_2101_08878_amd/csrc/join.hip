@@ -1046,20 +1046,56 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
 // rows are first counted per workgroup in an LDS map of hashes, so a key
 // repeated millions of times costs one global update per workgroup; rows
 // the map cannot take go to the table one by one.
-constexpr int kCountRows = 8;  // rows per thread loaded together
-#ifndef MDX_COUNT_MAP_BITS
-#define MDX_COUNT_MAP_BITS 12
-#endif
-#ifndef MDX_COUNT_WG_ROWS
-#define MDX_COUNT_WG_ROWS 16384
-#endif
-// On 5E7 x 5E7 Zipf(1.1) keys (P = 16) the count took 2.07 ms with 2048
-// entries, 1.98 with 4096 and 2.83 with 8192 (96 KB of LDS: fewer
-// workgroups per CU); 8192 or 32768 rows per workgroup instead of 16384
-// were slower.
-constexpr int kCountMapBits = MDX_COUNT_MAP_BITS;
+//
+// A workgroup's share of the rows: kCountWgRows, halved for smaller sides
+// until kCountFill workgroups run.  5E7 x 5E7 Zipf(1.1) keys (P = 16): the
+// table's updates, one per distinct hash and share, go at the rate of the
+// device's atomics on random lines, which more aggregation lowers (a share
+// holds 22% distinct hashes, one four times as large 16%) and fewer waves in
+// flight do not reach: 40 KB of LDS and 512 threads keep a CU's 32 waves,
+// 2.75 ms a count with its partitions; 32-bit counts (24 waves) 2.81; 256
+// threads 3.20, 1024 2.90; 8192 entries for 32768 rows 3.48, 2048 for 8192
+// 2.99.  Four entries' slots walked at once by each thread were slower (3.03).
+// 2E5 x 1E5 keys: 197 us with shares of 16384 rows (13 workgroups), 72 with
+// 1024; 3E6 x 2E6 int32: 309 and 189.
+constexpr int kCountBlock = 512;
+constexpr int kCountRows = 4;  // rows per thread loaded together
+constexpr int kCountMapBits = 12;
 constexpr int kCountMap = 1 << kCountMapBits;  // LDS map entries
-constexpr int kCountWgRows = MDX_COUNT_WG_ROWS;  // rows per workgroup
+constexpr int kCountWgRows = 16384;            // a share; its counts fit 16 bits
+constexpr int kCountMinRows = 1024;
+constexpr int kCountFill = 384;
+
+// The LDS map of a workgroup: hashes and their rows in the share (two
+// 16-bit counts per word).
+struct CountMap {
+    uint64_t key[kCountMap];
+    uint32_t cnt[kCountMap / 2];
+    __device__ __forceinline__ void clear()
+    {
+        for (int i = threadIdx.x; i < kCountMap; i += kCountBlock) {
+            key[i] = ~0ull;
+            if (i < kCountMap / 2)
+                cnt[i] = 0;
+        }
+    }
+    __device__ __forceinline__ void add(int e)
+    {
+        atomicAdd(&cnt[e >> 1], 1u << 16 * (e & 1));
+    }
+    // fn(hash, rows) for every entry.  Each workgroup starts elsewhere, so
+    // that those of one partition do not come to a hot hash's slot together.
+    template <typename Fn>
+    __device__ __forceinline__ void each(Fn fn) const
+    {
+        const int turn = (int)((blockIdx.x * 0x9E3779B1u) >> (32 - kCountMapBits));
+        for (int i = threadIdx.x; i < kCountMap; i += kCountBlock) {
+            const int e = i ^ turn;
+            if (key[e] != ~0ull)
+                fn(key[e], cnt[e >> 1] >> 16 * (e & 1) & 0xffffu);
+        }
+    }
+};
 
 // Entry of hash h in the LDS map (inserted if there is room within
 // kAggProbe probes), or -1.  ~0 marks an empty entry, so a row whose hash is
@@ -1116,8 +1152,7 @@ __device__ __forceinline__ void slot_add(const TView &v, int64_t o0, int p, uint
     }
 }
 
-// Rows [r0, r1) of the workgroup's share (kCountWgRows rows each), kCountRows per
-// thread loaded together; fn(row, hash, partition) for every row in its
+// Rows [r0, r1) of the workgroup's share, kCountRows per thread loaded together; fn(row, hash, partition) for every row in its
 // partition, the others reported.
 template <typename K, typename Fn>
 __device__ __forceinline__ void count_rows(const K *__restrict__ keys, const int64_t *off, int P,
@@ -1125,16 +1160,16 @@ __device__ __forceinline__ void count_rows(const K *__restrict__ keys, const int
                                            Fn fn)
 {
     bool bad = false;
-    for (int64_t b = r0; b < r1; b += (int64_t)kCountRows * kBlock) {
+    for (int64_t b = r0; b < r1; b += (int64_t)kCountRows * kCountBlock) {
         K k[kCountRows];
 #pragma unroll
         for (int j = 0; j < kCountRows; ++j) {
-            const int64_t r = b + (int64_t)j * kBlock + threadIdx.x;
+            const int64_t r = b + (int64_t)j * kCountBlock + threadIdx.x;
             k[j] = r < r1 ? __builtin_nontemporal_load(keys + r) : K(0);
         }
 #pragma unroll
         for (int j = 0; j < kCountRows; ++j) {
-            const int64_t r = b + (int64_t)j * kBlock + threadIdx.x;
+            const int64_t r = b + (int64_t)j * kCountBlock + threadIdx.x;
             if (r < r1) {
                 const uint64_t h = fmix64(key_bits(k[j]));
                 const int p = upper_index(off, 0, P, r);
@@ -1165,30 +1200,24 @@ __global__ __launch_bounds__(kBlock) void cnt_setup(const int64_t *__restrict__ 
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void cnt_insert(const K *__restrict__ keys, TView v,
+__global__ __launch_bounds__(kCountBlock) void cnt_insert(const K *__restrict__ keys, TView v, int share,
                                                      int32_t *status)
 {
-    __shared__ uint64_t mkey[kCountMap];
-    __shared__ uint32_t mcnt[kCountMap];
-    for (int i = threadIdx.x; i < kCountMap; i += kBlock) {
-        mkey[i] = ~0ull;
-        mcnt[i] = 0;
-    }
+    __shared__ CountMap map;
+    map.clear();
     __syncthreads();
     const int64_t o0 = v.off[0], o1 = v.off[v.pe];
-    const int64_t r0 = o0 + (int64_t)blockIdx.x * kCountWgRows;
-    const int64_t r1 = r0 + kCountWgRows < o1 ? r0 + kCountWgRows : o1;
+    const int64_t r0 = o0 + (int64_t)blockIdx.x * share;
+    const int64_t r1 = r0 + share < o1 ? r0 + share : o1;
     count_rows(keys, v.off, v.pe, v.d, r0, r1, status, [&](uint64_t h, int p) {
-        const int e = hmap_insert(mkey, h);
+        const int e = hmap_insert(map.key, h);
         if (e >= 0)
-            atomicAdd(&mcnt[e], 1u);
+            map.add(e);
         else
             slot_add(v, o0, p, h, 1);
     });
     __syncthreads();
-    for (int i = threadIdx.x; i < kCountMap; i += kBlock)
-        if (mkey[i] != ~0ull)
-            slot_add(v, o0, (int)part_of(mkey[i], v.d), mkey[i], mcnt[i]);
+    map.each([&](uint64_t h, uint64_t c) { slot_add(v, o0, (int)part_of(h, v.d), h, c); });
 }
 
 // Build rows of hash h in partition p (0 when absent).
@@ -1201,29 +1230,26 @@ __device__ __forceinline__ uint64_t slot_count(const TView &v, int64_t o0, int p
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void cnt_probe(const K *__restrict__ keys,
+__global__ __launch_bounds__(kCountBlock) void cnt_probe(const K *__restrict__ keys,
                                                     const int64_t *__restrict__ off_probe,
-                                                    TView v, uint64_t *pcount, int32_t *status)
+                                                    TView v, uint64_t *pcount, int share,
+                                                    int32_t *status)
 {
     extern __shared__ unsigned long long psum[];  // [P]
-    __shared__ uint64_t mkey[kCountMap];
-    __shared__ uint32_t mcnt[kCountMap];
+    __shared__ CountMap map;
     const int P = v.pe;
-    for (int i = threadIdx.x; i < kCountMap; i += kBlock) {
-        mkey[i] = ~0ull;
-        mcnt[i] = 0;
-    }
-    for (int p = threadIdx.x; p < P; p += kBlock)
+    map.clear();
+    for (int p = threadIdx.x; p < P; p += kCountBlock)
         psum[p] = 0;
     __syncthreads();
     const int64_t o0 = v.off[0];
     const int64_t n = off_probe[P];
-    const int64_t r0 = off_probe[0] + (int64_t)blockIdx.x * kCountWgRows;
-    const int64_t r1 = r0 + kCountWgRows < n ? r0 + kCountWgRows : n;
+    const int64_t r0 = off_probe[0] + (int64_t)blockIdx.x * share;
+    const int64_t r1 = r0 + share < n ? r0 + share : n;
     count_rows(keys, off_probe, P, v.d, r0, r1, status, [&](uint64_t h, int p) {
-        const int e = hmap_insert(mkey, h);
+        const int e = hmap_insert(map.key, h);
         if (e >= 0) {
-            atomicAdd(&mcnt[e], 1u);
+            map.add(e);
         } else {
             const uint64_t c = slot_count(v, o0, p, h);
             if (c)
@@ -1231,17 +1257,14 @@ __global__ __launch_bounds__(kBlock) void cnt_probe(const K *__restrict__ keys,
         }
     });
     __syncthreads();
-    for (int i = threadIdx.x; i < kCountMap; i += kBlock) {
-        const uint64_t h = mkey[i];
-        if (h != ~0ull) {
-            const int p = (int)part_of(h, v.d);
-            const uint64_t c = slot_count(v, o0, p, h);
-            if (c)
-                atomicAdd(&psum[p], (unsigned long long)(c * mcnt[i]));
-        }
-    }
+    map.each([&](uint64_t h, uint64_t rows) {
+        const int p = (int)part_of(h, v.d);
+        const uint64_t c = slot_count(v, o0, p, h);
+        if (c)
+            atomicAdd(&psum[p], (unsigned long long)(c * rows));
+    });
     __syncthreads();
-    for (int p = threadIdx.x; p < P; p += kBlock)
+    for (int p = threadIdx.x; p < P; p += kCountBlock)
         if (psum[p])
             atomicAdd((unsigned long long *)&pcount[p], psum[p]);
 }
@@ -1276,6 +1299,15 @@ static int sample_shift(int64_t rows)
     while (rows >> shift > kSampleRows)
         ++shift;
     return rows <= 4 * kSampleRows ? -1 : shift;
+}
+
+// Rows per workgroup of a count's kernel over `rows` rows.
+static int count_share(int64_t rows)
+{
+    int share = kCountWgRows;
+    while (share > kCountMinRows && rows < (int64_t)share * kCountFill)
+        share /= 2;
+    return share;
 }
 
 // G: workgroups of the grid-stride kernels.
@@ -1338,6 +1370,7 @@ hipError_t run_count(const K *lk, const int64_t *lofs, int64_t n_build, const K 
                      uint64_t *pcount, int64_t *out_offsets, int32_t *status, hipStream_t s)
 {
     const int P = v.pe;
+    const int bs = count_share(n_build), ps = count_share(n_probe);
     hipLaunchKernelGGL(cnt_setup, dim3(1), dim3(kBlock), 0, s, lofs, n_build, rofs, n_probe,
                        (int64_t *)v.off, off_probe, pcount, P);
     trace_begin("tbl_init", s);
@@ -1346,15 +1379,16 @@ hipError_t run_count(const K *lk, const int64_t *lofs, int64_t n_build, const K 
     if (n_build > 0) {
         trace_begin("cnt_insert", s);
         hipLaunchKernelGGL((cnt_insert<K>),
-                           dim3((unsigned)((n_build + kCountWgRows - 1) / kCountWgRows)),
-                           dim3(kBlock), 0, s, lk, v, status);
+                           dim3((unsigned)((n_build + bs - 1) / bs)),
+                           dim3(kCountBlock), 0, s, lk, v, bs, status);
         trace_end("cnt_insert", s);
     }
     if (n_probe > 0) {
         trace_begin("cnt_probe", s);
         hipLaunchKernelGGL((cnt_probe<K>),
-                           dim3((unsigned)((n_probe + kCountWgRows - 1) / kCountWgRows)),
-                           dim3(kBlock), (size_t)P * 8, s, rk, off_probe, v, pcount, status);
+                           dim3((unsigned)((n_probe + ps - 1) / ps)),
+                           dim3(kCountBlock), (size_t)P * 8, s, rk, off_probe, v, pcount, ps,
+                           status);
         trace_end("cnt_probe", s);
     }
     hipLaunchKernelGGL(cnt_finalize, dim3(1), dim3(kBlock), 0, s, pcount, P, out_offsets);

@@ -185,6 +185,24 @@ def test_join_count_many_partitions_and_large_counts():
     assert np.array_equal(np.diff(off), ref["per_part"]) and off[-1] == 9 * 10**10 + 500
 
 
+@pytest.mark.parametrize("n", [1023, 1025, 384 * 1024, 384 * 1024 + 1, 384 * 8192 - 1, 384 * 8192 + 3])
+@pytest.mark.parametrize("keys", ["distinct", "hot"])
+def test_join_count_shares(n, keys):
+    """Sides around the sizes where a workgroup's share of the rows doubles (1024
+    rows up to 16384): distinct keys, which overflow the LDS map, and one key
+    on half the rows, whose counts fill a share."""
+    announce(f"join count shares n={n} {keys}")
+    rng = np.random.default_rng(n)
+    kl = rng.permutation(n).astype(np.int64) - n // 2
+    kr = rng.integers(-n, n, n // 2 + 1).astype(np.int64)
+    if keys == "hot":
+        kl[: n // 2] = 11
+        kr[::3] = 11
+    v = np.zeros(n, np.int64)
+    ref = oracle.join(kl, v, kr, v[:kr.size], P=5, materialize=False)
+    assert np.array_equal(np.diff(_count(kl, kr, 5)), ref["per_part"])
+
+
 def test_join_count_bad_partitioning_is_reported():
     """Unpartitioned rows with offsets that claim a partitioning: flagged,
     skipped, nothing faults."""
