@@ -164,15 +164,26 @@ __device__ __forceinline__ int64_t pay_at(const Cols &c, int64_t r)
 struct Dest {
     uint64_t P;
     uint64_t mask;  // P - 1 when P is a power of two
+    uint64_t inv;   // floor(2^64 / P) when it is not
     int32_t pow2;
     int32_t sbits;  // sub-bucket bits taken from the top of h
     int32_t ndest;  // P << sbits
     int32_t nbits;  // bits needed to write ndest - 1 (0 for ndest = 1)
 };
 
+// h mod P.  Other P than powers of two: with inv = (2^64 - e) / P, 0 < e < P,
+// the quotient h inv / 2^64 is less than one below h / P, so its
+// floor is that of h / P or one less, and the remainder, in [0, 2 P), is exact
+// after one subtraction.  The general 64-bit remainder is some hundred
+// instructions a row, which set the partition's pace: 3E7 int32 rows, P = 7,
+// took 264 us with it, 193 so (P = 8: 194).
 __device__ __forceinline__ uint32_t part_of(uint64_t h, const Dest &d)
 {
-    return d.pow2 ? (uint32_t)(h & d.mask) : (uint32_t)(h % d.P);
+    if (d.pow2)
+        return (uint32_t)(h & d.mask);
+    const uint32_t P = (uint32_t)d.P;
+    const uint32_t r = (uint32_t)h - (uint32_t)__umul64hi(h, d.inv) * P;
+    return r >= P ? r - P : r;
 }
 
 __device__ __forceinline__ uint32_t dest_of(uint64_t h, const Dest &d)

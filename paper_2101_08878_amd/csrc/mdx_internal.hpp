@@ -54,6 +54,7 @@ inline Dest make_dest(int32_t P, int sbits = 0)
     d.P = (uint64_t)P;
     d.pow2 = (P & (P - 1)) == 0;
     d.mask = d.pow2 ? (uint64_t)(P - 1) : 0;
+    d.inv = d.pow2 ? 0 : ~0ull / (uint64_t)P;
     d.sbits = sbits;
     d.ndest = P << sbits;
     d.nbits = ceil_log2(d.ndest);

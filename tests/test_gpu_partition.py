@@ -149,3 +149,20 @@ def test_partition_tile_sizes(P, dtype):
     keys = np.random.default_rng(P).integers(info.min, info.max, N_RAGGED, dtype=np.int64,
                                              endpoint=True).astype(dtype)
     _assert_same(keys, np.arange(N_RAGGED, dtype=np.int64), P)
+
+
+@pytest.mark.parametrize("P", [3, 5, 6, 7, 57, 257, 300, 1023, 3072, 4093, 4095])
+def test_partition_hashes_at_multiples(P):
+    """The remainder by a P that is no power of two, at hashes where its
+    quotient can be off by one: multiples of P and their neighbours, at both
+    ends and spread over the 64 bits (keys made by running fmix64 backwards)."""
+    announce(f"partition hashes at multiples P={P}")
+    top = 2**64 // P
+    at = list(range(400)) + list(range(top - 400, top + 1)) + [top * i // 400 for i in range(400)]
+    h = np.array([q * P + e for q in at for e in (-1, 0, 1) if 0 <= q * P + e < 2**64], np.uint64)
+    k = h ^ h >> np.uint64(33)
+    for c in (0xC4CEB9FE1A85EC53, 0xFF51AFD7ED558CCD):
+        k = k * np.uint64(pow(c, -1, 2**64))
+        k ^= k >> np.uint64(33)
+    assert all(oracle.fmix64(int(x)) == int(y) for x, y in zip(k[::97], h[::97]))
+    _assert_same(k.view(np.int64), np.arange(k.size, dtype=np.int64), P)
