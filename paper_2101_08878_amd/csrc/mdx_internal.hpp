@@ -63,9 +63,14 @@ inline Dest make_dest(int32_t P, int sbits = 0)
 
 // ---- partition ------------------------------------------------------------
 // Rows per tile of the partition kernels: kBlock threads x R rows, R = 8, 4 or
-// 2: the largest whose tile is staged in half a CU's LDS, so that two
-// workgroups share a CU (else 2).  A tile's rows and its destinations' counts
-// share that LDS, so many destinations take smaller tiles.
+// 2.  A tile's rows and its destinations' counts are staged in LDS: the
+// largest of 8 and 4 that fits half a CU's, so that two workgroups share a CU
+// (6E7 int64 rows, 1024 destinations: 4 rows 1.11 ms, 8 alone on a CU 1.18).
+// Where neither does (from 1607 destinations, int32 from 1900), the largest
+// that fits the whole: one workgroup per CU then costs less than the
+// table of counts, 8 bytes per tile and destination, which smaller tiles write
+// and scan (6E7 int64 rows: 2048 destinations, 2 rows 3.03 ms, 8 rows 1.66; 4096,
+// 2 rows 7.6 ms, 4 rows 4.13; int32 alike).
 constexpr int kPartRowsSmall = 8;      // fused batches, D <= kPartSmallMaxP
 constexpr int kPartRowsLarge = 2;      // fused batches beyond
 constexpr int kPartSmallMaxP = 256;
@@ -114,6 +119,11 @@ inline int part_rows_per_thread(int64_t rows, int32_t ndest, int key_bytes)
     for (int R : {8, 4})
         if (rows >= kFillTiles * kBlock * R &&
             scatter_lds(kBlock * R, ndest, key_bytes, false).total <= kMaxLdsBytes / 2)
+            return R;
+    for (int R : {8, 4})
+        if (rows >= kFillTiles / 2 * kBlock * R &&
+            scatter_lds(kBlock * 4, ndest, key_bytes, false).total > kMaxLdsBytes / 2 &&
+            scatter_lds(kBlock * R, ndest, key_bytes, true).total <= kMaxLdsBytes)
             return R;
     return 2;
 }

@@ -166,3 +166,16 @@ def test_partition_hashes_at_multiples(P):
         k ^= k >> np.uint64(33)
     assert all(oracle.fmix64(int(x)) == int(y) for x, y in zip(k[::97], h[::97]))
     _assert_same(k.view(np.int64), np.arange(k.size, dtype=np.int64), P)
+
+
+@pytest.mark.parametrize("P", [1024, 1606, 1607, 1900, 3230, 3400, 4095, 4096])
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+@pytest.mark.parametrize("n", [256 * 512 * 4 - 1, 256 * 512 * 4, 256 * 512 * 8 + 5])
+def test_partition_tiles_of_many_destinations(P, dtype, n):
+    """Tiles of 2, 4 and 8 rows per thread that take a CU's LDS alone: the
+    sizes from which they do, on both sides of the limits of destinations."""
+    announce(f"partition many destinations P={P} dtype={np.dtype(dtype).name} n={n}")
+    info = np.iinfo(dtype)
+    keys = np.random.default_rng(P).integers(info.min, info.max, n, dtype=np.int64,
+                                             endpoint=True).astype(dtype)
+    _assert_same(keys, np.arange(n, dtype=np.int64), P)
