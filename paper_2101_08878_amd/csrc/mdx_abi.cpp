@@ -651,7 +651,6 @@ struct MergeLayout {
     MergePlan plan;
     bool again;     // the global-table join partitions the probe table again
     int64_t nA, S;  // first-pass destinations, sub-buckets
-    PartLayout pl, pr;
     SegLayout sl, sr;
     RJoinLayout jl;
     TableLayout tl;
@@ -668,9 +667,6 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     M.plan = merge_plan(nL, nR, P);
     M.nA = (int64_t)P << M.plan.q1bits;
     M.S = (int64_t)P << M.plan.qbits;
-    const int R = part_rows_per_thread(nL + nR, (int32_t)M.nA, kt);
-    M.pl = part_layout(nL, (int32_t)M.nA, R);
-    M.pr = part_layout(nR, (int32_t)M.nA, R);
     M.sl = seg_layout(nL, M.nA, M.plan.q2bits);
     M.sr = seg_layout(nR, M.nA, M.plan.q2bits);
     M.jl = rjoin_layout(P, M.plan.qbits, nR);
@@ -683,8 +679,8 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
         field = o;
         o += align_up(bytes);
     };
-    take(M.partL_off, M.pl.bytes);
-    take(M.partR_off, M.pr.bytes);
+    take(M.partL_off, part_reserve_bytes(nL, (int32_t)M.nA, kt));
+    take(M.partR_off, part_reserve_bytes(nR, (int32_t)M.nA, kt));
     take(M.l1_off, rows_bytes((int64_t)kL, kt));
     take(M.r1_off, rows_bytes((int64_t)kR, kt));
     take(M.offAL_off, (size_t)(M.nA + 1) * 8);
@@ -1538,7 +1534,6 @@ size_t probe_request_bytes(const mdx_probe_desc &d, int32_t P, int32_t key_type)
 // A probe job's slot workspace: the probe rows partitioned by the table's P
 // (partition workspace, keys, payloads, offsets), then the probe workspace.
 struct ProbeJobLayout {
-    PartLayout pl;
     ProbeLayout ql;
     size_t part_off, keys_off, pay_off, off_off, probe_off, bytes;
 };
@@ -1546,12 +1541,11 @@ struct ProbeJobLayout {
 ProbeJobLayout probe_job_layout(int64_t n, int32_t P, int32_t kt)
 {
     ProbeJobLayout L;
-    L.pl = part_layout_alone(n, P, kt);
     L.ql = probe_layout(n, P);
     const size_t k = (size_t)(n > 0 ? n : 1);
     size_t o = 0;
     L.part_off = o;
-    o += align_up(L.pl.bytes);
+    o += align_up(part_reserve_bytes(n, P, kt));
     L.keys_off = o;
     o += align_up(k * (size_t)kt);
     L.pay_off = o;

@@ -2,6 +2,7 @@
 // files (partition.hip, join.hip).  Not installed; not part of the ABI.
 #pragma once
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -150,10 +151,19 @@ inline PartLayout part_layout(int64_t n, int32_t ndest, int R)
     return L;
 }
 
-// The layout of one table partitioned alone.
-inline PartLayout part_layout_alone(int64_t n, int32_t ndest, int key_bytes)
+// Bytes for any layout that a table of at most n rows takes, alone or with
+// another: smaller tables take smaller tiles, whose counts can need more, and
+// what is sized for n rows serves fewer too.
+inline size_t part_reserve_bytes(int64_t n, int32_t ndest, int key_bytes)
 {
-    return part_layout(n, ndest, part_rows_per_thread(n, ndest, key_bytes));
+    const int top = part_rows_per_thread((int64_t)1 << 40, ndest, key_bytes);
+    size_t most = 0;
+    for (int R = 2; R <= top; R *= 2) {
+        const int64_t below = kFillTiles * kBlock * 2 * R;  // rows from which larger tiles are taken
+        const int64_t rows = R < top && n > below ? below : n;
+        most = std::max(most, part_layout(rows, ndest, R).bytes);
+    }
+    return most;
 }
 
 // What a partition asks of its caller: at least the layout with 4096-row
@@ -162,9 +172,7 @@ inline PartLayout part_layout_alone(int64_t n, int32_t ndest, int key_bytes)
 // need more only for few rows).
 inline size_t part_workspace_bytes(int64_t n, int32_t P, int key_bytes)
 {
-    const size_t a = part_layout(n, P, P <= 256 ? 8 : 2).bytes;
-    const size_t b = part_layout_alone(n, P, key_bytes).bytes;
-    return a > b ? a : b;
+    return std::max(part_layout(n, P, P <= 256 ? 8 : 2).bytes, part_reserve_bytes(n, P, key_bytes));
 }
 
 // One table of a partition launch: stable partition into

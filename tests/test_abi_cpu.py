@@ -418,3 +418,13 @@ def test_noalloc_partition_rejects_sizes_beyond_its_scratch():
     assert L._part_noalloc(None, v, n, mdx.MDX_KEY_I64, 32, ko, vo, off, None) == mdx.MDX_ERR_INVALID
     assert L._part_noalloc(k, v, n, mdx.MDX_KEY_I64, 0, ko, vo, off, None) == mdx.MDX_ERR_INVALID
     assert L._part_noalloc(k, v, n, mdx.MDX_KEY_I64, 32, k, vo, off, None) == mdx.MDX_ERR_INVALID
+
+
+def test_partition_workspace_monotone_in_rows():
+    """A partition workspace sized at the most rows a program will see serves
+    fewer rows too, though fewer rows take smaller tiles."""
+    for P in (1, 3, 8, 57, 256, 300, 1607, 4096):
+        for kt in (4, 8):
+            sizes = [0, 1, 10**5] + [512 * 512 * 2 * m + e for m in (1, 2, 4, 8) for e in (-1, 0, 1)] + [10**8]
+            ws = [mdx.mdx_hash_partition_workspace_bytes(n, P, kt) for n in sizes]
+            assert ws == sorted(ws), (P, kt)
