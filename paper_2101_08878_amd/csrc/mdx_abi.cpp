@@ -242,14 +242,14 @@ int32_t mdx_hash_partition(const void *d_keys, const int64_t *d_payload, int64_t
     if (int32_t e = check_partition(d_keys, d_payload, n, key_type, P, d_keys_out, d_payload_out,
                                     d_offsets, W))
         return e;
-    const size_t need = part_workspace_bytes(n, P, key_type);
+    const size_t need = part_least_bytes(n, P);
     if (!d_ws || !aligned(d_ws, kAlign))
         return fail(MDX_ERR_INVALID, "mdx_hash_partition: workspace null or not 256-byte aligned");
     if (ws_bytes < need)
         return fail(MDX_ERR_WORKSPACE, "mdx_hash_partition: workspace needs " +
                                            std::to_string(need) + " bytes");
     const PartArgs t = {d_keys, d_payload, n, d_keys_out, d_payload_out, d_offsets, nullptr, d_ws};
-    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream);
+    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream, ws_bytes);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
 
@@ -309,7 +309,7 @@ int32_t mdx_hash_partition_noalloc(const void *d_keys, const int64_t *d_payload,
     if (int32_t e = check_partition(d_keys, d_payload, n, key_type, P, d_keys_out, d_payload_out,
                                     d_offsets, W))
         return e;
-    const size_t need = part_workspace_bytes(n, P, key_type);
+    const size_t need = part_least_bytes(n, P);
     if (need > (size_t)MDX_NOALLOC_SCRATCH_BYTES)
         return fail(MDX_ERR_WORKSPACE,
                     std::string(W) + ": needs " + std::to_string(need) +
@@ -320,7 +320,8 @@ int32_t mdx_hash_partition_noalloc(const void *d_keys, const int64_t *d_payload,
     if (int32_t e = scratch_address(&ws, W))
         return e;
     const PartArgs t = {d_keys, d_payload, n, d_keys_out, d_payload_out, d_offsets, nullptr, ws};
-    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream);
+    hipError_t e = launch_partition(&t, 1, key_type, P, 0, false, 0, 0, stream,
+                                    (size_t)MDX_NOALLOC_SCRATCH_BYTES);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
 

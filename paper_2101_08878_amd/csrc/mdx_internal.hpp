@@ -166,13 +166,23 @@ inline size_t part_reserve_bytes(int64_t n, int32_t ndest, int key_bytes)
     return most;
 }
 
-// What a partition asks of its caller: at least the layout with 4096-row
-// tiles to 256 destinations and 1024-row ones beyond, so that the sizes
-// mdx_hash_partition_noalloc accepts do not depend on the tiles taken (which
-// need more only for few rows).
+// The least a partition's workspace may hold: the counts of 4096-row tiles to
+// 256 destinations and of 1024-row ones beyond.
+inline int part_least_rows(int32_t ndest)
+{
+    return ndest <= 256 ? 8 : 2;
+}
+
+inline size_t part_least_bytes(int64_t n, int32_t P)
+{
+    return part_layout(n, P, part_least_rows(P)).bytes;
+}
+
+// What a partition asks of its caller.  With less, down to part_least_bytes, few
+// rows take the larger tiles that it holds.
 inline size_t part_workspace_bytes(int64_t n, int32_t P, int key_bytes)
 {
-    return std::max(part_layout(n, P, P <= 256 ? 8 : 2).bytes, part_reserve_bytes(n, P, key_bytes));
+    return std::max(part_least_bytes(n, P), part_reserve_bytes(n, P, key_bytes));
 }
 
 // One table of a partition launch: stable partition into
@@ -195,7 +205,8 @@ struct PartArgs {
 // Partition 1 or 2 tables (same key width and destinations) with one set of
 // launches.
 hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, int32_t P,
-                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s);
+                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s,
+                            size_t ws_bytes = SIZE_MAX);
 
 // ---- segmented partition (second split of the join) -------------------------
 // Segment a (rows [segoff[a], segoff[a+1]) of an already partitioned table of

@@ -737,14 +737,17 @@ void write_seg_rec(const SegArgs *tables, int64_t nseg, int shift, int bits, voi
 }  // namespace
 
 hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, int32_t P,
-                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s)
+                            int sbits, bool rows_out, int dshift, int dbits, hipStream_t s,
+                            size_t ws_bytes)
 {
     if (ntables < 1 || ntables > 2)
         return hipErrorInvalidValue;
     int64_t rows = 0;
     for (int i = 0; i < ntables; ++i)
         rows += tables[i].n;
-    const int R = part_rows_per_thread(rows, P << sbits, key_bytes);
+    int R = part_rows_per_thread(rows, P << sbits, key_bytes);
+    if (part_layout(rows, P << sbits, R).bytes > ws_bytes)
+        R = part_least_rows(P << sbits);
     auto run = [&](auto f) { return f(tables, ntables, P, sbits, rows_out, dshift, dbits, s); };
     if (key_bytes == 8)
         return R == 8   ? run(run_partition<int64_t, 8>)

@@ -179,3 +179,26 @@ def test_partition_tiles_of_many_destinations(P, dtype, n):
     keys = np.random.default_rng(P).integers(info.min, info.max, n, dtype=np.int64,
                                              endpoint=True).astype(dtype)
     _assert_same(keys, np.arange(n, dtype=np.int64), P)
+
+
+@pytest.mark.parametrize("P", [1, 8, 200, 256])
+@pytest.mark.parametrize("n", [5000, 300_000, 1_100_000])
+def test_partition_in_the_least_workspace(P, n):
+    """A workspace that holds only 4096-row tiles' counts: few rows then take
+    those tiles; 256 bytes less are refused."""
+    announce(f"partition least workspace P={P} n={n}")
+    import torch
+    import paper_2101_08878_amd as mdx
+    from tests.gpu_util import dev, host
+    keys = np.random.default_rng(n + P).integers(-n, n, n).astype(np.int64)
+    pay = np.arange(n, dtype=np.int64)
+    up = lambda b: -(-b // 256) * 256  # noqa: E731
+    least = up(8 * P * -(-n // 4096)) + up(8 * P)
+    assert least <= mdx.mdx_hash_partition_workspace_bytes(n, P)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    got = mdx.mdx_hash_partition(dev(keys), dev(pay), P, workspace=ws)
+    torch.cuda.synchronize()
+    for g, w in zip(got, oracle.hash_partition(keys, pay, P)):
+        assert np.array_equal(host(g), w)
+    with pytest.raises(Exception, match="workspace"):
+        mdx.mdx_hash_partition(dev(keys), dev(pay), P, workspace=ws[: least - 256])
