@@ -38,7 +38,7 @@ COPY_KERNEL = "__amd_rocclr_copyBuffer"
 KERNEL_FILES = {
     "part_hist": "partition.hip", "part_scatter": "partition.hip", "seg_hist": "partition.hip",
     "seg_scatter": "partition.hip", "rj_join": "rjoin.hip", "transpose_sum": "transpose.hip",
-    "transpose_sum_tiles": "transpose.hip",
+    "transpose_sum_tiles": "transpose.hip", "transpose_sum_big": "transpose.hip",
 }
 SHARED_FILES = ("mdx_device.hpp", "mdx_internal.hpp", "mdx_partition.hpp")
 
