@@ -41,7 +41,6 @@ namespace mdx {
 namespace {
 
 constexpr int kJoinWaves = kJoinThreads / kWave;
-constexpr int kBuildBatch = 8;  // build rows per thread loaded together
 constexpr int kCells = kJoinRows * kJoinWaves;  // (row step, wave) partial sums
 constexpr int kCellsPerLane = kCells / kWave;
 static_assert(kCells % kWave == 0, "one wave scans the partial sums");
@@ -53,9 +52,12 @@ template <class G>
 struct Tab {
     static constexpr uint32_t sent = G::cap;
     static constexpr int log_heads = __builtin_ctz(G::heads);
+    // build rows per thread, loaded together: what a full table takes (a
+    // merge's 3456 rows: 7; with 8, one load and insert more per item, 3E7 x
+    // 3E7 int32 rows took 1209 us, so 1198)
+    static constexpr int build_rows = (G::cap + kJoinThreads - 1) / kJoinThreads;
     static_assert(G::cap <= 0xffff, "chain links are 16-bit");
     static_assert((G::heads & (G::heads - 1)) == 0, "power-of-two heads");
-    static_assert(kBuildBatch * kJoinThreads >= G::cap, "one load batch per table");
     static_assert(kJoinRows % G::walk == 0, "walk groups tile the thread's rows");
 };
 
@@ -487,9 +489,8 @@ __device__ __forceinline__ void emit_batch(const K *kk, const int64_t *vv, const
     }
 }
 
-// Insert build rows [b0, b0 + n) (0 < n <= G::cap) into the LDS table,
-// kBuildBatch rows per thread at a time.  Rows past n load the last row (no
-// branch per load) and are not inserted.
+// Insert build rows [b0, b0 + n) (0 < n <= G::cap) into the LDS table.  Rows
+// past n load the last row (no branch per load) and are not inserted.
 template <class G, typename K>
 __device__ __forceinline__ void build_table(Rows<K> lrows, int64_t b0,
                                             int64_t n, int64_t *tkey, int64_t *tp, uint16_t *tn,
@@ -501,24 +502,23 @@ __device__ __forceinline__ void build_table(Rows<K> lrows, int64_t b0,
     __syncthreads();
     const Rows<K> b = lrows.from(b0);
     const uint32_t last = (uint32_t)n - 1;
-    for (int base = 0; base < (int)n; base += kBuildBatch * kJoinThreads) {
-        K bk[kBuildBatch];
-        int64_t bv[kBuildBatch];
-        b.template load<kBuildBatch>(
-            [&](int j) {
-                const uint32_t i = (uint32_t)(base + j * kJoinThreads) + tid;
-                return i < last ? i : last;
-            },
-            bk, bv);
+    constexpr int kBuild = Tab<G>::build_rows;
+    K bk[kBuild];
+    int64_t bv[kBuild];
+    b.template load<kBuild>(
+        [&](int j) {
+            const uint32_t i = (uint32_t)(j * kJoinThreads) + tid;
+            return i < last ? i : last;
+        },
+        bk, bv);
 #pragma unroll
-        for (int j = 0; j < kBuildBatch; ++j) {
-            const int i = base + j * kJoinThreads + tid;
-            if (i < n) {
-                const int64_t k = (int64_t)bk[j];
-                tkey[i] = k;
-                tp[i] = bv[j];
-                tn[i] = (uint16_t)atomicExch(&head[bucket_of<G>(k)], (uint32_t)i);
-            }
+    for (int j = 0; j < kBuild; ++j) {
+        const int i = j * kJoinThreads + tid;
+        if (i < n) {
+            const int64_t k = (int64_t)bk[j];
+            tkey[i] = k;
+            tp[i] = bv[j];
+            tn[i] = (uint16_t)atomicExch(&head[bucket_of<G>(k)], (uint32_t)i);
         }
     }
     __syncthreads();
@@ -551,21 +551,22 @@ __device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const uint32_t blast = (uint32_t)nb - 1, plast = (uint32_t)(eR - bR) - 1;
-    K bk[kBuildBatch];
-    int64_t bv[kBuildBatch];
+    constexpr int kBuild = Tab<G>::build_rows;
+    K bk[kBuild];
+    int64_t bv[kBuild];
     auto clamped = [tid](uint32_t last) {
         return [tid, last](int j) {
             const uint32_t i = (uint32_t)(j * kJoinThreads + tid);
             return i < last ? i : last;
         };
     };
-    lrows.from(bL).template load<kBuildBatch>(clamped(blast), bk, bv);
+    lrows.from(bL).template load<kBuild>(clamped(blast), bk, bv);
     rrows.from(bR).template load_keys<kJoinRows>(clamped(plast), kk, vv);
     for (int i = tid; i < G::heads; i += kJoinThreads)
         L.head[i] = Tab<G>::sent;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kBuildBatch; ++j) {
+    for (int j = 0; j < kBuild; ++j) {
         const int i = j * kJoinThreads + tid;
         if (i < nb) {
             const int64_t k = (int64_t)bk[j];
@@ -707,27 +708,38 @@ __device__ __forceinline__ int64_t take_ticket(uint32_t *ticket, int64_t *s_next
 template <typename K, bool CHUNKED>
 __global__ __launch_bounds__(kJoinThreads)
 __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_join(
-    Rows<K> lrows, const int64_t *__restrict__ subL,
-    Rows<K> rrows, const int64_t *__restrict__ subR, RJoinWs w, int qbits, int by_part, ProbeOut o, int32_t *status)
+    Rows<K> lrows, const int64_t *__restrict__ subL, Rows<K> rrows,
+    const int64_t *__restrict__ subR, const uint32_t *__restrict__ istart,
+    const uint32_t *__restrict__ isub, RJoinWs w, int qbits, int by_part, ProbeOut o,
+    int32_t *status)
 {
     MDX_JOIN_LDS(MergeJoin)
     // no items when the plan found a build side too large; the first ticket is
     // taken while these loads are under way
     const int64_t n = !CHUNKED && w.plan_out[1] == 0 ? 0 : w.plan_out[0];
     const bool split = n != w.S;  // some sub-bucket is several items
-    const Place pl = {w.cursor, w.status, split ? w.istart : nullptr, n, o.offsets, qbits, by_part};
+    const Place pl = {w.cursor, w.status, split ? istart : nullptr, n, o.offsets, qbits, by_part};
     int cp = -1;
     int64_t cb = 0;
     for (;;) {
         const int64_t t = take_ticket(w.ticket, &s_next);
         if (t >= n)
             break;
-        const int64_t s = split ? w.isub[t] : t;
-        const int64_t bL = subL[s], nb = subL[s + 1] - bL;
-        int64_t bR = subR[s], eR = subR[s + 1];
+        const int64_t s = split ? isub[t] : t;
+        // The item's bounds, loaded together (nothing that uses the first of
+        // them passes the empty asm) and, as the list is only read here,
+        // through the scalar cache.  One after the other, with the list in
+        // vector loads, an item of a list began 0.4 us later: 51663 x 13.9E6
+        // int32 rows with a few sub-buckets of several batches took 411 us,
+        // so 405; 1E8 x 1E8 4054 and 4038.  (Without a list its entry is read
+        // too, inside the workspace, and not used.)
+        int64_t bL = subL[s], eL = subL[s + 1], bR = subR[s], eR = subR[s + 1];
+        uint32_t i0 = istart[s];
+        asm volatile("" : "+s"(bL), "+s"(eL), "+s"(bR), "+s"(eR), "+s"(i0));
+        const int64_t nb = eL - bL;
         bool first = true;
         if (split) {
-            const int64_t c = t - w.istart[s];
+            const int64_t c = t - i0;
             first = c == 0;
             bR += c * kJoinBatch;
             eR = nb > 0 && bR + kJoinBatch < eR ? bR + kJoinBatch : eR;
@@ -861,7 +873,8 @@ void launch_rjoin_kernel(int G, const void *lrows, int64_t nL, const int64_t *su
     const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
     const auto fn = chunked ? rj_join<K, true> : rj_join<K, false>;
     hipLaunchKernelGGL(fn, dim3(G), dim3(kJoinThreads), 0, s, make_rows<K>(lrows, nL), subL,
-                       make_rows<K>(rrows, nR), subR, w, qbits, by_part, o, status);
+                       make_rows<K>(rrows, nR), subR, w.istart, w.isub, w, qbits, by_part, o,
+                       status);
 }
 
 hipError_t launch_rjoin(const void *lrows, int64_t nL, const int64_t *subL, const void *rrows,
