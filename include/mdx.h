@@ -280,6 +280,8 @@ int32_t mdx_join_count(const void *d_lkeys, const int64_t *d_lofs, int64_t n_bui
  * MDX_DEV_OUTPUT_OVERFLOW if out_capacity is too small; row order inside a
  * partition is implementation-defined).
  * d_ws: at least mdx_merge_workspace_bytes(nL, nR, P, key_type) bytes.
+ * (That never shrinks as a side grows: a workspace for the most rows serves
+ * fewer, at the same P and key type.)
  * ------------------------------------------------------------------------- */
 int32_t mdx_merge_workspace_bytes(int64_t n_left, int64_t n_right, int32_t P, int32_t key_type,
                                   size_t *h_bytes);

@@ -709,6 +709,26 @@ MergeLayout merge_layout(int64_t nL, int64_t nR, int32_t P, int32_t kt, bool chu
     return M;
 }
 
+// What a merge asks of its caller: its own layout and that of any merge of
+// fewer rows, so that a workspace sized for the most rows serves them all.  A
+// layout grows with both sides except where the split goes from one pass to
+// two: a one-pass merge holds the probe rows twice too, and the counts of more
+// destinations.  (A merge itself needs no more than its layout.)
+size_t merge_workspace(int64_t nL, int64_t nR, int32_t P, int32_t kt)
+{
+    const auto passes = [P](int64_t rows) { return merge_plan(rows, 0, P).q2bits > 0 ? 2 : 1; };
+    size_t most = merge_layout(nL, nR, P, kt).bytes;
+    if (passes(std::max(nL, nR)) == 2) {
+        int64_t lo = 0, hi = std::max(nL, nR);  // one pass; two
+        while (hi - lo > 1) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            (passes(mid) == 1 ? lo : hi) = mid;
+        }
+        most = std::max(most, merge_layout(std::min(nL, lo), std::min(nR, lo), P, kt).bytes);
+    }
+    return most;
+}
+
 }  // namespace
 
 int32_t mdx_merge_workspace_bytes(int64_t n_left, int64_t n_right, int32_t P, int32_t key_type,
@@ -721,7 +741,7 @@ int32_t mdx_merge_workspace_bytes(int64_t n_left, int64_t n_right, int32_t P, in
         return e;
     if (!h_bytes)
         return fail(MDX_ERR_INVALID, "mdx_merge_workspace_bytes: h_bytes is null");
-    *h_bytes = merge_layout(n_left, n_right, P, key_type).bytes;
+    *h_bytes = merge_workspace(n_left, n_right, P, key_type);
     return MDX_OK;
 }
 

@@ -8,6 +8,7 @@ validation first (the pointers are fake).
 """
 
 import ctypes
+import math
 import os
 import re
 
@@ -351,6 +352,40 @@ def test_merge_workspace_monotone_in_both_sides():
                         assert ws[i + 1][j] >= ws[i][j], (P, kt, sizes[i], sizes[j])
                     if j + 1 < len(sizes):
                         assert ws[i][j + 1] >= ws[i][j], (P, kt, sizes[i], sizes[j])
+
+
+@pytest.mark.parametrize("P", [1, 3, 5, 8, 100, 128, 200, 256, 257, 512, 600, 4096])
+@pytest.mark.parametrize("kt", [4, 8])
+def test_merge_workspace_monotone_at_one_pass(P, kt):
+    """The same where the split changes from one pass over the rows to two:
+    around every power-of-two step of the sub-bucket count up to 2048, sides as
+    uneven as they come, for a merge and for a lane's slice."""
+    steps = sorted({int(q * 0.9 * 3456) + e for q in (P << i for i in range(12)) if q <= 2048
+                    for e in (-20_000, -1, 0, 1, 2, 20_000)})
+    big = [0] + [n for n in steps if n > 0] + [10**8]
+    for query in (lambda a, b: mdx.mdx_merge_workspace_bytes(a, b, P, kt),
+                  lambda a, b: _batch_bytes([_desc(a, b, P, kt)], 1)[1]):
+        for small in (0, 1, 1000, 6452, 100_000):
+            for ws in ([query(small, n) for n in big], [query(n, small) for n in big]):
+                assert ws == sorted(ws), small
+        both = [query(n, n) for n in big]
+        assert both == sorted(both)
+
+
+def test_merge_workspace_serves_every_smaller_merge():
+    """Random merges, each within a random pair of limits."""
+    import random
+    rng = random.Random(4)
+
+    def size(top):
+        return min(top, int(math.exp(rng.uniform(0, math.log(top + 1)))))
+
+    for _ in range(4000):
+        P, kt = rng.choice([1, 2, 3, 7, 8, 16, 100, 129, 256, 300]), rng.choice([4, 8])
+        nl, nr = size(5 * 10**7), rng.choice([size(5 * 10**7), rng.randint(1_000_000, 1_800_000)])
+        most = mdx.mdx_merge_workspace_bytes(nl, nr, P, kt)
+        for a, b in ((size(nl), size(nr)), (int(nl * rng.uniform(0.8, 1)), int(nr * rng.uniform(0.8, 1)))):
+            assert mdx.mdx_merge_workspace_bytes(a, b, P, kt) <= most, (P, kt, nl, nr, a, b)
 
 
 def test_server_workspace_and_validation():
