@@ -108,12 +108,14 @@ struct Place {
     int32_t qbits;           // 2^qbits sub-buckets per partition
     int32_t by_part;         // 1: by partition, 0: by sub-bucket
 };
-// A merge has at most 2^22 sub-buckets and 2^22 further probe batches (2^34
-// rows), so the count of a partition's items never carries into its rows;
-// the rows taken are kept modulo 2^40 (a carry out of them is lost), and a
-// partition reaching 2^40 output rows (far beyond any output buffer) is
-// reported as an output overflow.
-constexpr int kDoneBits = 24;
+// A merge has at most 2^20 sub-buckets and 2^22 further probe batches, so the
+// count of a partition's items never carries into its rows; the rows taken
+// are kept modulo 2^41 (a carry out of them is lost), and a partition
+// reaching 2^41 output rows (far beyond any output buffer) is reported as an
+// output overflow.
+constexpr int kDoneBits = 23;
+static_assert((int64_t)MDX_MAX_P * kSegMaxDest + MDX_MAX_ROWS / kJoinBatch < 1ll << kDoneBits,
+              "a partition's items fit their count");
 constexpr uint64_t kDoneMask = (1ull << kDoneBits) - 1;
 constexpr uint64_t kRowsLimit = 1ull << (64 - kDoneBits);
 

@@ -329,3 +329,26 @@ def test_merge_global_join_launches(n, hot, P, dtype):
         got = dict(key=host(ok), lpay=host(ol), rpay=host(orr), off=host(off),
                    status=int(status.item()), cap=total)
         assert_join_equals_oracle(kl, vl, kr, vr, P, got)
+
+
+def test_merge_count_beyond_2_to_40_rows():
+    """Output offsets stay exact where one partition's rows, placed by cursor
+    (P = 1), pass 2^40: one build key 3456 times (a full LDS table) against the
+    same key in 3.182E8 of the probe rows and a key that is absent in 1000 more.
+    No output is written (out_capacity 0)."""
+    announce("merge of 1.1E12 output rows, counted only")
+    import torch
+
+    import paper_2101_08878_amd as mdx
+    b, m = 3456, 318_200_000
+    assert b * m > 1 << 40
+    kl = torch.full((b,), 7, dtype=torch.int32, device="cuda")
+    vl = torch.arange(b, dtype=torch.int64, device="cuda")
+    kr = torch.full((m + 1000,), 7, dtype=torch.int32, device="cuda")
+    kr[::318_000][:1000] = 9
+    vr = torch.zeros(kr.numel(), dtype=torch.int64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    *_, off = mdx.mdx_merge(kl, vl, kr, vr, 1, out_capacity=0, status=status)
+    torch.cuda.synchronize()
+    assert host(off).tolist() == [0, b * m]
+    assert int(status.item()) == mdx.MDX_DEV_OUTPUT_OVERFLOW
