@@ -1033,9 +1033,13 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
         __syncthreads();
         if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            if (atomicAdd(t.sync + kSyncStride, 1u) + 1 == t.first[step + 1])
+            if (atomicAdd(t.sync + kSyncStride, 1u) + 1 == t.first[step + 1]) {
+                // the last item of the step passes on what it has seen of the
+                // others: those who wait read only the word that it stores
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
                 __hip_atomic_store(t.sync + 2 * kSyncStride, t.first[step + 1], __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }
