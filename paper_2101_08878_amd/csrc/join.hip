@@ -1067,7 +1067,8 @@ constexpr int kCountBlock = 512;
 constexpr int kCountRows = 4;  // rows per thread loaded together
 constexpr int kCountMapBits = 12;
 constexpr int kCountMap = 1 << kCountMapBits;  // LDS map entries
-constexpr int kCountWgRows = 16384;            // a share; its counts fit 16 bits
+constexpr int kCountWgRows = 16384;            // a share
+static_assert(kCountWgRows <= 0xffff, "a share's counts fit the map's 16 bits");
 constexpr int kCountMinRows = 1024;
 constexpr int kCountFill = 384;
 
