@@ -912,13 +912,14 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
 // ---- the whole global-table join in one launch --------------------------------
 // A merge launches its global-table join always and almost never needs it:
 // ten launches that return at once cost it 20 to 25 us of 62 (1E5 x 1E5) to 88
-// (1E6 x 1E6).  Up to kOneLaunchRows they are one launch: a step's workgroups
-// are items, handed out in order by a ticket counter, and an item of a step
-// first waits until every item of the steps before it is done (they were all
-// handed out before, to running workgroups, so the wait ends).  Merges that do
-// need the join then take up to 1.6 times as long (1E6 x 1E5 with hot build
-// keys: 260 us with ten launches, 406 with one; 4E6 x 4E5: 565 and 846): every
-// item writes its L2 back.
+// (1E6 x 1E6).  Up to kOneLaunchRows, and where the probe rows are partitioned
+// again (ProbePart, up to 3.2E6 rows: those steps are here alone), they are one
+// launch: a step's workgroups are items, handed out in order by a ticket
+// counter, and an item of a step first waits until every item of the steps
+// before it is done (they were all handed out before, to running workgroups, so
+// the wait ends).  Merges that do need the join then take up to 1.6 times as
+// long (1E6 x 1E5 with hot build keys: 260 us with ten launches, 392 with one;
+// 4E6 x 4E5: 565 and 846): every item writes its L2 back.
 enum JoinStep { kPartHist, kPartScan, kPartOffsets, kPartScatter, kSetup, kInit, kSample, kInsert, kReset, kCount, kAlloc, kScatter, kProbe, kExpand,
                 kJoinSteps };
 

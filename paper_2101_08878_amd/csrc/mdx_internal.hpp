@@ -589,7 +589,8 @@ hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab
 // offsets from the first pass's (offPL[p] = offAL[p stride], offPR[p] =
 // offAR[p strideR]),
 // the table built from `build`, probed with `probe`, the output and its
-// offsets.  one: in one launch.  sync: kJoinSync zeroed counters, kSyncStride
+// offsets.  one: in one launch (for up to kOneLaunchRows rows of both sides, and
+// wherever there is a ProbePart).  sync: kJoinSync zeroed counters, kSyncStride
 // apart.
 constexpr int64_t kOneLaunchRows = (int64_t)1 << 21;
 
@@ -606,7 +607,7 @@ struct GlobalJoin {
 
 // The probe table's partition as a two-pass merge's first pass makes it, for
 // a merge split in one pass: the global-table join's output rows follow this
-// order whatever the split.  pay null: not needed, `probe` has it already.
+// order whatever the split.  off null: not needed, `probe` has it already.
 // ws: part_layout(n, d.ndest, kProbePartRows).bytes.
 constexpr int kProbePartRows = 4;
 constexpr int kProbePartMax = 256;  // destinations

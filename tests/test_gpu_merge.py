@@ -13,7 +13,7 @@ import pytest
 import oracle
 from tests.gpu_util import (announce, assert_join_equals_oracle, dev, host, require_gpu,
                             run_merge)
-from tests.helpers import part_np
+from tests.helpers import fmix64_np, part_np
 from workloads import config_inputs, edge_tables, match_fraction_tables, uniform_tables, zipf_tables
 
 pytestmark = pytest.mark.gpu
@@ -352,3 +352,31 @@ def test_merge_count_beyond_2_to_40_rows():
     torch.cuda.synchronize()
     assert host(off).tolist() == [0, b * m]
     assert int(status.item()) == mdx.MDX_DEV_OUTPUT_OVERFLOW
+
+
+@pytest.mark.parametrize("nl,nr,P,bits", [
+    (100_000, 50_000, 1, 6),         # split in one pass, as two would split it
+    (1_500_000, 1_000_000, 8, 4),    # in one pass into 512: the probe rows split again
+    (1_200_000, 1_200_000, 200, 0),  # likewise, a P that is no power of two
+    (2_000_000, 1_500_000, 3, 5),    # in two passes, and one launch per step
+])
+@pytest.mark.parametrize("dtype", [np.int64, np.int32])
+def test_merge_global_join_order(nl, nr, P, bits, dtype):
+    """The global-table join's rows follow the probe rows by partition, then the
+    top `bits` bits of the hash that a split into at most 128 has, then input
+    order, whichever way the merge was split; more than 2^21 rows among them.
+    A build key repeated 5000 times sends the merge there."""
+    announce(f"global-table join order {nl}x{nr} P={P} {np.dtype(dtype).name}")
+    rng = np.random.default_rng(nl + P)
+    kl = np.concatenate([np.full(5000, -7), rng.permutation(nl - 5000)]).astype(dtype)
+    kr = np.concatenate([np.full(3, -7), rng.integers(0, 2 * nl, nr - 3)]).astype(dtype)
+    kl, kr = kl[rng.permutation(nl)], kr[rng.permutation(nr)]
+    vl, vr = np.arange(nl, dtype=np.int64), np.arange(nr, dtype=np.int64)
+    total = oracle.join(kl, vl, kr, vr, materialize=False)["total"]
+    got = run_merge(kl, vl, kr, vr, P, cap=total)
+    assert_join_equals_oracle(kl, vl, kr, vr, P, got)
+    h = fmix64_np(kr)
+    top = (h >> np.uint64(64 - bits)).astype(np.int64) if bits else np.zeros(nr, np.int64)
+    order = np.lexsort((vr, top, part_np(kr, P)))
+    matches = np.where(kr == -7, 5000, kr < nl - 5000)
+    assert np.array_equal(got["rpay"][:total], np.repeat(vr[order], matches[order]))
