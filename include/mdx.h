@@ -530,9 +530,11 @@ int32_t mdx_transpose_sum(const double *d_x, double *d_y, int64_t n, hipStream_t
  * creates and destroys the events and keeps the arrays and the counter
  * alive while tracing.  Up to 16 kernels can be traced at once; kernel ==
  * NULL stops all tracing on the thread.  Names: "part_hist", "part_scatter",
- * "seg_hist", "seg_scatter", "rj_join", "tbl_init", "tbl_insert",
+ * "seg_hist", "seg_scatter", "rj_join", "cnt_insert", "cnt_probe", "tbl_init",
+ * "tbl_insert" (one bracket around a build's inserts, its sample's included),
  * "grp_count", "grp_alloc", "grp_scatter", "probe_chain", "probe_expand",
- * "transpose_sum".
+ * "global_join" (the tbl_*, grp_* and probe_* steps of mdx_merge in one launch,
+ * where a merge is small enough for that), "transpose_sum".
  * ------------------------------------------------------------------------- */
 int32_t mdx_trace_kernel(const char *kernel, hipEvent_t *h_starts, hipEvent_t *h_stops,
                          int32_t capacity, int32_t *h_count);

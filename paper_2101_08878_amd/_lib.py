@@ -149,7 +149,8 @@ ABI_FUNCTIONS = [
 TRACEABLE_KERNELS = ["part_hist", "part_scatter", "seg_hist", "seg_scatter", "rj_join", "cnt_insert",
                      "cnt_probe", "grp_count",
                      "grp_alloc", "grp_scatter",
-                     "tbl_init", "tbl_insert", "probe_chain", "probe_expand", "transpose_sum"]
+                     "tbl_init", "tbl_insert", "probe_chain", "probe_expand", "global_join",
+                     "transpose_sum"]
 
 
 class MdxError(RuntimeError):

@@ -1491,8 +1491,10 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
         for (int i = 0; i < kJoinSteps; ++i)
             t.first[i + 1] = t.first[i] + (uint32_t)n[i];
         const int64_t G = cap(std::max(blocks(g.n_build), blocks(g.n_probe)));
+        trace_begin("global_join", s);
         hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
                            shift, pt, pp.d, t);
+        trace_end("global_join", s);
         return hipGetLastError();
     };
     if (one)

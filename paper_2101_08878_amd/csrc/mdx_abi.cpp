@@ -171,7 +171,8 @@ int32_t mdx_trace_kernel(const char *kernel, hipEvent_t *h_starts, hipEvent_t *h
     static const char *known[] = {"part_hist",  "part_scatter", "tbl_init",    "tbl_insert",
                                   "probe_chain", "probe_expand", "seg_hist",    "seg_scatter",
                                   "rj_join",    "cnt_insert",   "cnt_probe",   "grp_count",
-                                  "grp_alloc",  "grp_scatter",  "transpose_sum"};
+                                  "grp_alloc",  "grp_scatter",  "global_join", "transpose_sum"};
+    static_assert(sizeof(known) / sizeof(*known) <= kMaxTraces, "all can be traced at once");
     bool ok = false;
     for (const char *k : known)
         ok |= std::string(k) == kernel;

@@ -380,3 +380,30 @@ def test_merge_global_join_order(nl, nr, P, bits, dtype):
     order = np.lexsort((vr, top, part_np(kr, P)))
     matches = np.where(kr == -7, 5000, kr < nl - 5000)
     assert np.array_equal(got["rpay"][:total], np.repeat(vr[order], matches[order]))
+
+
+@pytest.mark.parametrize("n,one", [(100_000, True), (2_200_000, False)])
+def test_merge_global_join_is_traced(n, one):
+    """mdx_trace_kernel brackets a merge's global-table join, as one kernel or as
+    its steps, once each."""
+    announce(f"traced global-table join, {n} rows")
+    import torch
+
+    import paper_2101_08878_amd as mdx
+    names = ["tbl_init", "tbl_insert", "grp_count", "probe_chain", "probe_expand"]
+    kl = np.concatenate([np.full(4000, -7), np.arange(n - 4000)])
+    kr = np.arange(-10, 1000)
+    traces = {k: mdx.KernelTrace(k, 4) for k in names + ["global_join"]}
+    try:
+        for t in traces.values():
+            t.start()
+        got = run_merge(kl, kl, kr, kr, 3, cap=10_000)
+        mdx.KernelTrace.stop_all()
+        assert got["off"][-1] == 4000 + 1000
+        assert {k: t.launches() for k, t in traces.items()} == \
+            {**dict.fromkeys(names, 0 if one else 1), "global_join": 1 if one else 0}
+        assert all(d > 0 for t in traces.values() for d in t.durations_ms())
+    finally:
+        mdx.KernelTrace.stop_all()
+        for t in traces.values():
+            t.close()
