@@ -479,7 +479,8 @@ struct TView {
 // ---- probe ------------------------------------------------------------------
 // Rows per thread of the probe, which walk together.  Staged build + probe of
 // n x n rows, P = 8, in us: 1, 2, 4 (8: two groups of four) rows: n = 1E5 84,
-// 89, 89, (106); 6E5 165, 148, 146, (166); 1E7 1563, 1413, 1356, (1478).
+// 89, 89, (106); 6E5 165, 148, 146, (166); 1E7 1563, 1413, 1356, (1478); all
+// on a full device's workgroups (1E5 with one per tile: 74).
 constexpr int kProbeRows = 4;
 constexpr int kProbeTile = kBlock * kProbeRows;     // 2048 rows per tile
 
