@@ -1323,7 +1323,7 @@ static int count_share(int64_t rows)
     return share;
 }
 
-// G: workgroups of the grid-stride kernels.
+// G: the most workgroups of a kernel.
 template <typename K>
 hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *status, int G,
                      hipStream_t s)
@@ -1333,8 +1333,8 @@ hipError_t run_build(const Cols &in, const TView &v, int64_t rows, int32_t *stat
     const int64_t rshares = std::max<int64_t>(1, (rows + kAggRows - 1) / kAggRows);
     const int64_t sshares =
         std::max<int64_t>(1, (2 * rows + 16 * P + kAllocSlots - 1) / kAllocSlots);
-    const unsigned Gr = (unsigned)std::min<int64_t>(rshares, device_fill_blocks());
-    const unsigned Gs = (unsigned)std::min<int64_t>(sshares, device_fill_blocks());
+    const unsigned Gr = (unsigned)std::min<int64_t>(rshares, G);
+    const unsigned Gs = (unsigned)std::min<int64_t>(sshares, G);
     const int shift = sample_shift(rows);
     trace_begin("tbl_init", s);
     hipLaunchKernelGGL(tbl_init, dim3(G), dim3(kBlock), 0, s, v);
@@ -1443,8 +1443,11 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
                            const ProbePart &pp, bool one, uint32_t *sync, hipStream_t s)
 {
     // workgroups of 2048 rows (16384 left most of the device idle at 4E6
-    // rows: 725 against 567 us), at most a full device
-    const int full = device_fill_blocks();
+    // rows: 725 against 567 us), at most four per CU, which fill it: merges that
+    // do not need the join pay for every workgroup that starts and returns
+    // (5E6 x 5E6 int32: 250 us a merge with eight, 247 with four, 246 with two;
+    // hot keys, 4E6 x 4E5: 547, 539, 559; 2.5E6 x 2.5E6: 574, 547, 588)
+    const int full = std::max(1, device_fill_blocks() / 2);
     auto blocks = [&](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, full); };
     const int shift = sample_shift(g.n_build);
     const int64_t slots = 2 * g.n_build + 16 * (int64_t)g.w_P;
