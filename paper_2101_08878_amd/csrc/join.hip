@@ -188,8 +188,9 @@ __device__ __forceinline__ bool block_any_dup(const TView &v)
 // ---- build -----------------------------------------------------------------
 
 // One block: the table's sanitized build offsets, cleared per-partition flags.
-__device__ __forceinline__ void table_setup_block(const int64_t *off_in, int64_t n, int64_t *off_tab,
-                                  int32_t *flags, int64_t *bump, int P, int64_t *scratch)
+__device__ __forceinline__ void table_setup_block(const int64_t *off_in, int64_t n,
+                                                  int64_t *off_tab, int32_t *flags, int64_t *bump,
+                                                  int P, int64_t *scratch)
 {
     if (off_in)
         sanitize_offsets(off_in, off_tab, P, n, scratch);
@@ -243,8 +244,8 @@ __global__ __launch_bounds__(kBlock) void tbl_init(TView v)
 // over distinct slots, in any order); four rows per thread at a time were
 // slower (4E6 distinct keys: 305 against 245 us).
 template <typename K>
-__device__ __forceinline__ void tbl_insert_by(const Blk &b, const Cols &in, const TView &v, int shift,
-                                              bool sample, int32_t *status)
+__device__ __forceinline__ void tbl_insert_by(const Blk &b, const Cols &in, const TView &v,
+                                              int shift, bool sample, int32_t *status)
 {
     const int64_t o0 = v.off[v.pb], n = v.off[v.pe] - o0;
     const int64_t stride = (int64_t)b.n * kBlock;
@@ -395,7 +396,8 @@ __device__ __forceinline__ int agg_insert(int64_t *mkey, int64_t s)
 }
 
 // Rows of workgroup b: [o0 + b kAggRows, ...) of the view's rows.
-__device__ __forceinline__ void agg_rows(const Blk &b, const TView &v, int64_t &o0, int64_t &r0, int64_t &r1)
+__device__ __forceinline__ void agg_rows(const Blk &b, const TView &v, int64_t &o0, int64_t &r0,
+                                         int64_t &r1)
 {
     o0 = v.off[v.pb];
     const int64_t o1 = v.off[v.pe];
@@ -405,7 +407,8 @@ __device__ __forceinline__ void agg_rows(const Blk &b, const TView &v, int64_t &
 
 // value[s] += rows of the slot's key.
 template <typename K>
-__device__ __forceinline__ void grp_count_by(const Blk &b, AggLds &lds, const Cols &in, const TView &v)
+__device__ __forceinline__ void grp_count_by(const Blk &b, AggLds &lds, const Cols &in,
+                                             const TView &v)
 {
     if (!block_any_dup(v))
         return;
@@ -533,7 +536,8 @@ __global__ __launch_bounds__(kBlock) void grp_alloc(TView v, int64_t shares)
 // rank's place in its slot's range (rows the map could not hold take a place
 // from the slot directly).  Slots and ranks stay in registers.
 template <typename K>
-__device__ __forceinline__ void grp_scatter_by(const Blk &b, AggLds &lds, const Cols &in, const TView &v)
+__device__ __forceinline__ void grp_scatter_by(const Blk &b, AggLds &lds, const Cols &in,
+                                               const TView &v)
 {
     if (!block_any_dup(v))
         return;
@@ -829,8 +833,8 @@ __device__ __forceinline__ void probe_chain_by(ChainLds &lds, const Cols &in, co
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int group, ProbeWs w, ProbeOut o,
-                                                      int32_t *status)
+__global__ __launch_bounds__(kBlock) void probe_chain(Cols in, TView v, int group, ProbeWs w,
+                                                      ProbeOut o, int32_t *status)
 {
     if (skipped(v.skip))
         return;
@@ -866,7 +870,8 @@ __device__ __forceinline__ void probe_expand_by(const Blk &b, ExpandLds &lds, in
         int held = -1;  // the tile whose row prefixes are in pre
         Deferred D = {};
         for (int64_t j = acc + (((int64_t)b.id - acc) % G + G) % G; j < acc + all; j += G) {
-            const int te = upper_index(first, 0, ne, j);  // the last tile that starts at or before j
+            // the last tile that starts at or before j
+            const int te = upper_index(first, 0, ne, j);
             if (te != held) {
                 __syncthreads();  // pre is no longer read
                 D = w.defer[e0 + te];
@@ -900,7 +905,8 @@ __device__ __forceinline__ void probe_expand_by(const Blk &b, ExpandLds &lds, in
 }
 
 template <typename K>
-__global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int group, ProbeWs w, ProbeOut o)
+__global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int group, ProbeWs w,
+                                                       ProbeOut o)
 {
     if (skipped(v.skip))
         return;
@@ -920,8 +926,23 @@ __global__ __launch_bounds__(kBlock) void probe_expand(Cols in, TView v, int gro
 // the wait ends).  Merges that do need the join then take up to 1.6 times as
 // long (1E6 x 1E5 with hot build keys: 260 us with ten launches, 392 with one;
 // 4E6 x 4E5: 565 and 846): every item writes its L2 back.
-enum JoinStep { kPartHist, kPartScan, kPartOffsets, kPartScatter, kSetup, kInit, kSample, kInsert, kReset, kCount, kAlloc, kScatter, kProbe, kExpand,
-                kJoinSteps };
+enum JoinStep {
+    kPartHist,
+    kPartScan,
+    kPartOffsets,
+    kPartScatter,
+    kSetup,
+    kInit,
+    kSample,
+    kInsert,
+    kReset,
+    kCount,
+    kAlloc,
+    kScatter,
+    kProbe,
+    kExpand,
+    kJoinSteps
+};
 
 struct JoinSteps {
     uint32_t first[kJoinSteps + 1];  // first item of every step
@@ -1057,7 +1078,8 @@ __global__ __launch_bounds__(kBlock, 4) void global_join(GlobalJoin g, Cols buil
 // table's updates, one per distinct hash and share, go at the rate of the
 // device's atomics on random lines, which more aggregation lowers (a share
 // holds 22% distinct hashes, one four times as large 16%) and fewer waves in
-// flight do not reach: 40 KB of LDS and 512 threads keep a CU's 32 waves,
+// flight do not reach: 40 KB of LDS and 512 threads keep a CU's 32 waves
+// in cnt_insert (in cnt_probe, with its sums per partition, 24),
 // 2.75 ms a count with its partitions; 32-bit counts (24 waves) 2.81; 256
 // threads 3.20, 1024 2.90; 8192 entries for 32768 rows 3.48, 2048 for 8192
 // 2.99.  Four entries' slots walked at once by each thread were slower (3.03).
@@ -1111,7 +1133,8 @@ __device__ __forceinline__ int hmap_insert(uint64_t *mkey, uint64_t h)
 {
     if (h == ~0ull)
         return -1;
-    // bits from 32 up: the partition takes the low bits, a slot's home the top ones
+    // the top bits, as a slot's home in the table: the map's order is nearly the
+    // slots' order (the partition takes the low bits)
     uint32_t i = (uint32_t)(h >> 32) >> (32 - kCountMapBits);
     for (int k = 0; k < kAggProbe; ++k) {
         uint64_t cur = mkey[i];
@@ -1159,8 +1182,9 @@ __device__ __forceinline__ void slot_add(const TView &v, int64_t o0, int p, uint
     }
 }
 
-// Rows [r0, r1) of the workgroup's share, kCountRows per thread loaded together; fn(row, hash, partition) for every row in its
-// partition, the others reported.
+// Rows [r0, r1) of the workgroup's share, kCountRows per thread loaded
+// together; fn(hash, partition) for every row in its partition, the others
+// reported.
 template <typename K, typename Fn>
 __device__ __forceinline__ void count_rows(const K *__restrict__ keys, const int64_t *off, int P,
                                            const Dest &d, int64_t r0, int64_t r1, int32_t *status,
@@ -1213,8 +1237,8 @@ __global__ __launch_bounds__(kBlock) void cnt_setup(const int64_t *__restrict__ 
 }
 
 template <typename K>
-__global__ __launch_bounds__(kCountBlock) void cnt_insert(const K *__restrict__ keys, TView v, int share,
-                                                     int32_t *status)
+__global__ __launch_bounds__(kCountBlock) void cnt_insert(const K *__restrict__ keys, TView v,
+                                                          int share, int32_t *status)
 {
     __shared__ CountMap map;
     map.clear();
@@ -1371,8 +1395,8 @@ hipError_t run_probe_group(const Cols &in, const TView &v, int group,
     // probe row: it always gets a full device (it returns at once when no
     // tile deferred rows).
     trace_begin("probe_expand", s);
-    hipLaunchKernelGGL((probe_expand<K>), dim3(device_fill_blocks()), dim3(kBlock), 0, s, in, v, group,
-                       w, o);
+    hipLaunchKernelGGL((probe_expand<K>), dim3(device_fill_blocks()), dim3(kBlock), 0, s, in, v,
+                       group, w, o);
     trace_end("probe_expand", s);
     return hipGetLastError();
 }
@@ -1449,8 +1473,19 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
     // hot keys, 4E6 x 4E5: 547, 539, 559; 2.5E6 x 2.5E6: 574, 547, 588)
     const int full = std::max(1, device_fill_blocks() / 2);
     auto blocks = [&](int64_t rows) { return (int)std::min<int64_t>((rows >> 11) + 1, full); };
-    const int shift = sample_shift(g.n_build);
-    const int64_t slots = 2 * g.n_build + 16 * (int64_t)g.w_P;
+    if (!one) {
+        hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, g);
+        hipError_t e = run_build<K>(build, g.v, g.n_build, g.status, blocks(g.n_build), s);
+        if (e != hipSuccess)
+            return e;
+        return run_probe_group<K>(probe, g.v, 0, g.w, g.o, g.status, blocks(g.n_probe), s);
+    }
+    // All steps in one launch on at most kMost workgroups.  The ticket and the
+    // count of done items are one address each, so more workgroups make every
+    // step's end longer (1E6 rows: 506 us with 512 of them, 406 with 256, 445
+    // with 128).
+    constexpr int64_t kMost = 256;
+    auto cap = [&](int64_t items) { return std::min(items, kMost); };
     PartTable<K> pt = {};
     if (pp.off) {
         const PartLayout L = part_layout(pp.n, pp.d.ndest, kProbePartRows);
@@ -1463,50 +1498,38 @@ hipError_t run_global_join(const Cols &build, const Cols &probe, const GlobalJoi
         pt.cnt = (int64_t *)((char *)pp.ws + L.cnt_off);
         pt.totals = (int64_t *)((char *)pp.ws + L.totals_off);
     }
+    const int shift = sample_shift(g.n_build);
+    const int64_t slots = 2 * g.n_build + 16 * (int64_t)g.w_P;
     JoinSteps t;
+    t.sync = sync;
     t.shares_rows = std::max<int64_t>(1, (g.n_build + kAggRows - 1) / kAggRows);
     t.shares_slots = std::max<int64_t>(1, (slots + kAllocSlots - 1) / kAllocSlots);
-    // All steps in one launch on at most `most` workgroups.  The ticket and
-    // the count of done items are one address each, so more workgroups make
-    // every step's end longer (1E6 rows: 506 us with 512 of them, 406 with
-    // 256, 445 with 128).
-    auto run = [&](int64_t most) {
-        auto cap = [&](int64_t items) { return std::min<int64_t>(items, most); };
-        const int64_t again = pp.off ? 1 : 0;
-        // (the expansion's work is the output rows, which can be many for few
-        // probe rows)
-        const int64_t n[kJoinSteps] = {cap(pt.ntiles),
-                                       again * ((pp.d.ndest + kWavesPerBlock - 1) / kWavesPerBlock),
-                                       again,
-                                       cap(pt.ntiles),
-                                       1,
-                                       cap(blocks(slots)),
-                                       shift >= 0 ? kSampleBlocks : 0,
-                                       cap(blocks(g.n_build)),
-                                       cap(blocks(slots)),
-                                       cap(t.shares_rows),
-                                       cap(t.shares_slots),
-                                       cap(t.shares_rows),
-                                       cap(blocks(g.n_probe)),
-                                       most};
-        t.sync = sync;
-        t.first[0] = 0;
-        for (int i = 0; i < kJoinSteps; ++i)
-            t.first[i + 1] = t.first[i] + (uint32_t)n[i];
-        const int64_t G = cap(std::max(blocks(g.n_build), blocks(g.n_probe)));
-        trace_begin("global_join", s);
-        hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
-                           shift, pt, pp.d, t);
-        trace_end("global_join", s);
-        return hipGetLastError();
-    };
-    if (one)
-        return run(256);
-    hipLaunchKernelGGL(fallback_setup, dim3(1), dim3(kBlock), 0, s, g);
-    hipError_t e = run_build<K>(build, g.v, g.n_build, g.status, blocks(g.n_build), s);
-    if (e != hipSuccess)
-        return e;
-    return run_probe_group<K>(probe, g.v, 0, g.w, g.o, g.status, blocks(g.n_probe), s);
+    const int64_t again = pp.off ? 1 : 0;
+    // (the expansion's work is the output rows, which can be many for few probe
+    // rows)
+    const int64_t n[kJoinSteps] = {cap(pt.ntiles),
+                                   again * ((pp.d.ndest + kWavesPerBlock - 1) / kWavesPerBlock),
+                                   again,
+                                   cap(pt.ntiles),
+                                   1,
+                                   cap(blocks(slots)),
+                                   shift >= 0 ? kSampleBlocks : 0,
+                                   cap(blocks(g.n_build)),
+                                   cap(blocks(slots)),
+                                   cap(t.shares_rows),
+                                   cap(t.shares_slots),
+                                   cap(t.shares_rows),
+                                   cap(blocks(g.n_probe)),
+                                   kMost};
+    t.first[0] = 0;
+    for (int i = 0; i < kJoinSteps; ++i)
+        t.first[i + 1] = t.first[i] + (uint32_t)n[i];
+    const int64_t G = cap(std::max(blocks(g.n_build), blocks(g.n_probe)));
+    trace_begin("global_join", s);
+    hipLaunchKernelGGL((global_join<K>), dim3((unsigned)G), dim3(kBlock), 0, s, g, build, probe,
+                       shift, pt, pp.d, t);
+    trace_end("global_join", s);
+    return hipGetLastError();
 }
 
 hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_bytes,
@@ -1527,15 +1550,13 @@ hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const Pr
     return hipGetLastError();
 }
 
-hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
-                              const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
-                              int32_t *status, hipStream_t s)
+hipError_t launch_probe_group(const Cols &table, int key_bytes, const TView &v, int group,
+                              const ProbeWs &w, const ProbeOut &o, int32_t *status, hipStream_t s)
 {
     // A workgroup for every tile, at most a full device: one without a tile only
     // takes a ticket, and those of a full device, made one after the other at one
     // address, set the time of a small probe (build and probe of 1E4 x 3333 rows
     // 70 us, so 53).
-    (void)P;
     const int G = (int)std::min<int64_t>(device_fill_blocks(), w.max_tiles);
     if (key_bytes == 8)
         return run_probe_group<int64_t>(table, v, group, w, o, status, G, s);

@@ -487,7 +487,7 @@ int32_t mdx_join_probe(const mdx_table *h_table, const void *d_keys, const int64
     o.offsets = d_out_offsets;
     hipError_t e = launch_probe_plan(d_offsets, n, P, w, d_out_offsets, stream);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt, P,
+        e = launch_probe_group(cols_of(d_keys, d_payload, kt), kt,
                                make_view(t, t.d_offsets, 0, P), 0, w, o, d_status, stream);
     return e == hipSuccess ? MDX_OK : hip_fail(e, W);
 }
@@ -613,11 +613,12 @@ struct MergePlan {
     int qpbits;  // q1bits of a two-pass split: the order of the global-table join's output
 };
 
-// fill: average rows of the larger side per sub-bucket, as a fraction of a
-// table of `cap` rows (the join's table: the fused batch's holds more rows);
-// fanout: the first pass's largest number of destinations.
 constexpr int kOnePass = 512;
 
+// fill: average rows of the larger side per sub-bucket, as a fraction of a
+// table of `cap` rows (the join's table: the fused batch's holds more rows);
+// fanout: the first pass's largest number of destinations; one_pass: the most
+// sub-buckets that the first pass makes alone.
 MergePlan merge_plan(int64_t nL, int64_t nR, int32_t P, double fill = kJoinFill, int fanout = 128,
                      int cap = kJoinCap, int one_pass = kOnePass)
 {
@@ -658,7 +659,8 @@ struct MergeLayout {
     TableLayout tl;
     ProbeLayout ql;
     size_t partL_off, partR_off, l1_off, r1_off, offAL_off, offAR_off, offPL_off, offPR_off,
-        digL_off, digR_off, segL_off, segR_off, l2_off, r2_off, partP_off, offP_off, subL_off, subR_off, rjoin_off, table_off, probe_off, bytes;
+        digL_off, digR_off, segL_off, segR_off, l2_off, r2_off, partP_off, offP_off, subL_off,
+        subR_off, rjoin_off, table_off, probe_off, bytes;
 };
 
 // chunked: the merge joins oversized build sub-buckets in chunks and has no
@@ -807,7 +809,8 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     const PartArgs pt[2] = {
         {d.d_left_keys, d.d_left_payload, n_left, l1, nullptr, offAL, digL, b + M.partL_off},
         {d.d_right_keys, d.d_right_payload, n_right, r1, nullptr, offAR, digR, b + M.partR_off}};
-    hipError_t e = launch_partition(pt, 2, key_type, P, pl.q1bits, true, pl.q1bits, pl.q2bits, stream);
+    hipError_t e =
+        launch_partition(pt, 2, key_type, P, pl.q1bits, true, pl.q1bits, pl.q2bits, stream);
 
     // 2. split every first-pass bucket by the next q2bits: sub-buckets
     const void *lrows = l1, *rrows = r1;
@@ -829,7 +832,7 @@ static hipError_t enqueue_merge(const mdx_merge_desc &d, void *d_ws, hipStream_t
     if (e == hipSuccess)
         e = launch_rjoin_plan(subL, subR, M.S, jw, chunked, d_status, stream);
     if (e == hipSuccess)
-        e = launch_rjoin(lrows, n_left, subL, rrows, n_right, subR, key_type, P, pl.qbits, jw, o,
+        e = launch_rjoin(lrows, n_left, subL, rrows, n_right, subR, key_type, pl.qbits, jw, o,
                          d_status, chunked, stream);
 
     // 4. otherwise (a sub-bucket too large for LDS: heavy key repetition),
@@ -1390,8 +1393,10 @@ int32_t mdx_batch_create(int32_t count, const mdx_merge_desc *h_descs,
             uint8_t *digR = two ? (uint8_t *)(b + f.digR) : nullptr;
             int64_t *offAL = (int64_t *)(b + f.offAL), *offAR = (int64_t *)(b + f.offAR);
             const PartArgs pt[2] = {
-                {d.d_left_keys, d.d_left_payload, d.n_left, b + f.l1, nullptr, offAL, digL, b + f.partL},
-                {d.d_right_keys, d.d_right_payload, d.n_right, b + f.r1, nullptr, offAR, digR, b + f.partR}};
+                {d.d_left_keys, d.d_left_payload, d.n_left, b + f.l1, nullptr, offAL, digL,
+                 b + f.partL},
+                {d.d_right_keys, d.d_right_payload, d.n_right, b + f.r1, nullptr, offAR, digR,
+                 b + f.partR}};
             part_rec(pt, f.kt, d.P, f.plan.q1bits, f.R, f.plan.q1bits, f.plan.q2bits,
                      B->h_image + u.part_off + j * part_rec_bytes());
             JoinRec jr = {};
@@ -1778,8 +1783,8 @@ int32_t mdx_server_submit_probe(mdx_server *srv, const mdx_table *h_table,
     if (e == hipSuccess)
         e = launch_probe_plan(poff, d.n, P, w, o.offsets, st);
     if (e == hipSuccess)
-        e = launch_probe_group(cols_of(pk, pv, kt), kt, P, make_view(t, t.d_offsets, 0, P), 0, w,
-                               o, d.d_status, st);
+        e = launch_probe_group(cols_of(pk, pv, kt), kt, make_view(t, t.d_offsets, 0, P), 0, w, o,
+                               d.d_status, st);
     if (e == hipSuccess)
         e = hipEventRecord(srv->done[(size_t)sl], st);
     if (e != hipSuccess)

@@ -159,7 +159,8 @@ inline size_t part_reserve_bytes(int64_t n, int32_t ndest, int key_bytes)
     const int top = part_rows_per_thread((int64_t)1 << 40, ndest, key_bytes);
     size_t most = 0;
     for (int R = 2; R <= top; R *= 2) {
-        const int64_t below = kFillTiles * kBlock * 2 * R;  // rows from which larger tiles are taken
+        // rows from which larger tiles are taken
+        const int64_t below = kFillTiles * kBlock * 2 * R;
         const int64_t rows = R < top && n > below ? below : n;
         most = std::max(most, part_layout(rows, ndest, R).bytes);
     }
@@ -187,10 +188,11 @@ inline size_t part_workspace_bytes(int64_t n, int32_t P, int key_bytes)
 
 // One table of a partition launch: stable partition into
 // make_dest(P, sbits).ndest destinations; off has ndest + 1 entries; ws holds
-// part_layout(n, ndest, R).bytes, R = part_rows_per_thread of all the tables' rows.  The output is two columns, or with `rows_out`
-// Rows<K> at keys_out (pay_out is null).  With dig (n bytes, rows
-// only), every output row's digit_of(h, dshift, dbits) is written beside it,
-// for the histogram of a following segmented pass.
+// part_layout(n, ndest, R).bytes, R = part_rows_per_thread of all the tables'
+// rows.  The output is two columns, or with `rows_out` Rows<K> at keys_out
+// (pay_out is null).  With dig (n bytes, rows only), every output row's
+// digit_of(h, dshift, dbits) is written beside it, for the histogram of a
+// following segmented pass.
 struct PartArgs {
     const void *keys;
     const int64_t *pay;
@@ -210,7 +212,7 @@ hipError_t launch_partition(const PartArgs *tables, int ntables, int key_bytes, 
 
 // ---- segmented partition (second split of the join) -------------------------
 // Segment a (rows [segoff[a], segoff[a+1]) of an already partitioned table of
-// Rows<K>) // is split stably into 2^bits destinations by digit_of(h, shift, bits);
+// Rows<K>) is split stably into 2^bits destinations by digit_of(h, shift, bits);
 // destination (a, q) lands at [outoff[a 2^bits + q], outoff[a 2^bits + q + 1]).
 #ifndef MDX_SEG_ROWS
 #define MDX_SEG_ROWS 8
@@ -588,8 +590,7 @@ hipError_t launch_table_setup(const int64_t *off_in, int64_t n, int64_t *off_tab
 
 // A merge's global-table join: nothing when *v.skip, else per-partition
 // offsets from the first pass's (offPL[p] = offAL[p stride], offPR[p] =
-// offAR[p strideR]),
-// the table built from `build`, probed with `probe`, the output and its
+// offAR[p strideR]), the table built from `build`, probed with `probe`, the output and its
 // offsets.  one: in one launch (for up to kOneLaunchRows rows of both sides, and
 // wherever there is a ProbePart).  sync: kJoinSync zeroed counters, kSyncStride
 // apart.
@@ -632,9 +633,8 @@ hipError_t launch_global_join(const Cols &build, const Cols &probe, int key_byte
 // its offsets.
 hipError_t launch_probe_plan(const int64_t *offR, int64_t n, int32_t P, const ProbeWs &w,
                              int64_t *offsets, hipStream_t s);
-hipError_t launch_probe_group(const Cols &table, int key_bytes, int32_t P,
-                              const TView &v, int group, const ProbeWs &w, const ProbeOut &o,
-                              int32_t *status, hipStream_t s);
+hipError_t launch_probe_group(const Cols &table, int key_bytes, const TView &v, int group,
+                              const ProbeWs &w, const ProbeOut &o, int32_t *status, hipStream_t s);
 
 // Count-only join of two partitioned tables (full views, pb = 0, pe = P):
 // per-partition output counts into out_offsets (exclusive prefix, total at
@@ -654,9 +654,9 @@ hipError_t launch_join_count(const void *lk, const int64_t *lofs, int64_t n_buil
 hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S,
                              const RJoinWs &w, bool chunked, int32_t *status, hipStream_t s);
 hipError_t launch_rjoin(const void *lrows, int64_t nL, const int64_t *subL, const void *rrows,
-                        int64_t nR, const int64_t *subR, int key_bytes, int32_t P,
-                        int qbits, const RJoinWs &w, const ProbeOut &o, int32_t *status,
-                        bool chunked, hipStream_t s);
+                        int64_t nR, const int64_t *subR, int key_bytes, int qbits,
+                        const RJoinWs &w, const ProbeOut &o, int32_t *status, bool chunked,
+                        hipStream_t s);
 // Radix join of every merge of a batch (one key width): record m describes
 // merge m (its S sub-buckets, its chained scan jstatus of S entries and
 // cursors jcursor of P, output); Spre [M + 1] prefix of the merges' S in device memory, S its

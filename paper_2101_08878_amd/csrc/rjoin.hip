@@ -30,8 +30,8 @@
 // Latency hiding: two workgroups per CU, one running while the other waits
 // on the dependent steps of its sub-bucket; inside a sub-bucket the loads
 // are issued in the order they are needed (count_one_batch), and the hash
-// chains of a thread's probe rows are walked four at a time without
-// branches, so that their LDS reads are in flight together.
+// chains of a thread's probe rows are walked two (the fused batch: four) at a
+// time without branches, so that their LDS reads are in flight together.
 #include <algorithm>
 
 #include "mdx.h"
@@ -182,8 +182,9 @@ static_assert(kPlanChunk == (int64_t)kBlock * kPlanPer, "chunks of rj_plan");
 // the items.  The items are counted with consecutive lanes on consecutive
 // sub-buckets; the prefix is formed only when some sub-bucket has several.
 template <int PER>
-__device__ __forceinline__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR, int64_t s0, int m,
-                               uint32_t *pre, int64_t *scratch, bool &over)
+__device__ __forceinline__ int64_t plan_prefix(const int64_t *subL, const int64_t *subR,
+                                               int64_t s0, int m, uint32_t *pre,
+                                               int64_t *scratch, bool &over)
 {
     const int tid = threadIdx.x;
     int64_t nb[PER], nr[PER];
@@ -547,8 +548,8 @@ struct JoinLds {
 // their keys (needed only to write the output).
 template <class G, typename K>
 __device__ __forceinline__ void count_one_batch(Rows<K> lrows, int64_t bL,
-                                                int64_t nb, Rows<K> rrows,
-                                                int64_t bR, int64_t eR, const JoinLds &L, K *kk, int64_t *vv,
+                                                int64_t nb, Rows<K> rrows, int64_t bR,
+                                                int64_t eR, const JoinLds &L, K *kk, int64_t *vv,
                                                 uint32_t *mf)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -782,8 +783,8 @@ __attribute__((amdgpu_waves_per_eu(kJoinSimdWaves, kJoinSimdWaves))) void rj_joi
         const int64_t bL = subL[s];
         const Rows<K> lrows = make_rows<K>(r.lrows, r.nL), rrows = make_rows<K>(r.rrows, r.nR);
         const Place pl = {r.jcursor, r.jstatus, nullptr, r.S, r.o.offsets, r.qbits, r.by_part};
-        join_item<BatchJoin, K, true>(lrows, bL, subL[s + 1] - bL, rrows, subR[s], subR[s + 1], pl, s, s, true,
-                                      cp, cb, r.o, r.status, L);
+        join_item<BatchJoin, K, true>(lrows, bL, subL[s + 1] - bL, rrows, subR[s], subR[s + 1], pl,
+                                      s, s, true, cp, cb, r.o, r.status, L);
         __syncthreads();  // the table is reused by the next sub-bucket
     }
 }
@@ -869,8 +870,9 @@ hipError_t launch_rjoin_plan(const int64_t *subL, const int64_t *subR, int64_t S
 
 template <typename K>
 void launch_rjoin_kernel(int G, const void *lrows, int64_t nL, const int64_t *subL,
-                         const void *rrows, int64_t nR, const int64_t *subR, const RJoinWs &w, int qbits, const ProbeOut &o,
-                         int32_t *status, bool chunked, hipStream_t s)
+                         const void *rrows, int64_t nR, const int64_t *subR, const RJoinWs &w,
+                         int qbits, const ProbeOut &o, int32_t *status, bool chunked,
+                         hipStream_t s)
 {
     const int by_part = rjoin_by_partition(qbits, rjoin_grid(w.S)) ? 1 : 0;
     const auto fn = chunked ? rj_join<K, true> : rj_join<K, false>;
@@ -880,17 +882,13 @@ void launch_rjoin_kernel(int G, const void *lrows, int64_t nL, const int64_t *su
 }
 
 hipError_t launch_rjoin(const void *lrows, int64_t nL, const int64_t *subL, const void *rrows,
-                        int64_t nR, const int64_t *subR, int key_bytes, int32_t P, int qbits,
+                        int64_t nR, const int64_t *subR, int key_bytes, int qbits,
                         const RJoinWs &w, const ProbeOut &o, int32_t *status, bool chunked,
                         hipStream_t s)
 {
-    (void)P;
-    const int G = rjoin_grid(w.max_items);
+    const auto run = key_bytes == 8 ? launch_rjoin_kernel<int64_t> : launch_rjoin_kernel<int32_t>;
     trace_begin("rj_join", s);
-    if (key_bytes == 8)
-        launch_rjoin_kernel<int64_t>(G, lrows, nL, subL, rrows, nR, subR, w, qbits, o, status, chunked, s);
-    else
-        launch_rjoin_kernel<int32_t>(G, lrows, nL, subL, rrows, nR, subR, w, qbits, o, status, chunked, s);
+    run(rjoin_grid(w.max_items), lrows, nL, subL, rrows, nR, subR, w, qbits, o, status, chunked, s);
     trace_end("rj_join", s);
     return hipGetLastError();
 }

@@ -90,8 +90,8 @@ constexpr int64_t kStreamBytes = (int64_t)384 << 20;
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 template <bool STREAM>
-__global__ __launch_bounds__(kBThreads) void transpose_sum_big(const double *x, double *y, int64_t n,
-                                                               int64_t T)
+__global__ __launch_bounds__(kBThreads) void transpose_sum_big(const double *x, double *y,
+                                                               int64_t n, int64_t T)
 {
     __shared__ double t[kBT][kBT + 1];
     int64_t I, J;
@@ -156,7 +156,8 @@ hipError_t launch_transpose_sum(const double *x, double *y, int64_t n, hipStream
         return hipSuccess;
     const int64_t B = (n + kBT - 1) / kBT, big = B * (B + 1) / 2;
     if (big >= kBigPairs && n % 2 == 0 && ((uintptr_t)x | (uintptr_t)y) % 16 == 0) {
-        const auto fn = 8 * n * n > kStreamBytes ? transpose_sum_big<true> : transpose_sum_big<false>;
+        const auto fn =
+            8 * n * n > kStreamBytes ? transpose_sum_big<true> : transpose_sum_big<false>;
         trace_begin("transpose_sum", s);
         hipLaunchKernelGGL(fn, dim3((unsigned)big), dim3(kBThreads), 0, s, x, y, n, B);
         trace_end("transpose_sum", s);
