@@ -342,20 +342,23 @@ __global__ __launch_bounds__(kBlock) void rj_plan_one(const int64_t *__restrict_
 // This thread's rows of the batch starting at rb (the same on every lane),
 // up to re (rb < re): rb + j kJoinThreads + tid.  Rows past re load the
 // batch's last row instead (no branch per load) and are ignored by the
-// callers, which check r < re.
-template <typename K>
+// callers, which check r < re.  KEYS: only what holds the keys (int64 rows
+// come whole).
+template <bool KEYS, typename K>
 __device__ __forceinline__ void load_batch(Rows<K> rrows, int64_t rb, int64_t re,
                                            K *kk, int64_t *vv)
 {
     const Rows<K> b = rrows.from(rb);
     const int64_t left = re - rb;
     const uint32_t last = (uint32_t)((left < kJoinBatch ? left : kJoinBatch) - 1);
-    b.template load<kJoinRows>(
-        [&](int j) {
-            const uint32_t r = (uint32_t)(j * kJoinThreads) + threadIdx.x;
-            return r < last ? r : last;
-        },
-        kk, vv);
+    const auto index = [&](int j) {
+        const uint32_t r = (uint32_t)(j * kJoinThreads) + threadIdx.x;
+        return r < last ? r : last;
+    };
+    if (KEYS)
+        b.template load_keys<kJoinRows>(index, kk, vv);
+    else
+        b.template load<kJoinRows>(index, kk, vv);
 }
 
 // Per row: the number of matches (high 16 bits; at most G::cap) and the
@@ -613,7 +616,7 @@ __device__ __forceinline__ void join_item(Rows<K> lrows, int64_t bL, int64_t nb,
             build_table<G>(lrows, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
                            L.head);
             for (int64_t b = bR; b < eR; b += kJoinBatch) {
-                load_batch(rrows, b, eR, kk, vv);
+                load_batch<true>(rrows, b, eR, kk, vv);
                 match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
                 cell_sums(mf, L.cw, lane, wv);
                 __syncthreads();
@@ -654,10 +657,11 @@ __device__ __forceinline__ void join_item(Rows<K> lrows, int64_t bL, int64_t nb,
     int64_t run = E;
     for (int64_t c0 = 0; c0 < nb; c0 += kCap) {
         __syncthreads();  // s_total has been read, the last chunk's table used
-        build_table<G>(lrows, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
-                       L.head);
+        if (nb > kCap)    // (a single table is still there)
+            build_table<G>(lrows, bL + c0, nb - c0 < kCap ? nb - c0 : kCap, L.tkey, L.tp, L.tn,
+                           L.head);
         for (int64_t b = bR; b < eR; b += kJoinBatch) {
-            load_batch(rrows, b, eR, kk, vv);
+            load_batch<false>(rrows, b, eR, kk, vv);
             match_batch<G>(b, eR, L.tkey, L.tn, L.head, kk, mf);
             cell_sums(mf, L.cw, lane, wv);
             __syncthreads();

@@ -205,6 +205,33 @@ def test_fused_batch_one_key_at_table_size():
     fb.close()
 
 
+def test_fused_batch_hot_probe_key():
+    """A probe key repeated around multiples of a probe batch (4096 rows), whose
+    sub-bucket one workgroup joins batch by batch, its build side one table
+    (counted and written from the same one) or several."""
+    import paper_2101_08878_amd as mdx
+    announce("fused batch hot probe key")
+    rng = np.random.default_rng(17)
+    items = []
+    for dtype in (np.int64, np.int32):
+        for hot in (4096, 4097, 8193, 40_961):
+            for extra in (0, 5, 3900):  # further build rows of the hot key
+                kl = np.concatenate([rng.permutation(20_000), np.full(extra, 31)])
+                kr = np.concatenate([np.full(hot if extra < 3900 else 4097, 31),
+                                     rng.integers(0, 40_000, 9000)])
+                kl, kr = (rng.permutation(k).astype(dtype) for k in (kl, kr))
+                items.append((kl, np.arange(kl.size, dtype=np.int64), kr,
+                              np.arange(kr.size, dtype=np.int64), 3))
+            if hot > 4096:
+                items.pop()
+    jobs = _jobs(items)
+    fb = mdx.FusedBatch(jobs)
+    fb.run()
+    torch.cuda.synchronize()
+    _check(items, jobs)
+    fb.close()
+
+
 def test_fused_batch_graph_replays():
     """The batch captured into a graph (the plan's copy to the device and
     every launch); three replays with eager clearing in between, each checked
