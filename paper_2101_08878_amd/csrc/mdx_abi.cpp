@@ -596,7 +596,7 @@ namespace {
 
 // How mdx_merge splits partitions into sub-buckets for the radix join: each
 // partition into Q = 2^qbits sub-buckets by the top hash bits, sized so that
-// an average sub-bucket of the larger side fills ~80% of an LDS table: the
+// an average sub-bucket of the larger side fills at most 90% of an LDS table: the
 // build side's rows must fit the table, and the probe side's should fit one
 // probe batch (with sub-buckets sized by a small build side alone, a large
 // probe side would leave a few workgroups looping over many batches each).
