@@ -360,7 +360,7 @@ int32_t mdx_merge_batch(int32_t count, const mdx_merge_desc *h_descs, int32_t la
  * owns a range of the launch's workgroups, found from a prefix of the
  * merges' block counts), and the join's workgroups take sub-buckets of all
  * merges from one ticket counter.  A batch of thousands of merges is then
- * about a dozen launches per wave instead of twenty per merge.
+ * about a dozen launches per wave instead of six to twenty-one per merge.
  *
  * Merge i computes the rows and offsets mdx_merge computes with the same
  * descriptor (row order inside a partition is implementation-defined, as
